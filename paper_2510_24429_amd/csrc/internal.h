@@ -21,7 +21,14 @@ constexpr int kWG = 256;          // threads per workgroup (4 wave64s)
 constexpr int kTile64 = PDHG_TILE64;  // nonzeros staged per multi-row block, FP64
 constexpr int kTile32 = PDHG_TILE32;  // same, FP32 (same LDS bytes)
 constexpr int kMaxLevels = 32;
-constexpr int kRedBlocks = 512;   // blocks per side of the KKT reduction
+constexpr int kRedBlocks = 1024;  // most blocks of a reduction (KKT: per side)
+
+// Blocks of a reduction over k entries: two per lane and round, one round as
+// long as that needs no more than kRedBlocks (4 workgroups per CU).
+inline int red_blocks(int64_t k) {
+    const int64_t b = (k + 2 * kWG - 1) / (2 * kWG);
+    return (int)(b < 1 ? 1 : b > kRedBlocks ? kRedBlocks : b);
+}
 
 // One workgroup's share of a CSR SpMV.  Rows [r0, r1) of one matrix:
 //  - several rows (r1 - r0 > 1): their nonzeros (<= tile) are streamed
@@ -212,8 +219,9 @@ void launch_kkt_reduce(int ncand, const void *x0, const void *y0,
                        const double *cs, const double *ls, const double *dr,
                        const double *dc, int64_t m, int64_t n,
                        double *partial, hipStream_t s);
-void launch_control(State *st, const double *partial, int ncand, int batch,
-                    int initial, double *log, hipStream_t s);
+void launch_control(State *st, const double *partial, int64_t m, int64_t n,
+                    int ncand, int batch, int initial, double *log,
+                    hipStream_t s);
 // When the evaluation asked for a polishing attempt: the candidate it chose,
 // unscaled (D_c x, D_r y) in FP64, into xs / ys (before any restart moves it).
 void launch_polish_stash(const State *st, bool f32, const void *x0,

@@ -169,10 +169,9 @@ struct PrimalEpi {
     T tau;
     T t;
     __device__ __forceinline__ bool begin() {
-        if (st->status != PDHG_RUNNING) return false;
         tau = (T)st->tau;
         t = (T)(double)(st->t_base + off + 1);
-        return true;
+        return st->status == PDHG_RUNNING;
     }
     struct Pre {
         T x, c, l, xb;
@@ -200,10 +199,9 @@ struct DualEpi {
     T sigma;
     T t;
     __device__ __forceinline__ bool begin() {
-        if (st->status != PDHG_RUNNING) return false;
         sigma = (T)st->sigma;
         t = (T)(double)(st->t_base + off + 1);
-        return true;
+        return st->status == PDHG_RUNNING;
     }
     struct Pre {
         T y, b, a, yb;
@@ -232,12 +230,11 @@ struct PrimalHalpernEpi {
     int off;
     T tau, lam, rho;
     __device__ __forceinline__ bool begin() {
-        if (st->status != PDHG_RUNNING) return false;
         tau = (T)st->tau;
         const double t = (double)(st->t_base + off + 1);
         lam = (T)(t / (t + 1.0));
         rho = (T)st->reflect;
-        return true;
+        return st->status == PDHG_RUNNING;
     }
     struct Pre {
         T x, c, l, x0;
@@ -266,12 +263,11 @@ struct DualHalpernEpi {
     int off;
     T sigma, lam, rho;
     __device__ __forceinline__ bool begin() {
-        if (st->status != PDHG_RUNNING) return false;
         sigma = (T)st->sigma;
         const double t = (double)(st->t_base + off + 1);
         lam = (T)(t / (t + 1.0));
         rho = (T)st->reflect;
-        return true;
+        return st->status == PDHG_RUNNING;
     }
     struct Pre {
         T a, y, b, y0, a0;
@@ -377,11 +373,16 @@ __global__ __launch_bounds__(kWG) void k_rowblock(
     __shared__ int s_rp[TILE + 1];
     __shared__ Acc s_red[4];
     Epi epi = epi_in;
-    if (!epi.begin()) return;
+    // the control state and the descriptor are loaded together, and a
+    // multi-row block issues its streamed loads before it looks at the state:
+    // one memory latency less in a chain of four, which is what a launch over
+    // a small matrix costs
     const RowBlock b = blks[blockIdx.x];
+    const bool live = epi.begin();
     if (b.r1 == b.r0) return;         // padding of an XCD queue
     const int tid = threadIdx.x;
     if (b.r1 - b.r0 == 1) {
+        if (!live) return;
         // one row: the workgroup strides it in aligned groups of four
         // nonzeros per lane (16-byte index and value loads), two groups in
         // flight; entries outside [p0, p1) are masked and never gathered
@@ -449,6 +450,7 @@ __global__ __launch_bounds__(kWG) void k_rowblock(
             const int base = a0 + 4 * (tid + g * kWG);
             if (base < p0 + nz) elem.fetch4(base, jj[g], aa[g]);
         }
+        if (!live) return;
 #pragma unroll
         for (int g = 0; g < G4; ++g) {
             const int base = a0 + 4 * (tid + g * kWG);
@@ -775,118 +777,193 @@ struct KktArgs {
     const double *ax[2], *aty[2];
     const double *bs, *cs, *ls, *dr, *dc;
     int64_t m, n;
-    int ncand;
 };
 
-// Blocks [0, kRedBlocks) reduce over rows, [kRedBlocks, 2 kRedBlocks) over
-// columns.  Per candidate c and quantity q the block writes its partial to
-// partial[(c * Q_NQ + q) * 2 kRedBlocks + block].
+// Two consecutive entries of a vector as one load (the vectors are whole
+// allocations, so even entries are aligned); past the end the second is 0.
+typedef float v2f __attribute__((ext_vector_type(2)));
 template <typename T>
-__global__ __launch_bounds__(kWG) void k_kkt(KktArgs<T> a,
-                                            double *__restrict__ partial) {
-    __shared__ double s_red[4];
-    double acc[2][Q_NQ];
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int q = 0; q < Q_NQ; ++q) acc[c][q] = 0.0;
-    const int blk = blockIdx.x;
-    const int64_t stride = (int64_t)kRedBlocks * kWG;
-    if (blk < kRedBlocks) {
-        for (int64_t i = (int64_t)blk * kWG + threadIdx.x; i < a.m; i += stride) {
-            const double bi = a.bs[i], dri = a.dr[i], yli = (double)a.yl[i];
-            for (int c = 0; c < a.ncand; ++c) {
-                const double rs = bi - a.ax[c][i];
-                const double ru = rs / dri;
-                acc[c][Q_RP2] += ru * ru;
-                acc[c][Q_RPMAX] = fmax(acc[c][Q_RPMAX], fabs(ru));
-                acc[c][Q_SRP2] += rs * rs;
-                const double yv = (double)a.y[c][i];
-                acc[c][Q_BY] += bi * yv;
-                const double dy = yv - yli;
-                acc[c][Q_DY2] += dy * dy;
-            }
-            if (a.ncand > 1) {
-                const double f = (double)a.y[1][i] - (double)a.y[0][i];
-                acc[1][Q_FY2] += f * f;
-            }
+__device__ __forceinline__ void ld_pair(const T *p, int64_t i, bool both,
+                                        double (&o)[2]) {
+    if (both) {
+        if constexpr (sizeof(T) == 8) {
+            const v2d v = *(const v2d *)(p + i);
+            o[0] = v.x; o[1] = v.y;
+        } else {
+            const v2f v = *(const v2f *)(p + i);
+            o[0] = (double)v.x; o[1] = (double)v.y;
         }
     } else {
-        for (int64_t j = (int64_t)(blk - kRedBlocks) * kWG + threadIdx.x;
-             j < a.n; j += stride) {
-            const double cj = a.cs[j], dcj = a.dc[j], xlj = (double)a.xl[j];
-            const double lj = a.ls ? a.ls[j] : 0.0;
-            for (int c = 0; c < a.ncand; ++c) {
-                const double ds = cj - a.aty[c][j];
-                const double zs = ds > 0.0 ? ds : 0.0;
-                const double rds = zs - ds;
-                const double du = ds / dcj;
-                const double zu = du > 0.0 ? du : 0.0;
-                const double rdu = zu - du;
-                acc[c][Q_RD2] += rdu * rdu;
-                acc[c][Q_RDMAX] = fmax(acc[c][Q_RDMAX], fabs(rdu));
-                acc[c][Q_SRD2] += rds * rds;
-                const double xv = (double)a.x[c][j];
-                acc[c][Q_CX] += cj * xv;
-                acc[c][Q_LZ] += lj * zs;
-                const double dx = xv - xlj;
-                acc[c][Q_DX2] += dx * dx;
-            }
-            if (a.ncand > 1) {
-                const double f = (double)a.x[1][j] - (double)a.x[0][j];
-                acc[1][Q_FX2] += f * f;
-            }
-        }
+        o[0] = (double)p[i];
+        o[1] = 0.0;
     }
-    const int nb = 2 * kRedBlocks;
-    for (int c = 0; c < a.ncand; ++c)
-        for (int q = 0; q < Q_NQ; ++q) {
-            double v = (q == Q_RPMAX || q == Q_RDMAX) ? block_max(acc[c][q], s_red)
-                                                      : block_sum(acc[c][q], s_red);
-            if (threadIdx.x == 0) partial[(c * Q_NQ + q) * nb + blk] = v;
+}
+
+// Sums / maxima over the workgroup of NQ quantities of NC candidates, written
+// to partial[(c * Q_NQ + ids[q]) * kRedBlocks + blk].  Each wave reduces its
+// quantities by shuffles; one pass through LDS joins the four waves.
+template <int NC, int NQ>
+__device__ __forceinline__ void kkt_finish(const double (&acc)[NC][NQ],
+                                           const int (&ids)[NQ], int blk,
+                                           double *__restrict__ partial) {
+    __shared__ double s_w[4][NC * NQ];
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const bool mx = ids[q] == Q_RPMAX || ids[q] == Q_RDMAX;
+            const double v = mx ? wave_max(acc[c][q]) : wave_sum(acc[c][q]);
+            if (l == 0) s_w[w][c * NQ + q] = v;
         }
+    __syncthreads();
+    if (threadIdx.x < NC * NQ) {
+        const int c = threadIdx.x / NQ, q = threadIdx.x % NQ;
+        int id = 0;
+#pragma unroll
+        for (int i = 0; i < NQ; ++i)
+            if (i == q) id = ids[i];
+        const double a = s_w[0][threadIdx.x], b = s_w[1][threadIdx.x],
+                     d = s_w[2][threadIdx.x], e = s_w[3][threadIdx.x];
+        partial[(c * Q_NQ + id) * kRedBlocks + blk] =
+            (id == Q_RPMAX || id == Q_RDMAX) ? fmax(fmax(a, b), fmax(d, e))
+                                             : (a + b) + (d + e);
+    }
+}
+
+// Blocks [0, nbr) reduce over rows, [nbr, nbr + nbc) over columns, each of
+// the quantities of its side.  Bound by streaming 7 vectors per side and
+// candidate pair: two entries per lane and load, and enough blocks to keep
+// every CU's loads in flight.  Reducing the quantities one block reduction
+// after the other, over 512 blocks a side however small the LP, took 29 us on
+// a 500 x 1000 LP and 252 us on the 1.35M x 4.95M one (1.4 TB/s).
+template <typename T, int NC>
+__global__ __launch_bounds__(kWG) void k_kkt(KktArgs<T> a, int nbr, int nbc,
+                                            double *__restrict__ partial) {
+    if ((int)blockIdx.x < nbr) {
+        constexpr int ids[6] = {Q_RP2, Q_RPMAX, Q_SRP2, Q_BY, Q_DY2, Q_FY2};
+        double acc[NC][6] = {};
+        for (int64_t i = 2 * ((int64_t)blockIdx.x * kWG + threadIdx.x); i < a.m;
+             i += 2 * (int64_t)nbr * kWG) {
+            const bool both = i + 1 < a.m;
+            double b[2], dr[2], yl[2], ax[NC][2], y[NC][2];
+            ld_pair(a.bs, i, both, b);
+            ld_pair(a.dr, i, both, dr);
+            ld_pair(a.yl, i, both, yl);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                ld_pair(a.ax[c], i, both, ax[c]);
+                ld_pair(a.y[c], i, both, y[c]);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (u && !both) break;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const double rs = b[u] - ax[c][u];
+                    const double ru = rs / dr[u];
+                    acc[c][0] += ru * ru;
+                    acc[c][1] = fmax(acc[c][1], fabs(ru));
+                    acc[c][2] += rs * rs;
+                    acc[c][3] += b[u] * y[c][u];
+                    const double dy = y[c][u] - yl[u];
+                    acc[c][4] += dy * dy;
+                }
+                if (NC > 1) {
+                    const double f = y[NC - 1][u] - y[0][u];
+                    acc[NC - 1][5] += f * f;
+                }
+            }
+        }
+        kkt_finish<NC, 6>(acc, ids, blockIdx.x, partial);
+    } else {
+        constexpr int ids[7] = {Q_RD2, Q_RDMAX, Q_SRD2, Q_CX, Q_LZ, Q_DX2, Q_FX2};
+        const int blk = (int)blockIdx.x - nbr;
+        double acc[NC][7] = {};
+        for (int64_t j = 2 * ((int64_t)blk * kWG + threadIdx.x); j < a.n;
+             j += 2 * (int64_t)nbc * kWG) {
+            const bool both = j + 1 < a.n;
+            double cj[2], dc[2], xl[2], lj[2] = {0.0, 0.0}, g[NC][2], x[NC][2];
+            ld_pair(a.cs, j, both, cj);
+            ld_pair(a.dc, j, both, dc);
+            ld_pair(a.xl, j, both, xl);
+            if (a.ls) ld_pair(a.ls, j, both, lj);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                ld_pair(a.aty[c], j, both, g[c]);
+                ld_pair(a.x[c], j, both, x[c]);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (u && !both) break;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const double ds = cj[u] - g[c][u];
+                    const double zs = ds > 0.0 ? ds : 0.0;
+                    const double rds = zs - ds;
+                    const double du = ds / dc[u];
+                    const double zu = du > 0.0 ? du : 0.0;
+                    const double rdu = zu - du;
+                    acc[c][0] += rdu * rdu;
+                    acc[c][1] = fmax(acc[c][1], fabs(rdu));
+                    acc[c][2] += rds * rds;
+                    acc[c][3] += cj[u] * x[c][u];
+                    acc[c][4] += lj[u] * zs;
+                    const double dx = x[c][u] - xl[u];
+                    acc[c][5] += dx * dx;
+                }
+                if (NC > 1) {
+                    const double f = x[NC - 1][u] - x[0][u];
+                    acc[NC - 1][6] += f * f;
+                }
+            }
+        }
+        kkt_finish<NC, 7>(acc, ids, blk, partial);
+    }
 }
 
 // One evaluation's decisions: a fixed-order finish of the partial sums in one
-// workgroup, then control_decide (control.h) on thread 0.
-__global__ __launch_bounds__(kWG) void k_control(State *st,
-                                                 const double *__restrict__ partial,
-                                                 int ncand, int batch,
-                                                 int initial, double *elog) {
+// workgroup (a wave per quantity), then control_decide (control.h) on thread
+// 0.  The control state is decided on in LDS and written back at the end:
+// latency of dependent accesses is all that this kernel costs.  With a tree of
+// barriers per quantity and the state in global memory it took 54-59 us per
+// evaluation.
+constexpr int kCtlThreads = 1024;
+__global__ __launch_bounds__(kCtlThreads) void k_control(
+    State *st, const double *__restrict__ partial, int nbr, int nbc, int ncand,
+    int batch, int initial, double *elog) {
     __shared__ double tot[2][Q_NQ];
-    __shared__ double sred[kWG];
-    __shared__ int running;
-    const int tid = threadIdx.x;
-    if (tid == 0) running = (st->status == PDHG_RUNNING);
-    __syncthreads();
-    if (!running) {
-        if (tid == 0) {
-            st->copy_pending = 0;
-            st->snap_n = 0;
+    __shared__ State s;
+    static_assert(sizeof(State) % sizeof(uint32_t) == 0, "copied by words");
+    constexpr int kWords = sizeof(State) / sizeof(uint32_t);
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+    for (int i = tid; i < kWords; i += kCtlThreads)
+        ((uint32_t *)&s)[i] = ((const uint32_t *)st)[i];
+    for (int p = w; p < ncand * Q_NQ; p += kCtlThreads / 64) {
+        const int q = p % Q_NQ;
+        const bool mx = q == Q_RPMAX || q == Q_RDMAX;
+        const int nb = (q <= Q_DY2 || q == Q_FY2) ? nbr : nbc;
+        double v = 0.0;
+#pragma unroll 4
+        for (int b = l; b < nb; b += 64) {
+            const double t = partial[p * kRedBlocks + b];
+            v = mx ? fmax(v, t) : v + t;
         }
-        return;
+        v = mx ? wave_max(v) : wave_sum(v);
+        if (l == 0) tot[p / Q_NQ][q] = v;
     }
-    const int nb = 2 * kRedBlocks;
-    for (int c = 0; c < ncand; ++c)
-        for (int q = 0; q < Q_NQ; ++q) {
-            const bool isMax = (q == Q_RPMAX || q == Q_RDMAX);
-            double v = 0.0;
-            for (int b = tid; b < nb; b += kWG) {
-                const double p = partial[(c * Q_NQ + q) * nb + b];
-                v = isMax ? fmax(v, p) : v + p;
-            }
-            sred[tid] = v;
-            __syncthreads();
-            for (int s = kWG / 2; s > 0; s >>= 1) {
-                if (tid < s)
-                    sred[tid] = isMax ? fmax(sred[tid], sred[tid + s])
-                                      : sred[tid] + sred[tid + s];
-                __syncthreads();
-            }
-            if (tid == 0) tot[c][q] = sred[0];
-            __syncthreads();
+    __syncthreads();
+    if (tid == 0) {
+        if (s.status == PDHG_RUNNING) {
+            control_decide(&s, tot, ncand, batch, initial, elog);
+        } else {
+            s.copy_pending = 0;
+            s.snap_n = 0;
         }
-    if (tid == 0) control_decide(st, tot, ncand, batch, initial, elog);
+    }
+    __syncthreads();
+    for (int i = tid; i < kWords; i += kCtlThreads)
+        ((uint32_t *)st)[i] = ((const uint32_t *)&s)[i];
 }
 
 template <typename T>
@@ -986,29 +1063,31 @@ void launch_kkt_reduce(int ncand, const void *x0, const void *y0,
                        const void *yl, const double *bs, const double *cs,
                        const double *ls, const double *dr, const double *dc,
                        int64_t m, int64_t n, double *partial, hipStream_t s) {
-    if (f32) {
-        KktArgs<float> a{{(const float *)x0, (const float *)x1},
-                         {(const float *)y0, (const float *)y1},
-                         (const float *)xl, (const float *)yl,
-                         {ax0, ax1}, {aty0, aty1}, bs, cs, ls, dr, dc, m, n,
-                         ncand};
-        hipLaunchKernelGGL(k_kkt<float>, dim3(2 * kRedBlocks), dim3(kWG), 0,
-                           s, a, partial);
-    } else {
-        KktArgs<double> a{{(const double *)x0, (const double *)x1},
-                          {(const double *)y0, (const double *)y1},
-                          (const double *)xl, (const double *)yl,
-                          {ax0, ax1}, {aty0, aty1}, bs, cs, ls, dr, dc, m, n,
-                          ncand};
-        hipLaunchKernelGGL(k_kkt<double>, dim3(2 * kRedBlocks), dim3(kWG), 0,
-                           s, a, partial);
-    }
+    const int nbr = red_blocks(m), nbc = red_blocks(n);
+    auto run = [&](auto zero) {
+        using T = decltype(zero);
+        const KktArgs<T> a{{(const T *)x0, (const T *)x1},
+                           {(const T *)y0, (const T *)y1},
+                           (const T *)xl, (const T *)yl,
+                           {ax0, ax1}, {aty0, aty1}, bs, cs, ls, dr, dc, m, n};
+        if (ncand > 1)
+            hipLaunchKernelGGL((k_kkt<T, 2>), dim3(nbr + nbc), dim3(kWG), 0, s,
+                               a, nbr, nbc, partial);
+        else
+            hipLaunchKernelGGL((k_kkt<T, 1>), dim3(nbr + nbc), dim3(kWG), 0, s,
+                               a, nbr, nbc, partial);
+    };
+    if (f32)
+        run(0.0f);
+    else
+        run(0.0);
 }
 
-void launch_control(State *st, const double *partial, int ncand, int batch,
-                    int initial, double *log, hipStream_t s) {
-    hipLaunchKernelGGL(k_control, dim3(1), dim3(kWG), 0, s, st, partial,
-                       ncand, batch, initial, log);
+void launch_control(State *st, const double *partial, int64_t m, int64_t n,
+                    int ncand, int batch, int initial, double *log,
+                    hipStream_t s) {
+    hipLaunchKernelGGL(k_control, dim3(1), dim3(kCtlThreads), 0, s, st, partial,
+                       red_blocks(m), red_blocks(n), ncand, batch, initial, log);
 }
 
 void launch_polish_stash(const State *st, bool f32, const void *x0,
@@ -1370,18 +1449,18 @@ __global__ __launch_bounds__(kWG) void k_norm_unscaled_partial(
 
 void launch_dot(const double *a, const double *b, int64_t k, double *partial,
                 double *result, hipStream_t s) {
-    hipLaunchKernelGGL(k_dot_partial, dim3(kRedBlocks), dim3(kWG), 0, s, a, b,
+    hipLaunchKernelGGL(k_dot_partial, dim3(red_blocks(k)), dim3(kWG), 0, s, a, b,
                        k, partial);
     hipLaunchKernelGGL(k_finish, dim3(1), dim3(kWG), 0, s, partial,
-                       kRedBlocks, result, 0);
+                       red_blocks(k), result, 0);
 }
 
 void launch_norm_unscaled(const double *vs, const double *d, int64_t k,
                           double *partial, double *result, hipStream_t s) {
-    hipLaunchKernelGGL(k_norm_unscaled_partial, dim3(kRedBlocks), dim3(kWG),
+    hipLaunchKernelGGL(k_norm_unscaled_partial, dim3(red_blocks(k)), dim3(kWG),
                        0, s, vs, d, k, partial);
     hipLaunchKernelGGL(k_finish, dim3(1), dim3(kWG), 0, s, partial,
-                       kRedBlocks, result, 0);
+                       red_blocks(k), result, 0);
 }
 
 void launch_scale_vec(double *dst, const double *src, const double *factor,

@@ -805,8 +805,8 @@ void enqueue_eval(pdhg_ctx *c, int batch, bool initial) {
                       c->aty_avg, xl, yl, c->act_bs, c->act_cs,
                       c->act_has_l ? c->act_ls : nullptr, c->dr, c->dc, c->m,
                       c->n, c->partial, c->stream);
-    launch_control(c->st, c->partial, ncand, batch, initial ? 1 : 0, c->log,
-                   c->stream);
+    launch_control(c->st, c->partial, c->m, c->n, ncand, batch, initial ? 1 : 0,
+                   c->log, c->stream);
     if (c->n_slots > 0)
         launch_snapshot_pack(c->st, h, x0, y0, x1, y1, c->aty_cur, c->aty_avg,
                              c->act_cs, c->dr, c->dc, c->pr, c->pc, c->slots,
@@ -1169,16 +1169,16 @@ void kkt_pair64(pdhg_ctx *c, const double *xs, const double *ys,
     launch_kkt_reduce(1, xs, ys, xs, ys, false, c->ax_cur, c->aty_cur,
                       c->ax_cur, c->aty_cur, xs, ys, bs, cs, ls, c->dr, c->dc,
                       c->m, c->n, c->partial, c->stream);
-    const int nbk = 2 * kRedBlocks;
-    std::vector<double> h((size_t)Q_NQ * nbk);
+    std::vector<double> h((size_t)Q_NQ * kRedBlocks);
     HIPC(hipMemcpyAsync(h.data(), c->partial, h.size() * sizeof(double),
                         hipMemcpyDeviceToHost, c->stream));
     sync(c);
     double Q[Q_NQ];
     for (int q = 0; q < Q_NQ; ++q) {
         double v = 0.0;
-        for (int b = 0; b < nbk; ++b) {
-            double p = h[(size_t)q * nbk + b];
+        const int nb = red_blocks((q <= Q_DY2 || q == Q_FY2) ? c->m : c->n);
+        for (int b = 0; b < nb; ++b) {
+            double p = h[(size_t)q * kRedBlocks + b];
             v = (q == Q_RPMAX || q == Q_RDMAX) ? std::max(v, p) : v + p;
         }
         Q[q] = v;
@@ -1433,7 +1433,7 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
     c->yo = dmalloc<double>(m);
     c->rho = dmalloc<double>(m);
     c->kap = dmalloc<double>(n);
-    c->partial = dmalloc<double>(2 * Q_NQ * 2 * kRedBlocks);
+    c->partial = dmalloc<double>(2 * Q_NQ * kRedBlocks);
     c->scal = dmalloc<double>(16);
     c->log = dmalloc<double>(8 * (int64_t)c->log_cap);
     // until configure: unit scaling so that pdhg_spmv works on A~ = A

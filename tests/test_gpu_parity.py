@@ -599,3 +599,36 @@ def test_residuals_of_the_better_candidate(Solver, oracle):
         k0, k1, kb = s.residuals(0), s.residuals(1), s.residuals(2)
     want = k1 if k1["maxresid"] < k0["maxresid"] else k0
     assert kb["maxresid"] == want["maxresid"] and kb["candidate"] == want["candidate"]
+
+
+@pytest.mark.parametrize("m,n", [(1, 2), (2, 511), (512, 513), (513, 1025),
+                                 (1025, 524_287), (524_289, 3)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_kkt_reduction_edges(Solver, m, n, precision):
+    """The KKT reduction where its pairs, blocks and rounds end (512 entries a
+    block, 1,024 blocks a round), with and without lower bounds, against numpy
+    on the same iterate."""
+    rng = np.random.default_rng(m + n)
+    k = np.arange(max(m, n))
+    v = rng.standard_normal(k.size)
+    b, c = rng.standard_normal(m), rng.standard_normal(n)
+    lp = lpgen.from_coo(m, n, k % m, k % n, v, b, c)
+    for lb in (None, rng.standard_normal(n) - 2.0):
+        with Solver.from_lp(lp, lb=lb) as s:
+            s.configure(precision=precision)
+            s.set_iterate(rng.standard_normal(n), rng.standard_normal(m))
+            x, y, _ = s.get_iterate()
+            got = s.residuals(0)
+        rp = b - np.bincount(k % m, weights=v * x[k % n], minlength=m)
+        red = c - np.bincount(k % n, weights=v * y[k % m], minlength=n)
+        rd = np.maximum(-red, 0.0)
+        l = np.zeros(n) if lb is None else lb
+        pobj, dobj = c @ x, b @ y + l @ np.maximum(red, 0.0)
+        # sums of at most 5e5 products, some of them cancelling
+        for key, ref, size in (("norm_rp", np.linalg.norm(rp), np.linalg.norm(rp)),
+                               ("norm_rd", np.linalg.norm(rd), np.linalg.norm(rd)),
+                               ("rp_inf", np.abs(rp).max(), np.abs(rp).max()),
+                               ("rd_inf", rd.max(), rd.max()),
+                               ("pobj", pobj, np.abs(c * x).sum()),
+                               ("dobj", dobj, np.abs(b * y).sum() + np.abs(l * red).sum())):
+            assert abs(got[key] - ref) <= 1e-11 * size + 1e-300, (key, got[key], ref)
