@@ -578,7 +578,14 @@ int pdhg_spmv(pdhg_ctx *ctx, int which, int scaled, int precision,
 int pdhg_spmv_noalloc(pdhg_ctx *ctx, int which, int scaled, int precision,
                       const double *in, double *out, int mem);
 
-/* Row-bin tuning, taking effect at the next pdhg_load:
+/* Layout tuning, taking effect at the next pdhg_load:
+ *  "layout_a", "layout_at": how the products with A and with A^T run: 0 in
+ *      row blocks, 1 in tiles (buckets of rows whose nonzeros gather in column
+ *      order), 2 by pushed products (a pass over column blocks writes the
+ *      products to the buckets of their rows, a second sums them), -1
+ *      (default) chooses from the sizes.  Sums stay deterministic but round
+ *      differently; the keys below on blocks and splits are those of layout 0,
+ *      which a panel count other than 0 also selects under -1;
  *  "split_threshold": nnz above which a row is split over several
  *      workgroups; "split_chunk": nnz per split part;
  *  "panels_a", "panels_at": column panels (1, 2, 4 or 8; 0 = chosen from

@@ -389,11 +389,21 @@ Relabeled relabel(int64_t m, int64_t n, int64_t nnz, const int64_t *a_rp,
     R.a_v.resize((size_t)nnz);
     R.apos.resize((size_t)nnz);
     // rows are independent: fill them on a few host threads
+    const bool same_cols = !R.sorted_cols;    // the columns keep their order
     auto fill_rows = [&](int64_t lo, int64_t hi) {
         std::vector<std::pair<int32_t, int32_t>> tmp;
         for (int64_t i2 = lo; i2 < hi; ++i2) {
             const int64_t i = R.pr[i2];
             const int64_t p0 = a_rp[i], L = a_rp[i + 1] - p0;
+            if (same_cols) {
+                const int64_t o = R.a_rp[i2];
+                for (int64_t q = 0; q < L; ++q) {
+                    R.a_ci[o + q] = a_ci[p0 + q];
+                    R.a_v[o + q] = a_v[p0 + q];
+                    R.apos[o + q] = (int32_t)(p0 + q);
+                }
+                continue;
+            }
             tmp.resize((size_t)L);
             for (int64_t q = 0; q < L; ++q)
                 tmp[q] = {ic[a_ci[p0 + q]], (int32_t)(p0 + q)};
@@ -406,7 +416,7 @@ Relabeled relabel(int64_t m, int64_t n, int64_t nnz, const int64_t *a_rp,
             }
         }
     };
-    const int nt = (int)std::max<int64_t>(1, std::min<int64_t>(8, nnz / 1000000));
+    const int nt = (int)std::max<int64_t>(1, std::min<int64_t>(8, nnz / 100000));
     if (nt == 1) {
         fill_rows(0, m);
     } else {
@@ -557,6 +567,286 @@ HostBins build_panel_blocks(int64_t rows, const int64_t *srp, int P, int tile,
             out.blocks.push_back(i < q[x].size() ? q[x][i]
                                                  : RowBlock{0, 0, 0, 1, -1, 0, 0, 0});
     return out;
+}
+
+// Cost of rows [r0, r1) to a bucket: its nonzeros, and the epilogue's operands
+// of a row (40 to 56 bytes) as three more.
+static int64_t bucket_cost(const int64_t *rp, int64_t r0, int64_t r1) {
+    return rp[r1] - rp[r0] + 3 * (r1 - r0);
+}
+
+// Cost per bucket: equal shares of whole rounds of one bucket on each CU.
+static int64_t bucket_fill(int64_t cost, int64_t nnz) {
+    constexpr int64_t kCus = 256, most = 2 * (int64_t)kBktCap;
+    const int64_t nr = std::max<int64_t>(
+        1, std::max((nnz + kCus * kBktCap - 1) / (kCus * kBktCap),
+                    (cost + kCus * most - 1) / (kCus * most)));
+    return (int64_t)(1.01 * (double)cost / (double)(kCus * nr)) + 64;
+}
+
+// Consecutive rows of [row0, row1) packed into buckets of about cost `fill`
+// and at most kBktCap nonzeros; a longer row is cut into parts.  skip_empty:
+// no bucket starts at an empty row.
+static void pack_buckets(HostBuckets &B, int64_t row0, int64_t row1,
+                         const int64_t *rp, int64_t fill, bool skip_empty) {
+    for (int64_t r = row0; r < row1;) {
+        const int64_t len = rp[r + 1] - rp[r];
+        if (skip_empty && len == 0) {
+            ++r;
+            continue;
+        }
+        if (len > kBktCap) {
+            const int np = (int)((len + kBktCap - 1) / kBktCap);
+            const int64_t chunk = (len + np - 1) / np;
+            const int slot = (int)B.splits.size();
+            for (int q = 0; q < np; ++q) {
+                const int64_t a = rp[r] + q * chunk, e = std::min(rp[r + 1], a + chunk);
+                B.buckets.push_back({(int32_t)r, (int32_t)(r + 1), (int32_t)a,
+                                     (int32_t)e, 0, 0, slot, q});
+            }
+            B.splits.push_back({(int32_t)r, np});
+            B.maxparts = std::max(B.maxparts, np);
+            ++r;
+            continue;
+        }
+        // G lanes (a power of two, at most 64) sum each of R rows: no row may
+        // keep its lanes longer than 64 steps because of many short ones
+        int64_t r1 = r + 1, longest = len;
+        while (r1 < row1 && rp[r1 + 1] - rp[r] <= kBktCap &&
+               bucket_cost(rp, r, r1 + 1) <= fill) {
+            const int64_t mx = std::max(longest, rp[r1 + 1] - rp[r1]);
+            const int64_t G = std::min<int64_t>(64, kBktThreads / (r1 + 1 - r));
+            if (mx > 64 && mx > 64 * G && G < 64) break;
+            longest = mx;
+            ++r1;
+        }
+        B.buckets.push_back({(int32_t)r, (int32_t)r1, (int32_t)rp[r], (int32_t)rp[r1], 0, 0, -1, 0});
+        r = r1;
+    }
+}
+
+// Stable sort by the high 32 bits (below 2^31), in radix passes of 11 bits.
+static void sort_high(std::vector<uint64_t> &key, std::vector<uint64_t> &tmp) {
+    constexpr int kBits = 11;
+    uint64_t lo = ~0ull, hi = 0;
+    for (uint64_t k : key) {
+        lo = std::min(lo, k >> 32);
+        hi = std::max(hi, k >> 32);
+    }
+    tmp.resize(key.size());
+    for (int sh = 0; key.size() > 1 && sh < 32 && ((hi - lo) >> sh) != 0; sh += kBits) {
+        uint32_t at[(1 << kBits) + 1] = {0};
+        auto digit = [&](uint64_t k) { return (((k >> 32) - lo) >> sh) & ((1u << kBits) - 1); };
+        for (uint64_t k : key) ++at[digit(k) + 1];
+        for (int d = 0; d < 1 << kBits; ++d) at[d + 1] += at[d];
+        for (uint64_t k : key) tmp[at[digit(k)]++] = k;
+        key.swap(tmp);
+    }
+}
+
+// fn(b0, b1) over the buckets [0, nb) on a few threads.
+template <class Fn>
+static void over_buckets(int64_t nb, int64_t nnz, Fn fn) {
+    const int nt = (int)std::max<int64_t>(1, std::min<int64_t>(8, nnz / 100000));
+    std::vector<std::thread> th;
+    for (int t = 1; t < nt; ++t) th.emplace_back(fn, nb * t / nt, nb * (t + 1) / nt);
+    fn((int64_t)0, nb / nt);
+    for (auto &t : th) t.join();
+}
+
+// Push buckets.  Columns are cut into blocks of kBktCols.  The nonzeros of one
+// (column block, bucket) pair form a run, padded to whole quads: the push pass
+// walks the runs of a column block one after the other, and each run is
+// contiguous among its bucket's products.
+HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
+                       const int32_t *ci, bool force) {
+    HostBuckets B;
+    const int64_t nnz = rp[rows], cost = bucket_cost(rp, 0, rows);
+    const int64_t ncb = (cols + kBktCols - 1) / kBktCols;
+    const int64_t fill = bucket_fill(cost, nnz);
+    pack_buckets(B, 0, rows, rp, fill, false);
+    const int64_t nb = (int64_t)B.buckets.size();
+    B.fragmented = nb > 2 * (cost / fill) + 64;
+    if (B.fragmented && !force) return B;
+    // quads of each run; then the runs' places in both orders
+    std::vector<int32_t> run((size_t)(ncb * nb)), at((size_t)(ncb * nb));
+    over_buckets(nb, nnz, [&](int64_t b0, int64_t b1) {
+        std::vector<int32_t> cnt((size_t)ncb);
+        for (int64_t b = b0; b < b1; ++b) {
+            std::fill(cnt.begin(), cnt.end(), 0);
+            for (int64_t p = B.buckets[b].p0; p < B.buckets[b].p1; ++p) ++cnt[ci[p] / kBktCols];
+            for (int64_t k = 0; k < ncb; ++k) run[k * nb + b] = (cnt[k] + 3) / 4;
+        }
+    });
+    std::vector<int64_t> cq((size_t)ncb + 1, 0);
+    int64_t q = 0;
+    for (int64_t k = 0; k < ncb; ++k) {
+        for (int64_t b = 0; b < nb; ++b) {
+            at[k * nb + b] = (int32_t)q;
+            q += run[k * nb + b];
+        }
+        cq[k + 1] = q;
+    }
+    B.quads = q;
+    q = 0;
+    for (int64_t b = 0; b < nb; ++b) {
+        B.buckets[b].q0 = (int32_t)q;
+        for (int64_t k = 0; k < ncb; ++k) q += run[k * nb + b];
+        B.buckets[b].q1 = (int32_t)q;
+    }
+    B.col.assign((size_t)(4 * B.quads), 0);
+    B.pos.assign((size_t)(4 * B.quads), (uint16_t)kBktCap);
+    B.src.assign((size_t)(4 * B.quads), -1);
+    B.dest.resize((size_t)B.quads);
+    over_buckets(nb, nnz, [&](int64_t b0, int64_t b1) {
+        std::vector<int64_t> c1((size_t)ncb), c2((size_t)ncb);
+        for (int64_t b = b0; b < b1; ++b) {
+            const Bucket &K = B.buckets[b];
+            int64_t o = K.q0;
+            for (int64_t k = 0; k < ncb; ++k) {
+                const int64_t a = at[k * nb + b], n = run[k * nb + b];
+                for (int64_t i = 0; i < n; ++i) B.dest[a + i] = (int32_t)(o + i);
+                c1[k] = 4 * a;
+                c2[k] = 4 * o;
+                o += n;
+            }
+            for (int64_t p = K.p0; p < K.p1; ++p) {
+                const int64_t k = ci[p] / kBktCols;
+                B.col[c1[k]] = (uint16_t)(ci[p] % kBktCols);
+                B.src[c1[k]++] = (int32_t)p;
+                B.pos[c2[k]++] = (uint16_t)(p - K.p0);
+            }
+        }
+    });
+    // push items: equal shares of whole rounds (at most four) of one item per
+    // CU; each XCD (workgroups go to the 8 XCDs round-robin) takes
+    // neighbouring items, so that runs that share lines of the products are
+    // written through one L2
+    constexpr int64_t kCus = 256, kXcd = 8;
+    const int64_t want = kCus * std::max<int64_t>(1, std::min<int64_t>(4, B.quads / (kCus * 8192)));
+    auto count = [&](int64_t S) {
+        int64_t n = 0;
+        for (int64_t k = 0; k < ncb; ++k) n += (cq[k + 1] - cq[k] + S - 1) / S;
+        return n;
+    };
+    int64_t lo = 1, hi = std::max<int64_t>(1, B.quads);
+    const int64_t most = std::max<int64_t>(want, count(hi));
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        if (count(mid) <= most) hi = mid; else lo = mid + 1;
+    }
+    std::vector<PushItem> it;
+    for (int64_t k = 0; k < ncb; ++k) {
+        const int64_t n = cq[k + 1] - cq[k], ns = (n + lo - 1) / lo;
+        for (int64_t i = 0; i < ns; ++i)
+            it.push_back({(int32_t)k, (int32_t)(cq[k] + n * i / ns), (int32_t)(cq[k] + n * (i + 1) / ns), 0});
+    }
+    const int64_t ni = (int64_t)it.size(), per = (ni + kXcd - 1) / kXcd;
+    for (int64_t i = 0; i < per; ++i)
+        for (int64_t x = 0; x < kXcd; ++x)
+            B.items.push_back(x * per + i < ni ? it[x * per + i] : PushItem{0, 0, 0, 0});
+    return B;
+}
+
+// Tiles.  A tile's nonzeros are kept in column order, so that neighbouring
+// lanes gather from neighbouring lines; its products go to their CSR positions
+// in LDS.  Within a group of 64 quads lane l's quad holds the entries l,
+// l + 64, l + 128 and l + 192 of that order: each of the four gathers of a
+// wave then covers 64 neighbours.  Tiles of panel p are dealt to the XCDs x
+// with x % P == p (r0 == r1 pads queues of unequal length).
+HostBuckets build_tiles(int64_t rows, const int64_t *rp, const int32_t *ci,
+                        int P, bool force) {
+    constexpr int kXcd = 8;
+    HostBuckets B;
+    const int64_t nnz = rp[P * rows], cost = bucket_cost(rp, 0, P * rows);
+    const int64_t fill = bucket_fill(cost, nnz);
+    std::vector<int64_t> first;
+    for (int p = 0; p < P; ++p) {
+        first.push_back((int64_t)B.buckets.size());
+        pack_buckets(B, p * rows, (p + 1) * rows, rp, fill, P > 1);
+    }
+    first.push_back((int64_t)B.buckets.size());
+    const int64_t nb = (int64_t)B.buckets.size();
+    B.fragmented = nb > 2 * (cost / fill) + 64;
+    if (B.fragmented && !force) return B;
+    int64_t q = 0;
+    for (auto &b : B.buckets) {
+        b.q0 = (int32_t)q;
+        q += (b.p1 - b.p0 + 3) / 4;
+        b.q1 = (int32_t)q;
+    }
+    B.quads = q;
+    B.gcol.assign((size_t)(4 * q), 0);
+    B.pos.assign((size_t)(4 * q), (uint16_t)kBktCap);
+    B.src.assign((size_t)(4 * q), -1);
+    over_buckets(nb, nnz, [&](int64_t b0, int64_t b1) {
+        std::vector<uint64_t> key, tmp;
+        for (int64_t b = b0; b < b1; ++b) {
+            const Bucket &K = B.buckets[b];
+            const int64_t nz = K.p1 - K.p0, nq = K.q1 - K.q0;
+            key.resize((size_t)nz);
+            for (int64_t t = 0; t < nz; ++t)
+                key[t] = (uint64_t)(uint32_t)ci[K.p0 + t] << 32 | (uint64_t)t;
+            sort_high(key, tmp);
+            for (int64_t t = 0; t < 4 * nq; ++t) {
+                // entry t of the order: group g of up to 64 quads
+                const int64_t g = t / 256, L = std::min<int64_t>(64, nq - 64 * g);
+                const int64_t i = t - 256 * g;
+                const int64_t o = 4 * (K.q0 + 64 * g + i % L) + i / L;
+                const uint64_t e = key[std::min(t, nz - 1)];
+                B.gcol[o] = (int32_t)(e >> 32);
+                if (t < nz) {
+                    B.src[o] = (int32_t)(K.p0 + (int64_t)(e & 0xffffffffu));
+                    B.pos[o] = (uint16_t)(e & 0xffffffffu);
+                }
+            }
+        }
+    });
+    std::vector<std::vector<Bucket>> xq(kXcd);
+    const int per = kXcd / P;
+    for (int p = 0; p < P; ++p)
+        for (int64_t i = 0; i < first[p + 1] - first[p]; ++i)
+            xq[p + P * (int)(i % per)].push_back(B.buckets[first[p] + i]);
+    size_t depth = 0;
+    for (auto &v : xq) depth = std::max(depth, v.size());
+    B.buckets.clear();
+    for (size_t i = 0; i < depth; ++i)
+        for (int x = 0; x < kXcd; ++x)
+            B.buckets.push_back(i < xq[x].size() ? xq[x][i] : Bucket{0, 0, 0, 0, 0, 0, -1, 0});
+    return B;
+}
+
+// Which layout a side runs in, from its sizes (P: its column panels).  A
+// gather costs a line from L2 to the CU; a tile shares a line among its
+// gathers, which pays while a panel's part of the vector has few more lines
+// than a tile has nonzeros, and stacked rows are not short.  Pushing the
+// products costs 17 (FP64) or 9 (FP32) more bytes per nonzero and a second
+// launch, but gathers from LDS only; its runs shorten as the columns grow.
+// Measured, us a step, rows | tiles | push (FP64; FP32):
+//   power-law primal, 9.4M nonzeros, 1.6 MB:  64 | 54 | 66;  51 | 38 | 41
+//   ... dual, 8 MB in 4 panels, 47 a row:     61 | 53 | 64;  43 | 39 | 45
+//   1M x 400k dual, 8M, 8 MB, 20 a row:       72 | 62 | 55;  54 | 46 | 38
+//   ... primal, 3.2 MB:                       65 | 57 | 58;  51 | 44 | 36
+//   multicommodity primal, 14.6M, 10.8 MB:   133 | 118 | 119;  98 | 79 | 69
+//   ... dual, 40 MB in 8 panels:             143 | 142 | 115; 100 | 93 | 66
+//   840k-column one, dual, 2.4M, 6.7 MB:      30 | 26 | 26;  21 | 21 | 18
+//   ... primal, 1.9 MB:                       24 | 20 | 27;  21 | 15 | 19
+//   600k x 200k dual, 2.4M, 4.8 MB:           28 | 22 | 25;  21 | 18 | 17
+//   power-law 300k dual, 2.8M, 2.4 MB:        21 | 17 | 25;  17 | 14 | 17
+//   400k x 160k dual, 1.2M, 3.2 MB:           16 | 15 | 19;  14 | 12 | 14
+//   2M x 1M dual, 24M, 16 MB:                199 | 178 | 147; 152 | 134 | 84
+//   coupled dual, 55M, 80 MB in 8 panels:    708 | 563 | 467; 431 | 406 | 241
+//   ... 110M, 160 MB:                       1764 |  -  | 1011; 1260 | - | 566
+int choose_layout(int64_t rows, int64_t cols, int64_t nnz, int P) {
+    constexpr double kMiB = 1048576.0;
+    const double panel = 8.0 * (double)cols / P;
+    if (nnz < kTileMin32) return LAYOUT_ROWS;
+    if (panel <= (nnz < 4000000 ? 6.0 : 2.25) * kMiB &&
+        (P == 1 || nnz >= 8 * (int64_t)P * rows))
+        return LAYOUT_TILES;
+    // runs of eight nonzeros or more (33M columns)
+    const bool runs = (cols + kBktCols - 1) / kBktCols <= kBktCap / 8;
+    return nnz >= 2000000 && runs ? LAYOUT_PUSH : LAYOUT_ROWS;
 }
 
 }  // namespace pdhg

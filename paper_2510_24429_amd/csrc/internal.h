@@ -74,6 +74,68 @@ HostBins build_panel_blocks(int64_t rows, const int64_t *srp, int P, int tile,
                             int64_t split_threshold, int64_t split_chunk,
                             int max_rows = 0);
 
+// Buckets of one SpMV side (see host_csr.cpp): consecutive rows whose products
+// one workgroup sums in LDS.  A tile's nonzeros gather the vector themselves;
+// otherwise a push pass multiplies the nonzeros of one block of kBktCols
+// columns, its part of the vector in LDS, and writes the products to the
+// buckets of their rows.
+enum { LAYOUT_CHOOSE = -1, LAYOUT_ROWS = 0, LAYOUT_TILES = 1, LAYOUT_PUSH = 2 };
+constexpr int kBktCap = 1 << 14;      // most nonzeros of a bucket (128 KB of FP64)
+constexpr int kBktCols = 1 << 14;     // columns per block (the same)
+constexpr int kBktThreads = 1024;
+// Fewest nonzeros that run in tiles, FP64 and FP32.  Measured, us an iteration
+// in row blocks | tiles, by nonzeros: FP64 55k 8.5 | 9.3, 480k 11.4 | 11.9,
+// 800k 17.0 | 15.8; FP32 55k 9.6 | 8.4, 300k 11.3 | 9.7, 800k 15.7 | 12.6.
+constexpr int64_t kTileMin64 = 700000, kTileMin32 = 50000;
+// Quads [q0, q1) of the push order, all of column block cb (q0 == q1: padding).
+struct PushItem {
+    int32_t cb, q0, q1, pad;
+};
+// Rows [r0, r1) with nonzeros [p0, p1) and products at quads [q0, q1), or
+// (slot >= 0) part `part` of row r0, whose sum goes to partial slot `slot`.
+struct Bucket {
+    int32_t r0, r1, p0, p1, q0, q1, slot, part;
+};
+struct HostBuckets {
+    bool fragmented = false;          // row lengths too mixed to fill buckets
+    int64_t quads = 0;                // groups of four products, runs padded
+    std::vector<PushItem> items;
+    std::vector<Bucket> buckets;
+    std::vector<SplitRow> splits;
+    int maxparts = 1;
+    std::vector<uint16_t> col, pos;   // 4 * quads: column in its block (push
+                                      // order), CSR position in its bucket
+                                      // (kBktCap: padding)
+    std::vector<int32_t> src;         // 4 * quads: position in the CSR (-1: padding)
+    std::vector<int32_t> dest;        // quads: quad of the products
+    std::vector<int32_t> gcol;        // tiles: 4 * quads columns
+};
+// Unless forced, both stop at a fragmented matrix.
+HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
+                       const int32_t *ci, bool force);
+// Tiles over the rows of P stacked panels (rows each).
+HostBuckets build_tiles(int64_t rows, const int64_t *rp, const int32_t *ci,
+                        int P, bool force);
+int choose_layout(int64_t rows, int64_t cols, int64_t nnz, int P);
+
+// The same on the device.
+struct DevBuckets {
+    int nitems = 0, nbuckets = 0, nsplit = 0, maxparts = 1;
+    bool f64 = true;                  // FP64 products run here too
+    int64_t quads = 0;
+    PushItem *items = nullptr;
+    Bucket *buckets = nullptr;
+    SplitRow *split = nullptr;
+    uint16_t *col = nullptr, *pos = nullptr;
+    int32_t *src = nullptr, *dest = nullptr;
+    int32_t *gcol = nullptr;          // tiles (no push pass)
+    double *v64 = nullptr;            // scaled values in the order of src
+    float *v32 = nullptr;
+    void *prod = nullptr;             // products of either precision, shared by
+                                      // both sides (of the same stream)
+    void *part = nullptr;             // partial sums of split rows
+};
+
 // The internal (relabeled) problem: row i' of A' is row pr[i'] of A, column
 // j' of A' is column pc[j'] of A; apos[p'] is the position in A's arrays of
 // A''s nonzero p'; perm[p'] its position in A'^T's arrays.
@@ -113,6 +175,7 @@ struct DevCsr {
     // values kept equal to v64 / v32 through src), and the partial sums
     int P = 1;
     int stream_nt = 0;          // non-temporal streamed loads (see kernels)
+    DevBuckets *bkt = nullptr;  // tiles or push buckets
     DevCsr *pan = nullptr;
     int32_t *pan_src = nullptr;
     uint8_t *pan_mask = nullptr;  // per row: which panels hold entries of it
@@ -288,6 +351,9 @@ void launch_permute(double *dst, const double *src, const int32_t *perm,
                     int64_t k, hipStream_t s);
 void launch_gather(double *dst, const double *src, const int32_t *idx,
                    int64_t k, hipStream_t s);
+// ... the same in FP64 and rounded to FP32, 0 where idx < 0
+void launch_gather_pad(double *dst, float *dst32, const double *src,
+                       const int32_t *idx, int64_t k, hipStream_t s);
 
 // Refinement (FP64): residual data of the correction LP and its update.
 void launch_refine_rhs(const double *bs, const double *ax, const double *cs,

@@ -527,6 +527,339 @@ __global__ __launch_bounds__(kWG) void k_panel_combine(
     }
 }
 
+// ----------------------------------------------------------------- buckets
+
+// Streamed entries come in 16-byte units of values (2 FP64 or 4 FP32), one
+// unit per lane, so that a wave's load or store covers whole lines in order;
+// their indices and positions come in units of as many.
+typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+typedef unsigned short v4us __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+template <typename T>
+struct UnitOf;
+template <>
+struct UnitOf<double> {
+    static constexpr int W = 2;
+    using V = v2d;
+    using H = v2us;
+    using I = v2i;
+};
+template <>
+struct UnitOf<float> {
+    static constexpr int W = 4;
+    using V = v4f;
+    using H = v4us;
+    using I = v4i;
+};
+
+// Push pass: products of the quads of one item with its column block of x,
+// which sits in LDS, written to their buckets.
+template <typename MT, typename VT, typename Acc>
+__global__ __launch_bounds__(kBktThreads) void k_bkt_push(
+    const PushItem *__restrict__ items, const uint16_t *__restrict__ col,
+    const MT *__restrict__ val, const int32_t *__restrict__ dest,
+    const VT *__restrict__ x, int64_t cols, Acc *__restrict__ prod) {
+    __shared__ __align__(16) VT s_x[kBktCols];
+    using Un = UnitOf<MT>;
+    using Out = Acc __attribute__((ext_vector_type(Un::W)));
+    constexpr int U = 4, F = 4 / Un::W;       // F units per quad
+    const PushItem it = items[blockIdx.x];
+    if (it.q0 == it.q1) return;
+    const int tid = threadIdx.x;
+    const int64_t c0 = (int64_t)it.cb * kBktCols;
+    const int nc = (int)(cols - c0 < kBktCols ? cols - c0 : kBktCols);
+    using X = UnitOf<VT>;
+    for (int i = X::W * tid; i < nc; i += X::W * kBktThreads) {
+        if (i + X::W <= nc) {
+            *(typename X::V *)(s_x + i) = *(const typename X::V *)(x + c0 + i);
+        } else {
+            for (int u = i; u < nc; ++u) s_x[u] = x[c0 + u];
+        }
+    }
+    const int64_t end = (int64_t)F * it.q1;
+    struct Regs {
+        typename Un::V a;
+        typename Un::H j;
+        int d;
+    };
+    auto fetch = [&](int64_t p, Regs &r) {
+        r.a = __builtin_nontemporal_load((const typename Un::V *)val + p);
+        r.j = __builtin_nontemporal_load((const typename Un::H *)col + p);
+        r.d = __builtin_nontemporal_load(dest + p / F);
+    };
+    auto store = [&](int64_t p, const Regs &r) {
+        Out o;
+#pragma unroll
+        for (int i = 0; i < Un::W; ++i) o[i] = (Acc)r.a[i] * (Acc)s_x[r.j[i]];
+        *(Out *)(prod + 4 * (int64_t)r.d + Un::W * (p % F)) = o;
+    };
+    // whole rounds of U units per lane without a bound check, the next
+    // round's loads issued ahead of this round's products; then the rest
+    int64_t h = (int64_t)F * it.q0 + tid;
+    const int rounds = (int)((end - (h - tid)) / (U * kBktThreads));
+    Regs r[U];
+    if (rounds > 0)
+#pragma unroll
+        for (int u = 0; u < U; ++u) fetch(h + u * kBktThreads, r[u]);
+    __syncthreads();
+    for (int k = 1; k <= rounds; ++k, h += U * kBktThreads) {
+        Regs n[U];
+        if (k < rounds) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) fetch(h + (U + u) * kBktThreads, n[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) store(h + u * kBktThreads, r[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = n[u];
+    }
+    for (; h < end; h += kBktThreads) {
+        fetch(h, r[0]);
+        store(h, r[0]);
+    }
+}
+
+// Where a bucket's products come from: fetch() issues the streamed loads of
+// one unit, mul() forms its products.
+template <typename Acc>
+struct PushedUnits {                  // written by the push pass
+    static constexpr int W = UnitOf<Acc>::W;
+    static constexpr int kWaves = sizeof(Acc) == 4 ? 8 : 4;   // per SIMD
+    const Acc *prod;
+    struct Regs {
+        typename UnitOf<Acc>::V a;
+    };
+    __device__ __forceinline__ void fetch(int64_t p, Regs &r) const {
+        r.a = __builtin_nontemporal_load((const typename UnitOf<Acc>::V *)prod + p);
+    }
+    __device__ __forceinline__ Acc mul(const Regs &r, int i) const { return r.a[i]; }
+};
+template <typename MT, typename VT, typename Acc>
+struct GatheredUnits {                // values times gathers of the vector
+    static constexpr int W = 4;       // (a wave gathers 64 neighbours at a time)
+    static constexpr int kWaves = 4;
+    const int32_t *col;
+    const MT *val;
+    const VT *x;
+    struct Regs {
+        MT a[4];
+        int j[4];
+    };
+    __device__ __forceinline__ void fetch(int64_t p, Regs &r) const {
+        ld4<false>(col + 4 * p, r.j);
+        ld4<false>(val + 4 * p, r.a);
+    }
+    __device__ __forceinline__ Acc mul(const Regs &r, int i) const {
+        return (Acc)r.a[i] * (Acc)x[r.j[i]];
+    }
+};
+
+// Streamed loads of the units h, h + NT, ... (U of them; past the end the last
+// one again, so that no branch separates them), and their products to their
+// places in LDS (past the end to the spare slot).
+template <int U, class Units>
+struct UnitRegs {
+    typename Units::Regs a[U];
+    unsigned short __attribute__((ext_vector_type(Units::W))) j[U];
+};
+template <int U, class Units>
+__device__ __forceinline__ void bkt_fetch(const Units &units,
+                                          const uint16_t *__restrict__ pos,
+                                          int64_t h, int64_t end,
+                                          UnitRegs<U, Units> &r) {
+    using H = unsigned short __attribute__((ext_vector_type(Units::W)));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        int64_t p = h + u * kBktThreads;
+        p = p < end ? p : end - 1;
+        units.fetch(p, r.a[u]);
+        r.j[u] = __builtin_nontemporal_load((const H *)pos + p);
+    }
+}
+template <int U, class Units, typename Acc>
+__device__ __forceinline__ void bkt_store(const Units &units, int64_t h,
+                                          int64_t end,
+                                          const UnitRegs<U, Units> &r,
+                                          Acc *__restrict__ s_prod) {
+    constexpr int W = Units::W;
+    Acc o[U][W];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < W; ++i) o[u][i] = units.mul(r.a[u], i);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+            s_prod[h + u * kBktThreads < end ? (int)r.j[u][i] : kBktCap] = o[u][i];
+}
+// All units [h - tid, end) of a bucket, at most U per lane at a time and no
+// more than there are.
+template <int U, class Units, typename Acc>
+__device__ __forceinline__ void bkt_fill(const Units &units,
+                                         const uint16_t *__restrict__ pos,
+                                         int64_t h, int64_t end,
+                                         Acc *__restrict__ s_prod) {
+    const int64_t tid = threadIdx.x;
+    for (; end - (h - tid) > (U - 1) * kBktThreads; h += U * kBktThreads) {
+        UnitRegs<U, Units> r;
+        bkt_fetch(units, pos, h, end, r);
+        bkt_store(units, h, end, r, s_prod);
+    }
+    if constexpr (U > 1)
+        if (h - tid < end) bkt_fill<U - 1>(units, pos, h, end, s_prod);
+}
+
+// Sum pass: a bucket's products go to their CSR positions in LDS, then a
+// power-of-two group of lanes sums each row (one lane per row, several rows
+// per lane, when there are more rows than lanes), then the epilogue.  LOOP: a
+// workgroup takes every gridDim.x-th bucket and loads the next one while it
+// sums this one.
+template <typename Acc, bool LOOP, class Units, class Epi>
+__global__ __launch_bounds__(kBktThreads, Units::kWaves) void k_bkt_sum(
+    const Bucket *__restrict__ buckets, int nbuckets,
+    const int32_t *__restrict__ rp, const uint16_t *__restrict__ pos,
+    Units units, Acc *__restrict__ part, int maxparts, Epi epi_in) {
+    constexpr int NT = kBktThreads;
+    __shared__ Acc s_prod[kBktCap + 1];
+    __shared__ Acc s_sum[NT];
+    constexpr int F = 4 / Units::W, KP = 3;
+    constexpr int U = kBktCap / Units::W / NT;
+    Epi epi = epi_in;
+    int t = blockIdx.x;
+    Bucket b = buckets[t];
+    if (!epi.begin() || b.r0 == b.r1) return;
+    const int tid = threadIdx.x;
+    UnitRegs<LOOP ? U : 1, Units> regs;
+    int64_t h = (int64_t)F * b.q0 + tid, end = (int64_t)F * b.q1;
+    if (LOOP && b.q0 < b.q1) bkt_fetch(units, pos, h, end, regs);
+    for (;;) {
+        const bool more = LOOP && t + (int)gridDim.x < nbuckets;
+        t = more ? t + (int)gridDim.x : t;
+        const Bucket nb = LOOP ? buckets[t] : b;
+        const int R = b.r1 - b.r0, nz = b.p1 - b.p0;
+        int rs[KP], re[KP], G = 64;
+        if (R <= NT)
+            while (G * R > NT) G >>= 1;
+        else
+            G = 1;
+        const int r0 = tid / G, lane = tid & (G - 1);
+        typename PreOf<Epi>::type pre[KP]{};
+        if (R > 1) {
+#pragma unroll
+            for (int k = 0; k < KP; ++k) {
+                const int r = r0 + k * NT;
+                if (r < R) {
+                    rs[k] = rp[b.r0 + r] - b.p0;
+                    re[k] = rp[b.r0 + r + 1] - b.p0;
+                }
+                if constexpr (has_pre<Epi>::value)
+                    if (tid + k * NT < R) pre[k] = epi.pre(b.r0 + tid + k * NT);
+            }
+        }
+        if constexpr (LOOP) {
+            if (b.q0 < b.q1) {
+                bkt_store(units, h, end, regs, s_prod);
+                // units beyond the registers (the padding of short runs)
+                bkt_fill<1>(units, pos, h + U * NT, end, s_prod);
+            }
+            h = (int64_t)F * nb.q0 + tid;
+            end = (int64_t)F * nb.q1;
+            if (more && nb.q0 < nb.q1) bkt_fetch(units, pos, h, end, regs);
+        } else {
+            bkt_fill<U>(units, pos, h, end, s_prod);
+        }
+        __syncthreads();
+        if (R == 1) {
+            Acc s = (Acc)0;
+            for (int p = tid; p < nz; p += NT) s += s_prod[p];
+            s = wave_sum(s);
+            if ((tid & 63) == 0) s_sum[tid >> 6] = s;
+            __syncthreads();
+            if (tid == 0) {
+                s = s_sum[0];
+                for (int w = 1; w < NT / 64; ++w) s += s_sum[w];
+                if (b.slot >= 0)
+                    part[b.slot * maxparts + b.part] = s;
+                else
+                    epi(b.r0, s);
+            }
+        } else if (R <= NT) {
+            Acc s = (Acc)0;
+            if (r0 < R)
+                for (int p = rs[0] + lane; p < re[0]; p += G) s += s_prod[p];
+            for (int o = G >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o);
+            if (r0 < R && lane == 0) s_sum[r0] = s;
+            __syncthreads();
+            if (tid < R) {
+                if constexpr (has_pre<Epi>::value)
+                    epi.fin(b.r0 + tid, s_sum[tid], pre[0]);
+                else
+                    epi(b.r0 + tid, s_sum[tid]);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < KP; ++k) {
+                const int r = tid + k * NT;
+                if (r < R) {
+                    Acc s = (Acc)0;
+                    for (int p = rs[k]; p < re[k]; ++p) s += s_prod[p];
+                    if constexpr (has_pre<Epi>::value)
+                        epi.fin(b.r0 + r, s, pre[k]);
+                    else
+                        epi(b.r0 + r, s);
+                }
+            }
+            for (int r = tid + KP * NT; r < R; r += NT) {
+                const int p1 = rp[b.r0 + r + 1] - b.p0;
+                Acc s = (Acc)0;
+                for (int p = rp[b.r0 + r] - b.p0; p < p1; ++p) s += s_prod[p];
+                epi(b.r0 + r, s);
+            }
+        }
+        if (!more) break;
+        b = nb;
+        __syncthreads();
+    }
+}
+
+template <typename Acc, class Units, class Epi>
+void run_sum(const DevCsr &M, const Units &units, Epi e, hipStream_t s) {
+    const DevBuckets &K = *M.bkt;
+    Acc *part = (Acc *)K.part;
+    // FP64 products fill a CU's LDS with one bucket: workgroups that stay and
+    // load ahead (multicommodity iteration 247 -> 237 us).  Two buckets fit in
+    // FP32, which overlap by themselves (139 us against 145).
+    constexpr bool loop = std::is_same<Units, PushedUnits<double>>::value;
+    constexpr int kCus = 256;
+    if (K.nbuckets > 0)
+        hipLaunchKernelGGL((k_bkt_sum<Acc, loop, Units, Epi>),
+                           dim3(loop && K.nbuckets > kCus ? kCus : K.nbuckets),
+                           dim3(kBktThreads), 0, s, K.buckets, K.nbuckets, M.rp,
+                           K.pos, units, part, K.maxparts, e);
+    if (K.nsplit > 0)
+        hipLaunchKernelGGL((k_split_fix<Acc, Epi>),
+                           dim3((K.nsplit + kFixThreads - 1) / kFixThreads),
+                           dim3(kFixThreads), 0, s, K.split, K.nsplit, part,
+                           K.maxparts, e);
+}
+
+template <typename Acc, typename MT, typename VT, class Epi>
+void run_buckets(const DevCsr &M, const MT *vals, const VT *in, Epi e,
+                 hipStream_t s) {
+    const DevBuckets &K = *M.bkt;
+    if (K.gcol) {
+        run_sum<Acc>(M, GatheredUnits<MT, VT, Acc>{K.gcol, vals, in}, e, s);
+        return;
+    }
+    Acc *prod = (Acc *)K.prod;
+    if (K.nitems > 0)
+        hipLaunchKernelGGL((k_bkt_push<MT, VT, Acc>), dim3(K.nitems),
+                           dim3(kBktThreads), 0, s, K.items, K.col, vals, K.dest,
+                           in, M.cols, prod);
+    run_sum<Acc>(M, PushedUnits<Acc>{prod}, e, s);
+}
+
 template <typename Acc, int TILE, class Elem, class Epi>
 void run_rowblock(const RowBlock *blk, int nblk, const SplitRow *split,
                   int nsplit, Acc *part, int maxparts, const int32_t *rp,
@@ -562,12 +895,20 @@ void run_bins(const DevCsr &M, Elem e, Epi p, hipStream_t s) {
 }
 
 // out-row r of M x epilogue, with M's values `vals` (its scaled FP64 or FP32
-// values, or others).  A panelled M runs its scaled values through the panel
-// twin (XCD-dealt panel pass, then the combine with the epilogue); any other
-// value array takes the plain bins.
+// values, or others).  The scaled values of an M with buckets run through
+// these, a panelled M's through the panel twin (XCD-dealt panel pass, in tiles
+// or row blocks, then the combine with the epilogue); any other value array
+// takes the plain bins.
 template <typename Acc, typename MT, typename VT, class Epi>
 void rb_spmv(const DevCsr &M, const MT *vals, const VT *in, Epi e,
              hipStream_t s) {
+    if (M.bkt) {
+        if constexpr (std::is_same<MT, double>::value) {
+            if (vals == M.v64 && M.bkt->f64) return run_buckets<Acc>(M, (const MT *)M.bkt->v64, in, e, s);
+        } else {
+            if (vals == M.v32) return run_buckets<Acc>(M, (const MT *)M.bkt->v32, in, e, s);
+        }
+    }
     const MT *tv = nullptr;
     if (M.pan) {
         if constexpr (std::is_same<MT, double>::value) {
@@ -588,7 +929,14 @@ void rb_spmv(const DevCsr &M, const MT *vals, const VT *in, Epi e,
         q = M.q64;
     else
         q = M.q32;
-    if (M.stream_nt)
+    if (M.pan->bkt && (M.pan->bkt->f64 || std::is_same<MT, float>::value)) {
+        const MT *kv;
+        if constexpr (std::is_same<MT, double>::value)
+            kv = M.pan->bkt->v64;
+        else
+            kv = M.pan->bkt->v32;
+        run_buckets<Acc>(*M.pan, kv, in, PanelEpi<Epi, Acc>{e, q}, s);
+    } else if (M.stream_nt)
         run_bins<Acc>(*M.pan, SpmvElem<MT, VT, Acc, true>{M.pan->ci, tv, in},
                       PanelEpi<Epi, Acc>{e, q}, s);
     else
@@ -1519,6 +1867,26 @@ void launch_permute(double *dst, const double *src, const int32_t *perm,
                     int64_t k, hipStream_t s) {
     hipLaunchKernelGGL(k_permute, dim3(grid_for(k, kWG, 16384)), dim3(kWG), 0,
                        s, dst, src, perm, k);
+}
+
+namespace {
+__global__ __launch_bounds__(kWG) void k_gather_pad(
+    double *__restrict__ dst, float *__restrict__ dst32,
+    const double *__restrict__ src, const int32_t *__restrict__ idx, int64_t k) {
+    for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < k;
+         i += (int64_t)gridDim.x * kWG) {
+        const int p = idx[i];
+        const double v = p < 0 ? 0.0 : src[p];
+        dst[i] = v;
+        dst32[i] = (float)v;
+    }
+}
+}  // namespace
+
+void launch_gather_pad(double *dst, float *dst32, const double *src,
+                       const int32_t *idx, int64_t k, hipStream_t s) {
+    hipLaunchKernelGGL(k_gather_pad, dim3(grid_for(k, kWG, 16384)), dim3(kWG),
+                       0, s, dst, dst32, src, idx, k);
 }
 
 void launch_gather(double *dst, const double *src, const int32_t *idx,

@@ -16,6 +16,7 @@
 #include <cstring>
 #include <deque>
 #include <functional>
+#include <future>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -129,6 +130,12 @@ struct pdhg_ctx {
     bool loaded = false, configured = false;
     int64_t m = 0, n = 0, nnz = 0;
     DevCsr A, At;
+    double *prod = nullptr;     // products of the push passes
+    // sides whose tiles are planned at the first FP32 iteration (A, A^T)
+    struct {
+        std::vector<int64_t> rp;
+        std::vector<int32_t> ci;
+    } later[2];
     // internal relabeling (rows and columns by decreasing length)
     int32_t *pr = nullptr;      // internal row -> original row of A
     int32_t *pc = nullptr;      // internal column -> original column
@@ -141,6 +148,7 @@ struct pdhg_ctx {
     int64_t split_threshold = (int64_t)1 << 20;
     int64_t split_chunk = (int64_t)1 << 16;
     int panels_a = 0, panels_at = 0;    // column panels per side; 0 = choose
+    int layout_a = LAYOUT_CHOOSE, layout_at = LAYOUT_CHOOSE;   // per side
     int stream_nt = -1;                 // streamed-load kind; -1 = choose
     int sort_rows = -1, sort_cols = -1; // length sort of rows / columns; -1 = by skew
     int block_rows = kWG;               // row cap of multi-row blocks; 0 = tile
@@ -340,9 +348,13 @@ size_t spmv_noalloc_bytes(int64_t cols, int64_t rows, int precision) {
 // from the same source) rounded from `vals` (nnz, M's order).
 void put_f32_values(pdhg_ctx *c, const DevCsr &M, const double *vals) {
     launch_to_f32(M.v32, vals, M.nnz, c->stream);
+    if (M.bkt)
+        launch_gather_pad(M.bkt->v64, M.bkt->v32, vals, M.bkt->src, 4 * M.bkt->quads, c->stream);
     if (M.pan) {
         launch_gather(M.pan->v64, vals, M.pan_src, M.nnz, c->stream);
         launch_to_f32(M.pan->v32, M.pan->v64, M.nnz, c->stream);
+        if (M.pan->bkt)
+            launch_gather_pad(M.pan->bkt->v64, M.pan->bkt->v32, M.pan->v64, M.pan->bkt->src, 4 * M.pan->bkt->quads, c->stream);
     }
 }
 
@@ -389,6 +401,20 @@ void free_csr(DevCsr &M) {
         free_csr(*M.pan);
         delete M.pan;
     }
+    if (DevBuckets *k = M.bkt) {
+        dfree(k->items);
+        dfree(k->buckets);
+        dfree(k->split);
+        dfree(k->col);
+        dfree(k->pos);
+        dfree(k->src);
+        dfree(k->dest);
+        dfree(k->gcol);
+        dfree(k->v64);
+        dfree(k->v32);
+        dfree(k->part);
+        delete k;
+    }
     dfree(M.pan_src);
     dfree(M.pan_mask);
     dfree(M.q64);
@@ -434,6 +460,8 @@ void free_problem(pdhg_ctx *c) {
     invalidate_graph(c);
     free_csr(c->A);
     free_csr(c->At);
+    dfree(c->prod);
+    for (auto &l : c->later) l = {};
     dfree(c->perm);
     dfree(c->rowidx);
     dfree(c->pr);
@@ -521,12 +549,48 @@ void upload_bins(DevCsr &M, const HostBins &b64, const HostBins &b32) {
 // kernels' aligned 16-byte group loads stay inside the allocation.
 int64_t padded(int64_t nnz) { return ((nnz + 3) & ~(int64_t)3) + 4; }
 
+// A vector to a device array of its own.
+template <typename T>
+T *upload(const std::vector<T> &h) {
+    T *d = dmalloc<T>((int64_t)h.size());
+    if (!h.empty()) HIPC(hipMemcpy(d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
+    return d;
+}
+
+// Buckets or tiles to the device (their values are filled by apply_scaling);
+// null when their rows do not fill them.
+DevBuckets *upload_buckets(const HostBuckets &H, bool f64, bool force) {
+    if (H.fragmented && !force) return nullptr;
+    DevBuckets *K = new DevBuckets();
+    K->f64 = f64;
+    K->quads = H.quads;
+    K->nitems = (int)H.items.size();
+    K->nbuckets = (int)H.buckets.size();
+    K->nsplit = (int)H.splits.size();
+    K->maxparts = H.maxparts;
+    K->buckets = upload(H.buckets);
+    K->split = upload(H.splits);
+    K->pos = upload(H.pos);
+    K->src = upload(H.src);
+    K->v64 = dmalloc<double>(4 * K->quads);
+    K->v32 = dmalloc<float>(4 * K->quads);
+    K->part = dmalloc<double>((int64_t)K->nsplit * K->maxparts);
+    if (!H.gcol.empty()) {
+        K->gcol = upload(H.gcol);
+    } else {
+        K->items = upload(H.items);
+        K->col = upload(H.col);
+        K->dest = upload(H.dest);
+    }
+    return K;
+}
+
 // The panel twin of M (P > 1): the stacked panel matrix with its own index
 // array and scaled values (filled by apply_scaling), XCD-dealt bins, and the
 // P * rows partial sums.
 void upload_panels(pdhg_ctx *c, DevCsr &M, const std::vector<int64_t> &rp,
                    const std::vector<int32_t> &ci, int P,
-                   const std::vector<int64_t> &cut) {
+                   const std::vector<int64_t> &cut, int layout, bool force) {
     Panels S = build_panels(M.rows, rp.data(), ci.data(), P, cut);
     M.P = P;
     M.pan = new DevCsr();
@@ -558,16 +622,21 @@ void upload_panels(pdhg_ctx *c, DevCsr &M, const std::vector<int64_t> &rp,
         M.pan_mask = dmalloc<uint8_t>(M.rows);
         HIPC(hipMemcpy(M.pan_mask, S.mask.data(), M.rows * sizeof(uint8_t), hipMemcpyHostToDevice));
     }
+    if (layout == LAYOUT_TILES)
+        T.bkt = upload_buckets(build_tiles(M.rows, S.rp.data(), S.ci.data(), P, force),
+                               force || M.nnz >= kTileMin64, force);
     M.q64 = dmalloc<double>(T.rows);
     M.q32 = dmalloc<float>(T.rows);
 }
 
 // Upload one CSR (int64 row pointers on the host) and build both bin sets;
-// with P > 1 also its panel twin.
+// with P > 1 also its panel twin, and its buckets (tiles of an unpanelled side
+// come from the thread that plans them meanwhile).
 void upload_csr(pdhg_ctx *c, DevCsr &M, int64_t rows, int64_t cols,
                 int64_t nnz, const std::vector<int64_t> &rp,
                 const std::vector<int32_t> &ci, const std::vector<double> &v,
-                int P, const std::vector<int64_t> &cut) {
+                int P, const std::vector<int64_t> &cut, int layout,
+                bool force, std::future<HostBuckets> tiles) {
     M.rows = rows;
     M.cols = cols;
     M.nnz = nnz;
@@ -592,7 +661,14 @@ void upload_csr(pdhg_ctx *c, DevCsr &M, int64_t rows, int64_t cols,
     // TILE entries then always covers them
     upload_bins(M, build_row_blocks(rows, rp.data(), kTile64 - 3, c->split_threshold, c->split_chunk, c->block_rows),
                 build_row_blocks(rows, rp.data(), kTile32 - 3, c->split_threshold, c->split_chunk, c->block_rows));
-    if (P > 1) upload_panels(c, M, rp, ci, P, cut);
+    if (layout == LAYOUT_PUSH)
+        M.bkt = upload_buckets(build_push(rows, cols, rp.data(), ci.data(), force), true, force);
+    if (M.bkt)
+        M.P = P;
+    else if (P > 1)
+        upload_panels(c, M, rp, ci, P, cut, layout, force);
+    else if (tiles.valid())
+        M.bkt = upload_buckets(tiles.get(), true, force);
     // stream the CSR non-temporally when the FP64 gather table each XCD
     // works on exceeds 3 MiB, so that streaming does not evict it from L2
     M.stream_nt = c->stream_nt >= 0 ? c->stream_nt
@@ -641,11 +717,29 @@ void apply_scaling(pdhg_ctx *c) {
     launch_scale_values(c->A, c->A.v_orig, c->dr, c->dc, c->A.v64, c->A.v32, c->stream);
     launch_permute(c->At.v64, c->A.v64, c->perm, c->nnz, c->stream);
     launch_to_f32(c->At.v32, c->At.v64, c->nnz, c->stream);
-    for (DevCsr *M : {&c->A, &c->At})
+    for (DevCsr *M : {&c->A, &c->At}) {
+        if (M->bkt)
+            launch_gather_pad(M->bkt->v64, M->bkt->v32, M->v64, M->bkt->src, 4 * M->bkt->quads, c->stream);
         if (M->pan) {
             launch_gather(M->pan->v64, M->v64, M->pan_src, c->nnz, c->stream);
             launch_to_f32(M->pan->v32, M->pan->v64, c->nnz, c->stream);
+            if (M->pan->bkt)
+                launch_gather_pad(M->pan->bkt->v64, M->pan->bkt->v32, M->pan->v64, M->pan->bkt->src, 4 * M->pan->bkt->quads, c->stream);
         }
+    }
+}
+
+// The tiles of sides that only FP32 products run in, before the first of them.
+void ensure_f32_tiles(pdhg_ctx *c) {
+    for (int k = 0; k < 2; ++k) {
+        auto &l = c->later[k];
+        if (l.rp.empty()) continue;
+        DevCsr &M = k ? c->At : c->A;
+        M.bkt = upload_buckets(build_tiles(M.rows, l.rp.data(), l.ci.data(), 1, false), false, false);
+        l = {};
+        if (M.bkt)
+            launch_gather_pad(M.bkt->v64, M.bkt->v32, M.v64, M.bkt->src, 4 * M.bkt->quads, c->stream);
+    }
 }
 
 void apply_rhs_scaling(pdhg_ctx *c) {
@@ -1331,6 +1425,15 @@ int pdhg_set_tuning(pdhg_ctx *c, const char *key, int64_t value) {
         c->panels_at = (int)value;
         return PDHG_OK;
     }
+    const bool lv = value >= LAYOUT_CHOOSE && value <= LAYOUT_PUSH;
+    if (std::strcmp(key, "layout_a") == 0 && lv) {
+        c->layout_a = (int)value;
+        return PDHG_OK;
+    }
+    if (std::strcmp(key, "layout_at") == 0 && lv) {
+        c->layout_at = (int)value;
+        return PDHG_OK;
+    }
     if (std::strcmp(key, "stream_nt") == 0 && value >= -1 && value <= 1) {
         c->stream_nt = (int)value;
         return PDHG_OK;
@@ -1385,12 +1488,39 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
     // stacked panel rows are indexed in int32: keep P * rows below 2^31
     while (pa > 1 && (int64_t)pa * m >= ((int64_t)1 << 31)) pa /= 2;
     while (pat > 1 && (int64_t)pat * n >= ((int64_t)1 << 31)) pat /= 2;
+    // a panel count that the caller asked for runs as row blocks
+    auto layout = [&](int asked, int panels, int64_t rows, int64_t cols, int P) {
+        return asked != LAYOUT_CHOOSE ? asked : panels ? LAYOUT_ROWS : choose_layout(rows, cols, nnz, P);
+    };
     Relabeled R = relabel(m, n, nnz, h_arp.data(), h_aci.data(), h_av.data(),
                           h_atrp.data(), pa, pat, c->sort_rows, c->sort_cols);
     std::vector<int32_t>().swap(h_aci);
     std::vector<double>().swap(h_av);
-    upload_csr(c, c->A, m, n, nnz, R.a_rp, R.a_ci, R.a_v, pa, R.a_cut);
-    upload_csr(c, c->At, n, m, nnz, R.at_rp, R.at_ci, R.at_v, pat, R.at_cut);
+    const int la = layout(c->layout_a, c->panels_a, m, n, pa);
+    const int lat = layout(c->layout_at, c->panels_at, n, m, pat);
+    const bool fa = c->layout_a != LAYOUT_CHOOSE, fat = c->layout_at != LAYOUT_CHOOSE;
+    // tiles of an unpanelled side: planned while the arrays are uploaded, or,
+    // where only FP32 products use them, kept for the first FP32 iteration
+    const bool ta = la == LAYOUT_TILES && pa == 1, tat = lat == LAYOUT_TILES && pat == 1;
+    auto plan = [&](bool on, int64_t rows, const std::vector<int64_t> &rp,
+                    const std::vector<int32_t> &ci, bool force) {
+        return on && (force || nnz >= kTileMin64)
+                   ? std::async(std::launch::async, [&rp, &ci, rows, force] {
+                         return build_tiles(rows, rp.data(), ci.data(), 1, force);
+                     })
+                   : std::future<HostBuckets>();
+    };
+    auto plan_a = plan(ta, m, R.a_rp, R.a_ci, fa);
+    auto plan_at = plan(tat, n, R.at_rp, R.at_ci, fat);
+    upload_csr(c, c->A, m, n, nnz, R.a_rp, R.a_ci, R.a_v, pa, R.a_cut, la, fa, std::move(plan_a));
+    upload_csr(c, c->At, n, m, nnz, R.at_rp, R.at_ci, R.at_v, pat, R.at_cut, lat, fat, std::move(plan_at));
+    // one product buffer for the push passes of both sides
+    int64_t prods = 0;
+    for (DevCsr *M : {&c->A, &c->At})
+        if (M->bkt && M->bkt->items) prods = std::max(prods, 4 * M->bkt->quads);
+    if (prods) c->prod = dmalloc<double>(prods);
+    for (DevCsr *M : {&c->A, &c->At})
+        if (M->bkt) M->bkt->prod = c->prod;
     std::vector<int32_t> ridx((size_t)nnz);
     for (int64_t i = 0; i < m; ++i)
         for (int64_t p = R.a_rp[i]; p < R.a_rp[i + 1]; ++p) ridx[p] = (int32_t)i;
@@ -1406,6 +1536,8 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
     }
     HIPC(hipMemcpy(c->pr, R.pr.data(), m * sizeof(int32_t), hipMemcpyHostToDevice));
     HIPC(hipMemcpy(c->pc, R.pc.data(), n * sizeof(int32_t), hipMemcpyHostToDevice));
+    if (ta && !c->A.bkt && !fa && nnz < kTileMin64) c->later[0] = {R.a_rp, R.a_ci};
+    if (tat && !c->At.bkt && !fat && nnz < kTileMin64) c->later[1] = {R.at_rp, R.at_ci};
     c->tmp_m = dmalloc<double>(m);
     c->tmp_n = dmalloc<double>(n);
     c->b_orig = dmalloc<double>(m);
@@ -1685,10 +1817,12 @@ int pdhg_configure(pdhg_ctx *c, const pdhg_params *p) {
     c->levels.assign(p->levels, p->levels + p->n_levels);
     c->params.levels = nullptr;
     c->prec = p->precision;
-    if (c->prec == PDHG_FP32)
+    if (c->prec == PDHG_FP32) {
+        ensure_f32_tiles(c);
         alloc_iter(c->v32, c->m, c->n);
-    else
+    } else {
         alloc_iter(c->v64, c->m, c->n);
+    }
     if (c->n_slots < (int)c->levels.size()) {
         dfree(c->slots);
         c->n_slots = (int)c->levels.size();
@@ -2400,6 +2534,7 @@ void refine_impl(pdhg_ctx *c, const pdhg_refine_params &R, pdhg_refine_info *inf
                 zero_iter(c, c->v64);
             } else {
                 c->prec = PDHG_FP32;
+                ensure_f32_tiles(c);
                 c->v32.bs = c->bh32;
                 c->v32.cs = c->ch32;
                 c->v32.ls = c->lh32;
@@ -2761,6 +2896,7 @@ int pdhg_unrolled_forward(pdhg_ctx *c, int K, int ckpt_every, int precision,
         s.sigma = sigma;
         s.status = PDHG_RUNNING;
         HIPC(hipMemcpyAsync(tp->st, &s, sizeof s, hipMemcpyHostToDevice, c->stream));
+        if (precision == PDHG_FP32) ensure_f32_tiles(c);
         if (precision == PDHG_FP32)
             unrolled_forward_T<float>(c, tp, x0, y0, xK, mem);
         else

@@ -1,0 +1,186 @@
+// Plans of the bucketed SpMV layouts (push and tiles), executed on the host as
+// the kernels execute them and compared with the plain CSR product on integer
+// data (exact).  Every index is checked against its buffer.  Prints one line
+// per matrix and layout.
+#include <algorithm>
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+
+#include "internal.h"
+
+using namespace pdhg;
+
+#define CHECK(c)                                                   \
+    do {                                                           \
+        if (!(c)) {                                                \
+            std::printf("FAILED %s line %d\n", #c, __LINE__);      \
+            std::exit(1);                                          \
+        }                                                          \
+    } while (0)
+
+namespace {
+
+struct Csr {
+    int64_t m, n;
+    std::vector<int64_t> rp{0};
+    std::vector<int32_t> ci;
+};
+
+// kind 0: even lengths; 1: every 97th row 60 times longer; 2: empty stretches
+// and one full row; 3: a row 1,500 times longer among every 40
+Csr make(int64_t m, int64_t n, double avg, int kind, std::mt19937_64 &g) {
+    Csr A{m, n};
+    for (int64_t i = 0; i < m; ++i) {
+        double a = avg;
+        if (kind == 1 && i % 97 == 0) a *= 60;
+        if (kind == 2 && (i / 20000) % 2) a = 0;
+        if (kind == 3 && i % 40 == 0) a *= 1500;
+        int64_t L = std::min<int64_t>(n, (int64_t)(a * (0.5 + (double)(g() % 1000) / 1000.0) + 0.5));
+        if (kind == 2 && i == 77) L = n;
+        std::vector<int32_t> r;
+        for (int64_t k = 0; k < L; ++k) r.push_back(L == n ? (int32_t)k : (int32_t)(g() % n));
+        std::sort(r.begin(), r.end());
+        r.erase(std::unique(r.begin(), r.end()), r.end());
+        A.ci.insert(A.ci.end(), r.begin(), r.end());
+        A.rp.push_back((int64_t)A.ci.size());
+    }
+    return A;
+}
+
+// Rows of a bucket summed from its products in LDS order.
+void sum_rows(const HostBuckets &B, const Bucket &b, const std::vector<double> &s,
+              const std::vector<int64_t> &rp, std::vector<double> &part,
+              std::vector<double> &y) {
+    if (b.slot >= 0) {
+        double t = 0;
+        for (int64_t p = 0; p < b.p1 - b.p0; ++p) t += s[p];
+        part[b.slot * B.maxparts + b.part] = t;
+        return;
+    }
+    for (int64_t r = b.r0; r < b.r1; ++r) {
+        double t = 0;
+        CHECK(rp[r] >= b.p0 && rp[r + 1] <= b.p1);
+        for (int64_t p = rp[r]; p < rp[r + 1]; ++p) t += s[p - b.p0];
+        CHECK(std::isnan(y[r]));
+        y[r] = t;
+    }
+}
+
+void finish(const HostBuckets &B, const std::vector<double> &part, std::vector<double> &y) {
+    for (size_t t = 0; t < B.splits.size(); ++t) {
+        double q = 0;
+        for (int k = 0; k < B.splits[t].nparts; ++k) q += part[t * B.maxparts + k];
+        y[B.splits[t].row] = q;
+    }
+}
+
+}  // namespace
+
+int main() {
+    std::mt19937_64 g(1);
+    struct Case {
+        int64_t m, n;
+        double avg;
+        int kind;
+    };
+    for (Case c : {Case{1, 1, 1, 0}, Case{5, 3, 0, 0}, Case{3000, 40000, 7, 0},
+                   Case{40000, 3000, 3, 0}, Case{200, 100000, 300, 1},
+                   Case{100000, 50000, 2, 2}, Case{1, 50000, 40000, 0},
+                   Case{30000, kBktCols, 9, 1}, Case{30000, kBktCols + 1, 0.3, 0},
+                   Case{20000, 70001, 3, 3}, Case{300000, 400000, 12, 0}}) {
+        const Csr A = make(c.m, c.n, c.avg, c.kind, g);
+        const int64_t nnz = (int64_t)A.ci.size();
+        std::vector<double> x(c.n), v(nnz), ref(c.m);
+        for (auto &t : x) t = (double)(int64_t)(g() % 2001) - 1000;
+        for (auto &t : v) t = (double)(int64_t)(g() % 201) - 100;
+        for (int64_t i = 0; i < c.m; ++i)
+            for (int64_t p = A.rp[i]; p < A.rp[i + 1]; ++p) ref[i] += v[p] * x[A.ci[p]];
+        {
+            const HostBuckets B = build_push(c.m, c.n, A.rp.data(), A.ci.data(), true);
+            std::vector<double> prod(4 * B.quads, NAN), y(c.m, NAN);
+            std::vector<char> written(B.quads, 0), seen(nnz, 0);
+            int64_t covered = 0;
+            for (const PushItem &it : B.items) {
+                if (it.q0 == it.q1) continue;
+                CHECK(it.q0 >= 0 && it.q0 < it.q1 && it.q1 <= B.quads);
+                const int64_t c0 = (int64_t)it.cb * kBktCols;
+                CHECK(it.cb >= 0 && c0 < c.n);
+                for (int64_t q = it.q0; q < it.q1; ++q, ++covered) {
+                    CHECK(B.dest[q] >= 0 && B.dest[q] < B.quads && !written[B.dest[q]]);
+                    written[B.dest[q]] = 1;
+                    for (int i = 0; i < 4; ++i) {
+                        const int64_t e = 4 * q + i, p = B.src[e];
+                        CHECK(B.col[e] < kBktCols && p < nnz);
+                        if (p >= 0) {
+                            CHECK(!seen[p] && A.ci[p] == c0 + B.col[e]);
+                            seen[p] = 1;
+                        } else {
+                            CHECK(B.col[e] == 0);
+                        }
+                        prod[4 * (int64_t)B.dest[q] + i] = (p < 0 ? 0.0 : v[p]) * x[c0 + B.col[e]];
+                    }
+                }
+            }
+            CHECK(covered == B.quads);
+            CHECK(std::count(seen.begin(), seen.end(), 1) == nnz);
+            std::vector<double> part(B.splits.size() * B.maxparts, NAN);
+            for (const Bucket &b : B.buckets) {
+                std::vector<double> s(kBktCap + 1, NAN);
+                CHECK(b.r0 >= 0 && b.r0 < b.r1 && b.r1 <= c.m && b.p1 - b.p0 <= kBktCap);
+                CHECK(b.q0 >= 0 && b.q0 <= b.q1 && b.q1 <= B.quads);
+                for (int64_t e = 4 * (int64_t)b.q0; e < 4 * (int64_t)b.q1; ++e) {
+                    CHECK(B.pos[e] <= kBktCap);
+                    s[B.pos[e]] = prod[e];
+                }
+                sum_rows(B, b, s, A.rp, part, y);
+            }
+            finish(B, part, y);
+            CHECK(y == ref);
+            std::printf("push m %ld n %ld nnz %ld kind %d quads %ld buckets %zu splits %zu fragmented %d\n",
+                        (long)c.m, (long)c.n, (long)nnz, c.kind, (long)B.quads,
+                        B.buckets.size(), B.splits.size(), (int)B.fragmented);
+        }
+        for (int P : {1, 2, 8}) {
+            std::vector<int64_t> cut;
+            for (int p = 0; p <= P; ++p) cut.push_back(c.n * p / P);
+            const Panels S = build_panels(c.m, A.rp.data(), A.ci.data(), P, cut);
+            const HostBuckets B = build_tiles(c.m, S.rp.data(), S.ci.data(), P, true);
+            std::vector<double> part(B.splits.size() * B.maxparts, NAN), ys(P * c.m, NAN), y(c.m, 0.0);
+            std::vector<char> seen(nnz, 0);
+            CHECK((int64_t)B.gcol.size() == 4 * B.quads && B.pos.size() == B.gcol.size() &&
+                  B.src.size() == B.gcol.size());
+            for (size_t w = 0; w < B.buckets.size(); ++w) {
+                const Bucket &b = B.buckets[w];
+                if (b.r0 == b.r1) continue;
+                CHECK(b.r0 / c.m == (b.r1 - 1) / c.m && (int)(w % 8) % P == b.r0 / c.m);
+                CHECK(b.p1 - b.p0 <= kBktCap && b.q0 >= 0 && b.q0 <= b.q1 && b.q1 <= B.quads);
+                std::vector<double> s(kBktCap + 1, NAN);
+                for (int64_t e = 4 * (int64_t)b.q0; e < 4 * (int64_t)b.q1; ++e) {
+                    const int32_t p = B.src[e];
+                    CHECK(B.gcol[e] >= 0 && B.gcol[e] < c.n);
+                    if (p >= 0) {
+                        CHECK(!seen[p] && S.ci[p] == B.gcol[e] && B.pos[e] == p - b.p0);
+                        seen[p] = 1;
+                    } else {
+                        CHECK(B.pos[e] == kBktCap);
+                    }
+                    s[B.pos[e]] = p < 0 ? 0.0 : v[S.src[p]] * x[B.gcol[e]];
+                }
+                sum_rows(B, b, s, S.rp, part, ys);
+            }
+            CHECK(std::count(seen.begin(), seen.end(), 1) == nnz);
+            finish(B, part, ys);
+            for (int64_t i = 0; i < c.m; ++i)
+                for (int p = 0; p < P; ++p)
+                    if (P == 1 || (S.mask[i] >> p & 1)) y[i] += ys[(int64_t)p * c.m + i];
+            CHECK(y == ref);
+            std::printf("tiles m %ld n %ld nnz %ld kind %d panels %d quads %ld buckets %zu splits %zu fragmented %d\n",
+                        (long)c.m, (long)c.n, (long)nnz, c.kind, P, (long)B.quads,
+                        B.buckets.size(), B.splits.size(), (int)B.fragmented);
+        }
+    }
+    std::printf("done\n");
+    return 0;
+}

@@ -114,6 +114,64 @@ def test_spmv_bins_bitwise_on_integers(Solver, split, panels):
     s.close()
 
 
+LAYOUT_KINDS = {"tiles": {"layout_a": 1, "layout_at": 1},
+                "tiles_in_panels": {"layout_a": 1, "layout_at": 1, "panels_a": 4, "panels_at": 8},
+                "push": {"layout_a": 2, "layout_at": 2}}
+
+
+@pytest.mark.parametrize("kind", list(LAYOUT_KINDS))
+def test_bucketed_spmv_bitwise_on_integers(Solver, kind):
+    """Products through tiles and through pushed products equal numpy exactly
+    on integers, in both precisions: rows from empty to longer than a bucket
+    (16,384), column counts on both sides of a column block, and buckets of one
+    row, of fewer rows than lanes and of more."""
+    rng = np.random.default_rng(5)
+    for m, n, lens in ((7, 40_000, [0, 1, 16_384, 16_385, 40_000, 0, 3]),
+                       (3, 16_384, [5, 16_384, 16_383]), (4, 16_385, [16_385, 1, 0, 9]),
+                       (30_000, 900, rng.integers(0, 4, 30_000)),
+                       (2_000, 33_000, rng.integers(60, 140, 2_000)),
+                       (1, 1, [1])):
+        rows = np.repeat(np.arange(m), lens)
+        cols = np.concatenate([np.sort(rng.choice(n, L, replace=False)) for L in lens])
+        vals = rng.integers(-3, 4, rows.size).astype(float)
+        lp = lpgen.from_coo(m, n, rows, cols, vals, np.ones(m), np.ones(n))
+        x, y = rng.integers(-3, 4, n).astype(float), rng.integers(-3, 4, m).astype(float)
+        ref = (np.bincount(rows, weights=vals * x[cols], minlength=m),
+               np.bincount(cols, weights=vals * y[rows], minlength=n))
+        with Solver.from_lp(lp, tuning=LAYOUT_KINDS[kind]) as s:
+            for precision in (0, 1):
+                for which, vec in ((0, x), (1, y)):
+                    # (scaled: unit factors until configure)
+                    got = s.spmv(which, vec, scaled=True, precision=precision)
+                    assert np.array_equal(got, ref[which]), (m, n, which, precision)
+                    got = s.spmv(which, vec, scaled=False, precision=precision)
+                    assert np.array_equal(got, ref[which]), (m, n, which, precision)
+
+
+@pytest.mark.parametrize("kind", list(LAYOUT_KINDS))
+@pytest.mark.parametrize("variant", [0, 1])
+def test_iterates_match_in_bucketed_layouts(Solver, oracle, variant, kind):
+    """100 iterates within 1e-10 of the oracle with lower bounds and skewed
+    columns, new values and a re-configuration in between, and FP32 iterates
+    within FP32 rounding of the row-block path's."""
+    lp = lpgen.planted_powerlaw(m=700, n=2500, kmax=600, seed=17)
+    l = np.random.default_rng(3).uniform(-0.5, 0.1, lp.n)
+    worst = _trace_parity(Solver, oracle, lp, 100, l=l, eps_rel=1e-8, eval_every=32,
+                          max_iters=101, variant=variant, tuning=LAYOUT_KINDS[kind])
+    assert worst <= 1e-10, worst
+    v = lp.a_v * np.random.default_rng(4).uniform(0.5, 2.0, lp.nnz)
+    out = []
+    for tuning in (LAYOUT_KINDS[kind], None):
+        with Solver.from_lp(lp, tuning=tuning) as s:
+            s.configure(variant=variant)
+            s.set_values(v)
+            s.configure(variant=variant, precision=1)
+            s.iterate(100)
+            out.append(s.get_iterate())
+    for a, b in zip(*out):
+        assert err(a, b) <= 1e-4
+
+
 def test_ruiz_factors_bitwise(Solver, oracle):
     for lp in (lpgen.make("uniform_m500_n1k"),
                lpgen.planted_powerlaw(m=2000, n=10000, kmax=1500, seed=7)):
