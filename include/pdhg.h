@@ -586,6 +586,9 @@ int pdhg_spmv_noalloc(pdhg_ctx *ctx, int which, int scaled, int precision,
  *      (default) chooses from the sizes.  Sums stay deterministic but round
  *      differently; the keys below on blocks and splits are those of layout 0,
  *      which a panel count other than 0 also selects under -1;
+ *  "small": 1 (default) lets an LP of at most about 4,000 columns, 2,000 rows
+ *      and 25,000 nonzeros iterate in one workgroup when none of the layout,
+ *      panel, split, stream or block keys is set; 0 does not;
  *  "split_threshold": nnz above which a row is split over several
  *      workgroups; "split_chunk": nnz per split part;
  *  "panels_a", "panels_at": column panels (1, 2, 4 or 8; 0 = chosen from

@@ -816,6 +816,50 @@ HostBuckets build_tiles(int64_t rows, const int64_t *rp, const int32_t *ci,
     return B;
 }
 
+HostSmall build_small(int64_t rows, int64_t cols, const int64_t *rp,
+                      const int32_t *ci) {
+    HostSmall S;
+    S.G = 64;
+    while (S.G > 1 && S.G * rows > kSmallThreads) S.G >>= 1;
+    const int64_t per = kSmallThreads / S.G;     // rows per slot
+    S.K = (int)((rows + per - 1) / per);
+    std::vector<int32_t> order((size_t)rows);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+        return rp[a + 1] - rp[a] > rp[b + 1] - rp[b];
+    });
+    S.row.assign((size_t)(S.K * per), -1);
+    for (int64_t r = 0; r < rows; ++r) {
+        // every second slot from the other end: long rows next to short ones
+        const int64_t k = r / per, i = r % per;
+        S.row[k * per + (k & 1 ? per - 1 - i : i)] = order[r];
+    }
+    S.off.assign(1, 0);
+    for (int64_t sl = 0; sl < (int64_t)S.K * kSmallWaves; ++sl) {
+        int64_t steps = 0;
+        for (int64_t l = 0; l < 64; l += S.G) {
+            const int32_t r = S.row[(sl * 64 + l) / S.G];
+            if (r >= 0) steps = std::max(steps, (rp[r + 1] - rp[r] + S.G - 1) / S.G);
+        }
+        S.off.push_back(S.off.back() + (int32_t)((steps + 1) / 2));
+    }
+    S.src.assign((size_t)S.off.back() * 128, -1);
+    S.col.assign((size_t)S.off.back() * 128, (uint16_t)cols);
+    for (int64_t sl = 0; sl < (int64_t)S.K * kSmallWaves; ++sl)
+        for (int64_t l = 0; l < 64; ++l) {
+            const int32_t r = S.row[(sl * 64 + l) / S.G];
+            if (r < 0) continue;
+            // lane g of the row's G takes entries g, g + G, ...
+            int64_t step = 0;
+            for (int64_t p = rp[r] + l % S.G; p < rp[r + 1]; p += S.G, ++step) {
+                const int64_t e = ((S.off[sl] + step / 2) * 64 + l) * 2 + step % 2;
+                S.src[e] = (int32_t)p;
+                S.col[e] = (uint16_t)ci[p];
+            }
+        }
+    return S;
+}
+
 // Which layout a side runs in, from its sizes (P: its column panels).  A
 // gather costs a line from L2 to the CU; a tile shares a line among its
 // gathers, which pays while a panel's part of the vector has few more lines

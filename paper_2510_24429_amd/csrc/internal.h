@@ -136,6 +136,55 @@ struct DevBuckets {
     void *part = nullptr;             // partial sums of split rows
 };
 
+// A small LP iterates in one workgroup of kSmallThreads lanes (k_small in
+// kernels.hip).  Each row of a side is summed by G lanes (a power of two); a
+// lane holds K rows in slots.  Rows are dealt by decreasing length, and a
+// slice (64 lanes of one slot) keeps its nonzeros in pairs of steps: pair t of
+// lane l at (off + t) * 64 + l, padded to the slice's longest row.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / 64;
+template <typename T>
+struct SmallCap {
+    static constexpr int KX = 4;       // columns per lane
+    static constexpr int KY = 2;       // rows per lane
+    static constexpr int64_t nnz = sizeof(T) == 8 ? 24576 : 40960;
+};
+struct HostSmall {
+    int G = 1, K = 1;
+    std::vector<int32_t> off;         // K * kSmallWaves + 1: first pair of a slice
+    std::vector<int32_t> row;         // K * kSmallThreads / G: row of each (-1: none)
+    std::vector<int32_t> src;         // 128 * pairs: position in the CSR (-1: padding)
+    std::vector<uint16_t> col;        // 128 * pairs: column (cols: padding)
+};
+HostSmall build_small(int64_t rows, int64_t cols, const int64_t *rp,
+                      const int32_t *ci);
+// Measured, us an iteration of two launches | in one workgroup (Halpern, with
+// the evaluations' share), m x n with nonzeros: FP64 500 x 1000, 5k 7.5 | 1.9;
+// 900 x 2000, 12k 8.7 | 3.4; 1300 x 3000, 12k 8.9 | 4.7; 1501 x 3500, 17.5k
+// 8.5 | 6.2; 2000 x 4000, 28k 8.6 | 8.1; FP32 8.7 | 1.8, 9.6 | 3.0, 9.5 | 3.0,
+// 9.7 | 4.5, 9.7 | 5.9.  A row keeps its lanes for longest / G steps in a row.
+template <typename T>
+inline bool small_fits(int64_t m, int64_t n, int64_t nnz, int64_t longest_a,
+                       int64_t longest_at) {
+    using C = SmallCap<T>;
+    auto lanes = [](int64_t rows) {
+        int64_t G = 64;
+        while (G > 1 && G * rows > kSmallThreads) G >>= 1;
+        return G;
+    };
+    return nnz <= C::nnz && n <= C::KX * kSmallThreads && m <= C::KY * kSmallThreads &&
+           longest_a <= 48 * lanes(m) && longest_at <= 48 * lanes(n);
+}
+struct DevSmall {
+    int G = 1, K = 1;
+    int64_t entries = 0;
+    char *base = nullptr;             // the allocation of all that follows
+    int32_t *off = nullptr, *row = nullptr, *src = nullptr;
+    uint16_t *col = nullptr;
+    double *v64 = nullptr;            // scaled values in the order of src
+    float *v32 = nullptr;
+};
+
 // The internal (relabeled) problem: row i' of A' is row pr[i'] of A, column
 // j' of A' is column pc[j'] of A; apos[p'] is the position in A's arrays of
 // A''s nonzero p'; perm[p'] its position in A'^T's arrays.
@@ -176,6 +225,7 @@ struct DevCsr {
     int P = 1;
     int stream_nt = 0;          // non-temporal streamed loads (see kernels)
     DevBuckets *bkt = nullptr;  // tiles or push buckets
+    DevSmall *small = nullptr;
     DevCsr *pan = nullptr;
     int32_t *pan_src = nullptr;
     uint8_t *pan_mask = nullptr;  // per row: which panels hold entries of it
@@ -265,6 +315,13 @@ void launch_primal_halpern(const DevCsr &At, const Iter<T> &v, bool has_l,
 template <typename T>
 void launch_dual_halpern(const DevCsr &A, const Iter<T> &v, const State *st,
                          int off, hipStream_t s);
+// `count` iterations of a small LP (either variant; plain: no average) in one
+// launch; tx / ty (may be null) get the iterates after each step.
+enum { SMALL_AVG = 0, SMALL_HALPERN = 1, SMALL_PLAIN = 2 };
+template <typename T>
+void launch_small(const DevCsr &A, const DevCsr &At, const Iter<T> &v,
+                  bool has_l, int mode, const State *st, int off, int count,
+                  T *tx, T *ty, hipStream_t s);
 // Halpern evaluation: T(z) of the current iterate in FP64 arithmetic, into
 // v.xbar / v.ybar, with aty = A~^T y and axh = A~ x^ (FP64); axc is A~ x of
 // the current iterate (FP64).

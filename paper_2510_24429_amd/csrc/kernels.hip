@@ -1031,6 +1031,255 @@ void launch_eval_T(const DevCsr &A, const DevCsr &At, const Iter<T> &v,
                     DualEvalEpi<T>{v.y, axc, bs, v.ybar, axh, st}, s);
 }
 
+// ------------------------------------------------------------ small LPs
+
+namespace {
+
+template <typename T>
+struct SmallSide {
+    const int32_t *off, *row;
+    const uint16_t *col;
+    const T *val;
+    int G, K, rows;
+};
+
+template <typename T>
+struct SmallArgs {
+    SmallSide<T> at, a;
+    Iter<T> v;
+    const State *st;
+    int off, count;
+    T *tx, *ty;
+};
+
+// NP consecutive pairs of steps of one slice.
+template <typename T, int NP>
+struct SmallPairs {
+    T a[NP][2];
+    v2us j[NP];
+    // pairs t.. of a slice that ends at pair t1
+    __device__ __forceinline__ void load(const SmallSide<T> &s, int t, int t1) {
+        using V2 = T __attribute__((ext_vector_type(2)));
+        // uniform bases and one lane offset: addresses take few registers
+        const unsigned l = threadIdx.x & 63;
+        const V2 *val = (const V2 *)s.val + (int64_t)t * 64;
+        const v2us *col = (const v2us *)s.col + (int64_t)t * 64;
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+            if (t + u < t1) {
+                const V2 v = (val + u * 64)[l];
+                a[u][0] = v.x;
+                a[u][1] = v.y;
+                j[u] = (col + u * 64)[l];
+            }
+    }
+    __device__ __forceinline__ T dot(const T *s_x, int t, int t1, T acc) const {
+        T x[NP][2];
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+            if (t + u < t1) {
+                x[u][0] = s_x[j[u].x];
+                x[u][1] = s_x[j[u].y];
+            }
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+            if (t + u < t1) acc += a[u][0] * x[u][0] + a[u][1] * x[u][1];
+        return acc;
+    }
+};
+
+// Sum of this lane's row in the slice [t, t1), whose first pairs are given.
+template <typename T, int NP>
+__device__ __forceinline__ T small_row(const SmallSide<T> &s, const T *s_x,
+                                       const SmallPairs<T, NP> &first, int t,
+                                       int t1) {
+    T acc = first.dot(s_x, t, t1, (T)0);
+    for (t += NP; t < t1; t += 2) {
+        SmallPairs<T, 2> p;
+        p.load(s, t, t1);
+        acc = p.dot(s_x, t, t1, acc);
+    }
+    for (int o = s.G >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    return acc;
+}
+
+// `count` iterations in one workgroup.  On an LP of a few thousand nonzeros an
+// iteration of two launches is all latency; here the gathered vectors stay in
+// LDS, a row's other operands and the first NP pairs of its nonzeros with its
+// lane (the rest streams from L2), and one barrier ends each half.
+template <typename T, int MODE, int KX, int KY, int NP>
+__global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs<T> g) {
+    constexpr int NT = kSmallThreads;
+    __shared__ T s_x[KX * NT + 1];
+    __shared__ T s_y[KY * NT + 1];
+    if (g.st->status != PDHG_RUNNING) return;
+    const T tau = (T)g.st->tau, sigma = (T)g.st->sigma, rho = (T)g.st->reflect;
+    const long long t0 = g.st->t_base + g.off;
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = g.at.rows, m = g.a.rows;
+    // this lane's columns and rows (-1: none; one lane of a row's G keeps it)
+    // and their operands (xa, ya: average or anchor), and the wave's slices
+    T x[KX], xa[KX], c[KX], l[KX], y[KY], ya[KY], b[KY], ax[KY], ax0[KY];
+    int jx[KX], iy[KY], ex[KX], fx[KX], ey[KY], fy[KY];
+#pragma unroll
+    for (int k = 0; k < KX; ++k) {
+        x[k] = xa[k] = c[k] = l[k] = (T)0;
+        jx[k] = -1;
+        ex[k] = fx[k] = 0;
+        if (k < g.at.K) {
+            ex[k] = g.at.off[k * kSmallWaves + w];
+            fx[k] = g.at.off[k * kSmallWaves + w + 1];
+            if (tid % g.at.G == 0) jx[k] = g.at.row[(k * NT + tid) / g.at.G];
+        }
+        const int j = jx[k];
+        if (j >= 0) {
+            x[k] = g.v.x[j];
+            c[k] = g.v.cs[j];
+            if (g.v.ls) l[k] = g.v.ls[j];
+            if (MODE == SMALL_AVG) xa[k] = g.v.xbar[j];
+            if (MODE == SMALL_HALPERN) xa[k] = g.v.xl[j];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < KY; ++k) {
+        y[k] = ya[k] = b[k] = ax[k] = ax0[k] = (T)0;
+        iy[k] = -1;
+        ey[k] = fy[k] = 0;
+        if (k < g.a.K) {
+            ey[k] = g.a.off[k * kSmallWaves + w];
+            fy[k] = g.a.off[k * kSmallWaves + w + 1];
+            if (tid % g.a.G == 0) iy[k] = g.a.row[(k * NT + tid) / g.a.G];
+        }
+        const int i = iy[k];
+        if (i >= 0) {
+            y[k] = g.v.y[i];
+            b[k] = g.v.bs[i];
+            ax[k] = g.v.ax[i];
+            if (MODE == SMALL_AVG) ya[k] = g.v.ybar[i];
+            if (MODE == SMALL_HALPERN) {
+                ya[k] = g.v.yl[i];
+                ax0[k] = g.v.ax0[i];
+            }
+            s_y[i] = y[k];
+        }
+    }
+    if (tid == 0) s_x[n] = s_y[m] = (T)0;      // what padding gathers
+    SmallPairs<T, NP> px[KX], py[KY];
+#pragma unroll
+    for (int k = 0; k < KX; ++k) px[k].load(g.at, ex[k], fx[k]);
+#pragma unroll
+    for (int k = 0; k < KY; ++k) py[k].load(g.a, ey[k], fy[k]);
+    __syncthreads();
+    for (int it = 0; it < g.count; ++it) {
+        const double td = (double)(t0 + it + 1);
+        const T t = (T)td, lam = (T)(td / (td + 1.0));
+#pragma unroll
+        for (int k = 0; k < KX; ++k) {
+            if (k >= g.at.K) break;
+            const T s = small_row(g.at, s_y, px[k], ex[k], fx[k]);
+            const int j = jx[k];
+            if (j >= 0) {
+                const T v = x[k] - tau * (c[k] - s);
+                const T xn = v < l[k] ? l[k] : v;
+                s_x[j] = xn;
+                if (MODE == SMALL_HALPERN) {
+                    x[k] = lam * (((T)1 + rho) * xn - rho * x[k]) + ((T)1 - lam) * xa[k];
+                } else {
+                    x[k] = xn;
+                    if (MODE == SMALL_AVG) xa[k] = xa[k] + (xn - xa[k]) / t;
+                    if (MODE == SMALL_PLAIN && g.tx) g.tx[(int64_t)it * n + j] = xn;
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < KY; ++k) {
+            if (k >= g.a.K) break;
+            const T q = small_row(g.a, s_x, py[k], ey[k], fy[k]);
+            const int i = iy[k];
+            if (i >= 0) {
+                const T yh = y[k] + sigma * (b[k] - ((q + q) - ax[k]));
+                if (MODE == SMALL_HALPERN) {
+                    y[k] = lam * (((T)1 + rho) * yh - rho * y[k]) + ((T)1 - lam) * ya[k];
+                    ax[k] = lam * (((T)1 + rho) * q - rho * ax[k]) + ((T)1 - lam) * ax0[k];
+                } else {
+                    y[k] = yh;
+                    ax[k] = q;
+                    if (MODE == SMALL_AVG) ya[k] = ya[k] + (yh - ya[k]) / t;
+                    if (MODE == SMALL_PLAIN && g.ty) g.ty[(int64_t)it * m + i] = yh;
+                }
+                s_y[i] = y[k];
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < KX; ++k)
+        if (jx[k] >= 0) {
+            g.v.x[jx[k]] = x[k];
+            if (MODE == SMALL_AVG) g.v.xbar[jx[k]] = xa[k];
+            if (MODE == SMALL_HALPERN) g.v.xbar[jx[k]] = s_x[jx[k]];
+        }
+#pragma unroll
+    for (int k = 0; k < KY; ++k)
+        if (iy[k] >= 0) {
+            g.v.y[iy[k]] = y[k];
+            g.v.ax[iy[k]] = ax[k];
+            if (MODE == SMALL_AVG) g.v.ybar[iy[k]] = ya[k];
+        }
+}
+
+template <typename T>
+SmallSide<T> small_side(const DevCsr &M) {
+    const DevSmall &S = *M.small;
+    const T *v;
+    if constexpr (sizeof(T) == 8)
+        v = S.v64;
+    else
+        v = S.v32;
+    return {S.off, S.row, S.col, v, S.G, S.K, (int)M.rows};
+}
+
+}  // namespace
+
+template <typename T>
+void launch_small(const DevCsr &A, const DevCsr &At, const Iter<T> &v,
+                  bool has_l, int mode, const State *st, int off, int count,
+                  T *tx, T *ty, hipStream_t s) {
+    SmallArgs<T> g{small_side<T>(At), small_side<T>(A), v, st, off, count, tx, ty};
+    if (!has_l) g.v.ls = nullptr;
+    auto run = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(1), dim3(kSmallThreads), 0, s, g);
+    };
+    auto sized = [&](auto kx, auto ky, auto np) {
+        constexpr int KX = decltype(kx)::value, KY = decltype(ky)::value,
+                      NP = decltype(np)::value;
+        if (mode == SMALL_HALPERN)
+            run(k_small<T, SMALL_HALPERN, KX, KY, NP>);
+        else if (mode == SMALL_AVG)
+            run(k_small<T, SMALL_AVG, KX, KY, NP>);
+        else
+            run(k_small<T, SMALL_PLAIN, KX, KY, NP>);
+    };
+    // as many pairs as the registers of a lane (128) hold beside its rows
+    using std::integral_constant;
+    constexpr bool d = sizeof(T) == 8;
+    if (g.at.K <= 1 && g.a.K <= 1)
+        sized(integral_constant<int, 1>(), integral_constant<int, 1>(), integral_constant<int, d ? 4 : 6>());
+    else if (g.at.K <= 2 && g.a.K <= 1)
+        sized(integral_constant<int, 2>(), integral_constant<int, 1>(), integral_constant<int, d ? 2 : 4>());
+    else
+        sized(integral_constant<int, 4>(), integral_constant<int, 2>(), integral_constant<int, d ? 1 : 2>());
+}
+template void launch_small<double>(const DevCsr &, const DevCsr &,
+                                   const Iter<double> &, bool, int,
+                                   const State *, int, int, double *, double *,
+                                   hipStream_t);
+template void launch_small<float>(const DevCsr &, const DevCsr &,
+                                  const Iter<float> &, bool, int, const State *,
+                                  int, int, float *, float *, hipStream_t);
+
 #define INST_HALPERN(T)                                                        \
     template void launch_primal_halpern<T>(const DevCsr &, const Iter<T> &,   \
                                            bool, const State *, int,          \

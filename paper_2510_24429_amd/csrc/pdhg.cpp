@@ -98,6 +98,8 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 namespace {
 
 constexpr int kMaxDevices = 64;
+constexpr int64_t kSplitThreshold = (int64_t)1 << 20, kSplitChunk = (int64_t)1 << 16;
+constexpr int kSmallSteps = 4096;     // most iterations of one k_small launch
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices] = {nullptr};
 
@@ -131,6 +133,7 @@ struct pdhg_ctx {
     int64_t m = 0, n = 0, nnz = 0;
     DevCsr A, At;
     double *prod = nullptr;     // products of the push passes
+    bool small64 = false, small32 = false;   // iterates in one workgroup
     // sides whose tiles are planned at the first FP32 iteration (A, A^T)
     struct {
         std::vector<int64_t> rp;
@@ -145,10 +148,11 @@ struct pdhg_ctx {
     double *tmp_m = nullptr, *tmp_n = nullptr;  // staging for I/O
     double *b_orig = nullptr, *c_orig = nullptr, *l_orig = nullptr;
     bool has_l = false;
-    int64_t split_threshold = (int64_t)1 << 20;
-    int64_t split_chunk = (int64_t)1 << 16;
+    int64_t split_threshold = kSplitThreshold;
+    int64_t split_chunk = kSplitChunk;
     int panels_a = 0, panels_at = 0;    // column panels per side; 0 = choose
     int layout_a = LAYOUT_CHOOSE, layout_at = LAYOUT_CHOOSE;   // per side
+    int small = 1;                      // small LPs iterate in one workgroup
     int stream_nt = -1;                 // streamed-load kind; -1 = choose
     int sort_rows = -1, sort_cols = -1; // length sort of rows / columns; -1 = by skew
     int block_rows = kWG;               // row cap of multi-row blocks; 0 = tile
@@ -415,6 +419,10 @@ void free_csr(DevCsr &M) {
         dfree(k->part);
         delete k;
     }
+    if (DevSmall *k = M.small) {
+        dfree(k->base);
+        delete k;
+    }
     dfree(M.pan_src);
     dfree(M.pan_mask);
     dfree(M.q64);
@@ -629,6 +637,36 @@ void upload_panels(pdhg_ctx *c, DevCsr &M, const std::vector<int64_t> &rp,
     M.q32 = dmalloc<float>(T.rows);
 }
 
+// The one-workgroup layout: one allocation and one copy (values behind the
+// plan), since loading a small LP is mostly such calls.
+DevSmall *upload_small(const HostSmall &H) {
+    DevSmall *S = new DevSmall();
+    S->G = H.G;
+    S->K = H.K;
+    S->entries = (int64_t)H.src.size();
+    auto pad = [](size_t b) { return (b + 15) & ~(size_t)15; };
+    const size_t o_row = pad(H.off.size() * 4), o_src = o_row + pad(H.row.size() * 4),
+                 o_col = o_src + pad(H.src.size() * 4), plan = o_col + pad(H.col.size() * 2),
+                 o_v32 = plan + pad(H.src.size() * 8);
+    std::vector<char> h(plan);
+    auto put = [&](size_t at, const void *p, size_t n) {
+        if (n) std::memcpy(h.data() + at, p, n);
+    };
+    put(0, H.off.data(), H.off.size() * 4);
+    put(o_row, H.row.data(), H.row.size() * 4);
+    put(o_src, H.src.data(), H.src.size() * 4);
+    put(o_col, H.col.data(), H.col.size() * 2);
+    S->base = dmalloc<char>((int64_t)(o_v32 + pad(H.src.size() * 4)));
+    HIPC(hipMemcpy(S->base, h.data(), plan, hipMemcpyHostToDevice));
+    S->off = (int32_t *)S->base;
+    S->row = (int32_t *)(S->base + o_row);
+    S->src = (int32_t *)(S->base + o_src);
+    S->col = (uint16_t *)(S->base + o_col);
+    S->v64 = (double *)(S->base + plan);
+    S->v32 = (float *)(S->base + o_v32);
+    return S;
+}
+
 // Upload one CSR (int64 row pointers on the host) and build both bin sets;
 // with P > 1 also its panel twin, and its buckets (tiles of an unpanelled side
 // come from the thread that plans them meanwhile).
@@ -718,6 +756,8 @@ void apply_scaling(pdhg_ctx *c) {
     launch_permute(c->At.v64, c->A.v64, c->perm, c->nnz, c->stream);
     launch_to_f32(c->At.v32, c->At.v64, c->nnz, c->stream);
     for (DevCsr *M : {&c->A, &c->At}) {
+        if (M->small)
+            launch_gather_pad(M->small->v64, M->small->v32, M->v64, M->small->src, M->small->entries, c->stream);
         if (M->bkt)
             launch_gather_pad(M->bkt->v64, M->bkt->v32, M->v64, M->bkt->src, 4 * M->bkt->quads, c->stream);
         if (M->pan) {
@@ -933,6 +973,20 @@ hipEvent_t pool_event(pdhg_ctx *c) {
 }
 
 void enqueue_iterations(pdhg_ctx *c, int first_off, int count) {
+    if (!c->profile && (f32(c) ? c->small32 : c->small64)) {
+        const int mode = c->params.variant == 1 ? SMALL_HALPERN : SMALL_AVG;
+        // (bounded launches, however far apart the evaluations are)
+        for (int o = 0; o < count; o += kSmallSteps) {
+            const int k = std::min(kSmallSteps, count - o);
+            if (f32(c))
+                launch_small<float>(c->A, c->At, c->v32, c->act_has_l, mode, c->st,
+                                    first_off + o, k, nullptr, nullptr, c->stream);
+            else
+                launch_small<double>(c->A, c->At, c->v64, c->act_has_l, mode, c->st,
+                                     first_off + o, k, nullptr, nullptr, c->stream);
+        }
+        return;
+    }
     for (int off = first_off; off < first_off + count; ++off) {
         ProfRec r0{0, nullptr, nullptr}, r1{1, nullptr, nullptr};
         if (c->profile) {
@@ -1434,6 +1488,10 @@ int pdhg_set_tuning(pdhg_ctx *c, const char *key, int64_t value) {
         c->layout_at = (int)value;
         return PDHG_OK;
     }
+    if (std::strcmp(key, "small") == 0 && (value == 0 || value == 1)) {
+        c->small = (int)value;
+        return PDHG_OK;
+    }
     if (std::strcmp(key, "stream_nt") == 0 && value >= -1 && value <= 1) {
         c->stream_nt = (int)value;
         return PDHG_OK;
@@ -1514,6 +1572,23 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
     auto plan_at = plan(tat, n, R.at_rp, R.at_ci, fat);
     upload_csr(c, c->A, m, n, nnz, R.a_rp, R.a_ci, R.a_v, pa, R.a_cut, la, fa, std::move(plan_a));
     upload_csr(c, c->At, n, m, nnz, R.at_rp, R.at_ci, R.at_v, pat, R.at_cut, lat, fat, std::move(plan_at));
+    // a small LP iterates in one workgroup unless row blocks, a layout or panels
+    // were asked for
+    const bool plain = c->small != 0 && !fa && !fat && !c->panels_a && !c->panels_at &&
+                       c->split_threshold == kSplitThreshold && c->split_chunk == kSplitChunk &&
+                       c->block_rows == kWG && c->stream_nt < 0;
+    auto longest = [](const std::vector<int64_t> &rp) {
+        int64_t k = 0;
+        for (size_t i = 1; i < rp.size(); ++i) k = std::max(k, rp[i] - rp[i - 1]);
+        return k;
+    };
+    const int64_t longest_a = plain ? longest(R.a_rp) : 0, longest_at = plain ? longest(R.at_rp) : 0;
+    c->small64 = plain && small_fits<double>(m, n, nnz, longest_a, longest_at);
+    c->small32 = plain && small_fits<float>(m, n, nnz, longest_a, longest_at);
+    if (c->small64 || c->small32) {
+        c->A.small = upload_small(build_small(m, n, R.a_rp.data(), R.a_ci.data()));
+        c->At.small = upload_small(build_small(n, m, R.at_rp.data(), R.at_ci.data()));
+    }
     // one product buffer for the push passes of both sides
     int64_t prods = 0;
     for (DevCsr *M : {&c->A, &c->At})

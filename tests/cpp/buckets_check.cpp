@@ -181,6 +181,50 @@ int main() {
                         B.buckets.size(), B.splits.size(), (int)B.fragmented);
         }
     }
+    // the one-workgroup layout of small LPs, as its lanes walk it
+    for (Case c : {Case{1, 1, 1, 0}, Case{5, 3, 0, 0}, Case{3, 8192, 300, 0}, Case{500, 1000, 10, 0},
+                   Case{1024, 1025, 4, 0}, Case{1025, 700, 6, 1}, Case{4096, 8192, 12, 0},
+                   Case{8192, 4096, 5, 3}}) {
+        const Csr A = make(c.m, c.n, c.avg, c.kind, g);
+        const int64_t nnz = (int64_t)A.ci.size();
+        std::vector<double> x(c.n + 1), v(nnz), ref(c.m), y(c.m, NAN);
+        for (int64_t j = 0; j < c.n; ++j) x[j] = (double)(int64_t)(g() % 2001) - 1000;
+        for (auto &t : v) t = (double)(int64_t)(g() % 201) - 100;
+        for (int64_t i = 0; i < c.m; ++i)
+            for (int64_t p = A.rp[i]; p < A.rp[i + 1]; ++p) ref[i] += v[p] * x[A.ci[p]];
+        const HostSmall S = build_small(c.m, c.n, A.rp.data(), A.ci.data());
+        CHECK(S.off.size() == (size_t)S.K * kSmallWaves + 1 && S.row.size() == (size_t)S.K * kSmallThreads / S.G);
+        CHECK(S.src.size() == 128 * (size_t)S.off.back() && S.col.size() == S.src.size());
+        CHECK((S.G & (S.G - 1)) == 0 && (S.G == 1 || S.G * c.m <= kSmallThreads));
+        std::vector<char> seen(nnz, 0);
+        for (int k = 0; k < S.K; ++k)
+            for (int tid = 0; tid < kSmallThreads; tid += S.G) {
+                const int32_t r = S.row[((int64_t)k * kSmallThreads + tid) / S.G];
+                double t = 0;
+                for (int l = tid; l < tid + S.G; ++l) {
+                    const int sl = k * kSmallWaves + l / 64;
+                    for (int q = S.off[sl]; q < S.off[sl + 1]; ++q)
+                        for (int u = 0; u < 2; ++u) {
+                            const size_t e = ((size_t)q * 64 + l % 64) * 2 + u;
+                            CHECK(S.col[e] <= c.n && S.src[e] < nnz);
+                            if (S.src[e] >= 0) {
+                                CHECK(r >= 0 && !seen[S.src[e]] && A.ci[S.src[e]] == S.col[e]);
+                                seen[S.src[e]] = 1;
+                                t += v[S.src[e]] * x[S.col[e]];
+                            } else {
+                                CHECK(S.col[e] == c.n);
+                            }
+                        }
+                }
+                if (r >= 0) {
+                    CHECK(r < c.m && std::isnan(y[r]));
+                    y[r] = t;
+                }
+            }
+        CHECK(y == ref && std::count(seen.begin(), seen.end(), 1) == nnz);
+        std::printf("small m %ld n %ld nnz %ld kind %d lanes %d slots %d entries %zu\n",
+                    (long)c.m, (long)c.n, (long)nnz, c.kind, S.G, S.K, S.src.size());
+    }
     std::printf("done\n");
     return 0;
 }

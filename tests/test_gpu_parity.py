@@ -659,6 +659,28 @@ def test_residuals_of_the_better_candidate(Solver, oracle):
     assert kb["maxresid"] == want["maxresid"] and kb["candidate"] == want["candidate"]
 
 
+@pytest.mark.parametrize("m,n,k", [(1, 3, 1), (15, 40, 4), (512, 1024, 5), (1024, 1025, 6),
+                                   (1025, 2049, 3), (2048, 4096, 5)])
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_one_workgroup_iterations_match_row_blocks(Solver, m, n, k, variant, precision):
+    """LPs at the edges of the one-workgroup iteration (rows per lane, lanes
+    per row): the iterates of the row blocks within rounding, with lower
+    bounds, and the same bits however the iterations are cut into calls."""
+    lp = lpgen.planted_uniform(m=m, n=n, k=k, seed=m)
+    lb = np.random.default_rng(n).uniform(-0.5, 0.2, n)
+    out = []
+    for tuning, calls in ((None, [130]), (None, [1, 62, 5, 62]), ({"small": 0}, [130])):
+        with Solver.from_lp(lp, lb=lb, tuning=tuning) as s:
+            s.configure(eps_rel=1e-14, precision=precision, variant=variant)
+            for c in calls:
+                s.iterate(c)
+            out.append(s.get_iterate())
+    for a, b, r in zip(*out):
+        assert np.array_equal(a, b)
+        assert err(a, r) <= (1e-11 if precision == 0 else 1e-4)
+
+
 @pytest.mark.parametrize("m,n", [(1, 2), (2, 511), (512, 513), (513, 1025),
                                  (1025, 524_287), (524_289, 3)])
 @pytest.mark.parametrize("precision", [0, 1])
