@@ -464,7 +464,8 @@ int pdhg_unrolled_forward(pdhg_ctx *ctx, int K, int ckpt_every,
  * dL/dc (n), dL/db (m) and dL/dA.values (nnz, A's CSR order), with the
  * scaling factors held fixed.  Segments between checkpoints are recomputed
  * with the forward kernels, which are deterministic, so the result does not
- * depend on ckpt_every.  The projection's subgradient is 0 at a tie.
+ * depend on ckpt_every (a tape whose K + 1 iterates take at most 256 MiB, or
+ * what the tuning key "tape_bytes" says, keeps all of them instead).  The projection's subgradient is 0 at a tie.
  * The replay reads the context's current problem data, so a tape is valid
  * only until the next pdhg_load, pdhg_configure, pdhg_set_values or
  * pdhg_set_rhs_obj (with data) on its context: after any of them this call
@@ -586,6 +587,9 @@ int pdhg_spmv_noalloc(pdhg_ctx *ctx, int which, int scaled, int precision,
  *      (default) chooses from the sizes.  Sums stay deterministic but round
  *      differently; the keys below on blocks and splits are those of layout 0,
  *      which a panel count other than 0 also selects under -1;
+ *  "tape_bytes": pdhg_unrolled_forward keeps the iterates of every step when
+ *      they take at most this many bytes (256 MiB by default; at once, not
+ *      at the next load), and the checkpoints otherwise;
  *  "small": 1 (default) lets an LP of at most about 4,000 columns, 2,000 rows
  *      and 25,000 nonzeros iterate in one workgroup when none of the layout,
  *      panel, split, stream or block keys is set; 0 does not;

@@ -302,10 +302,10 @@ void spmv_f32(const DevCsr &M, const float *in, float *out, hipStream_t s);
 
 template <typename T>
 void launch_primal(const DevCsr &At, const Iter<T> &v, bool has_l,
-                   bool avg, const State *st, int off, hipStream_t s);
+                   const State *st, int off, hipStream_t s);
 template <typename T>
-void launch_dual(const DevCsr &A, const Iter<T> &v, bool avg,
-                 const State *st, int off, hipStream_t s);
+void launch_dual(const DevCsr &A, const Iter<T> &v, const State *st, int off,
+                 hipStream_t s);
 // Halpern iteration: primal writes x^ = T_x(z) into v.xbar and the combined
 // x; dual gathers v.xbar and combines y and A~x with the anchors (xl, yl,
 // ax0).
@@ -430,20 +430,37 @@ void launch_refine_update(double *xs, double *ys, const T *xh, const T *yh,
 void launch_norm_unscaled(const double *vs, const double *d, int64_t k,
                           double *partial, double *result, hipStream_t s);
 
-// Adjoint kernels (template over T = float/double).
+// Adjoint (template over T = float/double).  One plain step from (x0, y0) to
+// (v.x, v.y); A~x of the old and the new x in v.ax.
 template <typename T>
-void launch_adj_dual_bwd(const DevCsr &At, const T *gy, const T *gx_in,
-                         const T *x1, const T *ls, bool has_l, T *gx_out,
-                         T *gv, T *gc, double tau, double sigma,
-                         hipStream_t s);
+void launch_plain_step(const DevCsr &A, const DevCsr &At, const Iter<T> &v,
+                       const T *x0, const T *y0, bool has_l, const State *st,
+                       hipStream_t s);
+// Vectors of a reverse pass: gradients with respect to x, y, c~ and b~ so far,
+// gv of the current step, l~, and the 128-byte lines of each row (li) and
+// column (lj) that hold the last kAdjSteps<T> steps for dL/dA~.
 template <typename T>
-void launch_adj_primal_bwd(const DevCsr &A, const T *gv, const T *gy_in,
-                           T *gy_out, T *gb, double tau, double sigma,
-                           hipStream_t s);
+constexpr int kAdjSteps = 64 / (int)sizeof(T);
 template <typename T>
-void launch_adj_gA(const DevCsr &A, const int32_t *rowidx, const T *y0,
-                   const T *gy1, const T *gv, const T *x0, const T *x1,
-                   T *gA, double tau, double sigma, hipStream_t s);
+struct AdjVecs {
+    T *gx, *gy, *gv, *gc, *gb, *li, *lj;
+    const T *ls;
+};
+// The reverse of one step from (x0, y0) with result x1, into slot `slot`.
+template <typename T>
+void launch_adj_step(const DevCsr &A, const DevCsr &At, const AdjVecs<T> &v,
+                     const T *x0, const T *x1, const T *y0, bool has_l,
+                     int slot, double tau, double sigma, hipStream_t s);
+// Small LPs: the reverse of steps k1 - 1 .. k0 into slots slot0, slot0 - 1, ..
+// (X, Y: the iterates of every step, n and m apart).
+template <typename T>
+void launch_small_adj(const DevCsr &A, const DevCsr &At, const AdjVecs<T> &v,
+                      const T *X, const T *Y, bool has_l, int k0, int k1,
+                      int slot0, double tau, double sigma, hipStream_t s);
+// dL/dA~ += what the first cnt slots of the lines hold.
+template <typename T>
+void launch_adj_gA(const DevCsr &A, const int32_t *rowidx, const AdjVecs<T> &v,
+                   int cnt, T *gA, hipStream_t s);
 
 // Gather-rate probe: indices of n streamed pairs, chunk per workgroup, each
 // workgroup confined to its panel of a table of `table` entries; the probe

@@ -160,10 +160,11 @@ struct PanelEpi {
 
 // Fused primal step over a row j of A~^T:
 //   x_j <- max(l_j, x_j - tau (c_j - g_j)),  xbar_j <- xbar_j + (x_j - xbar_j)/t
+// (xin, the old x, may be x itself)
 template <typename T, bool HAS_L, bool AVG>
 struct PrimalEpi {
     T *x, *xbar;
-    const T *c, *l;
+    const T *xin, *c, *l;
     const State *st;
     int off;
     T tau;
@@ -177,7 +178,7 @@ struct PrimalEpi {
         T x, c, l, xb;
     };
     __device__ __forceinline__ Pre pre(int j) const {
-        return {x[j], c[j], HAS_L ? l[j] : (T)0, AVG ? xbar[j] : (T)0};
+        return {xin[j], c[j], HAS_L ? l[j] : (T)0, AVG ? xbar[j] : (T)0};
     }
     __device__ __forceinline__ void fin(int j, T g, const Pre &p) const {
         const T v = p.x - tau * (p.c - g);
@@ -190,10 +191,11 @@ struct PrimalEpi {
 
 // Fused extrapolated dual step over a row i of A~ (q = (A~ x_new)_i):
 //   y_i <- y_i + sigma (b_i - (2 q - (A~ x_old)_i)),  (A~ x)_i <- q,  ybar
+// (yin, the old y, may be y itself)
 template <typename T, bool AVG>
 struct DualEpi {
     T *y, *ybar, *ax;
-    const T *b;
+    const T *yin, *b;
     const State *st;
     int off;
     T sigma;
@@ -207,7 +209,7 @@ struct DualEpi {
         T y, b, a, yb;
     };
     __device__ __forceinline__ Pre pre(int i) const {
-        return {y[i], b[i], ax[i], AVG ? ybar[i] : (T)0};
+        return {yin[i], b[i], ax[i], AVG ? ybar[i] : (T)0};
     }
     __device__ __forceinline__ void fin(int i, T q, const Pre &p) const {
         const T yn = p.y + sigma * (p.b - ((q + q) - p.a));
@@ -325,39 +327,64 @@ struct DualEvalEpi {
     }
 };
 
+// The adjoint keeps, per row i and per column j, a line of 128 bytes with one
+// pair for each of the last kAdjSteps<T> steps k: (tau y_k, sigma gy_{k+1}) and
+// (gv_k, 2 x_{k+1} - x_k); dL/dA~ is updated from both lines once per line.
+template <typename T>
+constexpr int kAdjLine = 128 / (int)sizeof(T);
+template <typename T>
+__device__ __forceinline__ void adj_pair(T *lines, int r, int slot, T a, T b) {
+    using V2 = T __attribute__((ext_vector_type(2)));
+    *(V2 *)(lines + (int64_t)r * kAdjLine<T> + 2 * slot) = V2{a, b};
+}
+
 // Adjoint of the dual step, over a row j of A~^T (s = (A~^T gy_{k+1})_j):
 //   gxbar = -sigma s;  g = gx_{k+1} + 2 gxbar;  gv = 1[x_{k+1} > l] g
 //   gx_k = gv - gxbar;  gc -= tau gv
 template <typename T, bool HAS_L>
 struct AdjDualEpi {
-    const T *gx_in, *x1, *l;
-    T *gx_out, *gv, *gc;
+    const T *gx_in, *x1, *x0, *l;
+    T *gx_out, *gv, *gc, *lines;
+    int slot;
     T tau, sigma;
     __device__ __forceinline__ bool begin() { return true; }
-    __device__ __forceinline__ void operator()(int j, T s) const {
+    struct Pre {
+        T gx, x1, x0, l, gc;
+    };
+    __device__ __forceinline__ Pre pre(int j) const {
+        return {gx_in[j], x1[j], x0[j], HAS_L ? l[j] : (T)0, gc[j]};
+    }
+    __device__ __forceinline__ void fin(int j, T s, const Pre &p) const {
         const T gxbar = -sigma * s;
-        const T g = gx_in[j] + (gxbar + gxbar);
-        const T lj = HAS_L ? l[j] : (T)0;
-        const T v = x1[j] > lj ? g : (T)0;
+        const T g = p.gx + (gxbar + gxbar);
+        const T v = p.x1 > p.l ? g : (T)0;
         gv[j] = v;
         gx_out[j] = v - gxbar;
-        gc[j] = gc[j] - tau * v;
+        gc[j] = p.gc - tau * v;
+        adj_pair(lines, j, slot, v, (p.x1 + p.x1) - p.x0);
     }
+    __device__ __forceinline__ void operator()(int j, T s) const { fin(j, s, pre(j)); }
 };
 
 // Adjoint of the primal step, over a row i of A~ (s = (A~ gv)_i):
 //   gy_k = gy_{k+1} + tau s;  gb += sigma gy_{k+1}
 template <typename T>
 struct AdjPrimalEpi {
-    const T *gy_in;
-    T *gy_out, *gb;
+    const T *gy_in, *y0;
+    T *gy_out, *gb, *lines;
+    int slot;
     T tau, sigma;
     __device__ __forceinline__ bool begin() { return true; }
-    __device__ __forceinline__ void operator()(int i, T s) const {
-        const T g = gy_in[i];
-        gy_out[i] = g + tau * s;
-        gb[i] = gb[i] + sigma * g;
+    struct Pre {
+        T g, y0, gb;
+    };
+    __device__ __forceinline__ Pre pre(int i) const { return {gy_in[i], y0[i], gb[i]}; }
+    __device__ __forceinline__ void fin(int i, T s, const Pre &p) const {
+        gy_out[i] = p.g + tau * s;
+        gb[i] = p.gb + sigma * p.g;
+        adj_pair(lines, i, slot, tau * p.y0, sigma * p.g);
     }
+    __device__ __forceinline__ void operator()(int i, T s) const { fin(i, s, pre(i)); }
 };
 
 // ---------------------------------------------------------------- kernels
@@ -976,28 +1003,18 @@ static void rbT(const DevCsr &M, const T *in, Epi e, hipStream_t s) {
 }
 
 template <typename T>
-void launch_primal(const DevCsr &At, const Iter<T> &v, bool has_l, bool avg,
+void launch_primal(const DevCsr &At, const Iter<T> &v, bool has_l,
                    const State *st, int off, hipStream_t s) {
-    if (has_l) {
-        if (avg)
-            rbT<T>(At, v.y, PrimalEpi<T, true, true>{v.x, v.xbar, v.cs, v.ls, st, off}, s);
-        else
-            rbT<T>(At, v.y, PrimalEpi<T, true, false>{v.x, v.xbar, v.cs, v.ls, st, off}, s);
-    } else {
-        if (avg)
-            rbT<T>(At, v.y, PrimalEpi<T, false, true>{v.x, v.xbar, v.cs, v.ls, st, off}, s);
-        else
-            rbT<T>(At, v.y, PrimalEpi<T, false, false>{v.x, v.xbar, v.cs, v.ls, st, off}, s);
-    }
+    if (has_l)
+        rbT<T>(At, v.y, PrimalEpi<T, true, true>{v.x, v.xbar, v.x, v.cs, v.ls, st, off}, s);
+    else
+        rbT<T>(At, v.y, PrimalEpi<T, false, true>{v.x, v.xbar, v.x, v.cs, v.ls, st, off}, s);
 }
 
 template <typename T>
-void launch_dual(const DevCsr &A, const Iter<T> &v, bool avg, const State *st,
-                 int off, hipStream_t s) {
-    if (avg)
-        rbT<T>(A, v.x, DualEpi<T, true>{v.y, v.ybar, v.ax, v.bs, st, off}, s);
-    else
-        rbT<T>(A, v.x, DualEpi<T, false>{v.y, v.ybar, v.ax, v.bs, st, off}, s);
+void launch_dual(const DevCsr &A, const Iter<T> &v, const State *st, int off,
+                 hipStream_t s) {
+    rbT<T>(A, v.x, DualEpi<T, true>{v.y, v.ybar, v.ax, v.y, v.bs, st, off}, s);
 }
 
 template <typename T>
@@ -1230,6 +1247,117 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs<T> g) {
         }
 }
 
+// The reverse of steps [k0, k1), last first, in one workgroup: as k_small, with
+// gy and gv as the gathered vectors.  X and Y hold the iterates of all steps.
+template <typename T>
+struct SmallAdjArgs {
+    SmallSide<T> at, a;
+    AdjVecs<T> v;
+    const T *X, *Y, *ls;
+    int k0, k1, slot0;
+    T tau, sigma;
+};
+template <typename T, int KX, int KY, int NP>
+__global__ __launch_bounds__(kSmallThreads) void k_small_adj(SmallAdjArgs<T> g) {
+    constexpr int NT = kSmallThreads;
+    __shared__ T s_gv[KX * NT + 1];
+    __shared__ T s_gy[KY * NT + 1];
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = g.at.rows, m = g.a.rows;
+    T gx[KX], gc[KX], l[KX], x1[KX], gy[KY], gb[KY];
+    int jx[KX], iy[KY], ex[KX], fx[KX], ey[KY], fy[KY];
+#pragma unroll
+    for (int k = 0; k < KX; ++k) {
+        gx[k] = gc[k] = l[k] = x1[k] = (T)0;
+        jx[k] = -1;
+        ex[k] = fx[k] = 0;
+        if (k < g.at.K) {
+            ex[k] = g.at.off[k * kSmallWaves + w];
+            fx[k] = g.at.off[k * kSmallWaves + w + 1];
+            if (tid % g.at.G == 0) jx[k] = g.at.row[(k * NT + tid) / g.at.G];
+        }
+        const int j = jx[k];
+        if (j >= 0) {
+            gx[k] = g.v.gx[j];
+            gc[k] = g.v.gc[j];
+            if (g.ls) l[k] = g.ls[j];
+            x1[k] = g.X[(int64_t)g.k1 * n + j];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < KY; ++k) {
+        gy[k] = gb[k] = (T)0;
+        iy[k] = -1;
+        ey[k] = fy[k] = 0;
+        if (k < g.a.K) {
+            ey[k] = g.a.off[k * kSmallWaves + w];
+            fy[k] = g.a.off[k * kSmallWaves + w + 1];
+            if (tid % g.a.G == 0) iy[k] = g.a.row[(k * NT + tid) / g.a.G];
+        }
+        const int i = iy[k];
+        if (i >= 0) {
+            gy[k] = g.v.gy[i];
+            gb[k] = g.v.gb[i];
+            s_gy[i] = gy[k];
+        }
+    }
+    if (tid == 0) s_gv[n] = s_gy[m] = (T)0;    // what padding gathers
+    SmallPairs<T, NP> px[KX], py[KY];
+#pragma unroll
+    for (int k = 0; k < KX; ++k) px[k].load(g.at, ex[k], fx[k]);
+#pragma unroll
+    for (int k = 0; k < KY; ++k) py[k].load(g.a, ey[k], fy[k]);
+    __syncthreads();
+    for (int st = g.k1 - 1, slot = g.slot0; st >= g.k0; --st, --slot) {
+        T x0[KX], y0[KY];
+#pragma unroll
+        for (int k = 0; k < KX; ++k) x0[k] = jx[k] >= 0 ? g.X[(int64_t)st * n + jx[k]] : (T)0;
+#pragma unroll
+        for (int k = 0; k < KY; ++k) y0[k] = iy[k] >= 0 ? g.Y[(int64_t)st * m + iy[k]] : (T)0;
+#pragma unroll
+        for (int k = 0; k < KX; ++k) {
+            if (k >= g.at.K) break;
+            const T s = small_row(g.at, s_gy, px[k], ex[k], fx[k]);
+            if (jx[k] >= 0) {
+                const T gxbar = -g.sigma * s;
+                const T q = gx[k] + (gxbar + gxbar);
+                const T v = x1[k] > l[k] ? q : (T)0;
+                s_gv[jx[k]] = v;
+                gx[k] = v - gxbar;
+                gc[k] = gc[k] - g.tau * v;
+                adj_pair(g.v.lj, jx[k], slot, v, (x1[k] + x1[k]) - x0[k]);
+                x1[k] = x0[k];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < KY; ++k) {
+            if (k >= g.a.K) break;
+            const T s = small_row(g.a, s_gv, py[k], ey[k], fy[k]);
+            if (iy[k] >= 0) {
+                gb[k] = gb[k] + g.sigma * gy[k];
+                adj_pair(g.v.li, iy[k], slot, g.tau * y0[k], g.sigma * gy[k]);
+                gy[k] = gy[k] + g.tau * s;
+                s_gy[iy[k]] = gy[k];
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < KX; ++k)
+        if (jx[k] >= 0) {
+            g.v.gx[jx[k]] = gx[k];
+            g.v.gc[jx[k]] = gc[k];
+        }
+#pragma unroll
+    for (int k = 0; k < KY; ++k)
+        if (iy[k] >= 0) {
+            g.v.gy[iy[k]] = gy[k];
+            g.v.gb[iy[k]] = gb[k];
+        }
+}
+
 template <typename T>
 SmallSide<T> small_side(const DevCsr &M) {
     const DevSmall &S = *M.small;
@@ -1239,6 +1367,20 @@ SmallSide<T> small_side(const DevCsr &M) {
     else
         v = S.v32;
     return {S.off, S.row, S.col, v, S.G, S.K, (int)M.rows};
+}
+
+// fn(columns per lane, rows per lane, resident pairs per slice) as constants:
+// as many pairs as the registers of a lane (128) hold beside its rows.
+template <typename T, class Fn>
+void small_sized(int kx, int ky, Fn fn) {
+    using std::integral_constant;
+    constexpr bool d = sizeof(T) == 8;
+    if (kx <= 1 && ky <= 1)
+        fn(integral_constant<int, 1>(), integral_constant<int, 1>(), integral_constant<int, d ? 4 : 6>());
+    else if (kx <= 2 && ky <= 1)
+        fn(integral_constant<int, 2>(), integral_constant<int, 1>(), integral_constant<int, d ? 2 : 4>());
+    else
+        fn(integral_constant<int, 4>(), integral_constant<int, 2>(), integral_constant<int, d ? 1 : 2>());
 }
 
 }  // namespace
@@ -1262,16 +1404,30 @@ void launch_small(const DevCsr &A, const DevCsr &At, const Iter<T> &v,
         else
             run(k_small<T, SMALL_PLAIN, KX, KY, NP>);
     };
-    // as many pairs as the registers of a lane (128) hold beside its rows
-    using std::integral_constant;
-    constexpr bool d = sizeof(T) == 8;
-    if (g.at.K <= 1 && g.a.K <= 1)
-        sized(integral_constant<int, 1>(), integral_constant<int, 1>(), integral_constant<int, d ? 4 : 6>());
-    else if (g.at.K <= 2 && g.a.K <= 1)
-        sized(integral_constant<int, 2>(), integral_constant<int, 1>(), integral_constant<int, d ? 2 : 4>());
-    else
-        sized(integral_constant<int, 4>(), integral_constant<int, 2>(), integral_constant<int, d ? 1 : 2>());
+    small_sized<T>(g.at.K, g.a.K, sized);
 }
+
+template <typename T>
+void launch_small_adj(const DevCsr &A, const DevCsr &At, const AdjVecs<T> &v,
+                      const T *X, const T *Y, bool has_l, int k0, int k1,
+                      int slot0, double tau, double sigma, hipStream_t s) {
+    const SmallAdjArgs<T> g{small_side<T>(At), small_side<T>(A), v, X, Y,
+                            has_l ? v.ls : nullptr, k0, k1, slot0, (T)tau, (T)sigma};
+    small_sized<T>(g.at.K, g.a.K, [&](auto kx, auto ky, auto np) {
+        constexpr int KX = decltype(kx)::value, KY = decltype(ky)::value,
+                      NP = decltype(np)::value;
+        hipLaunchKernelGGL((k_small_adj<T, KX, KY, NP>), dim3(1),
+                           dim3(kSmallThreads), 0, s, g);
+    });
+}
+template void launch_small_adj<double>(const DevCsr &, const DevCsr &,
+                                       const AdjVecs<double> &, const double *,
+                                       const double *, bool, int, int, int,
+                                       double, double, hipStream_t);
+template void launch_small_adj<float>(const DevCsr &, const DevCsr &,
+                                      const AdjVecs<float> &, const float *,
+                                      const float *, bool, int, int, int,
+                                      double, double, hipStream_t);
 template void launch_small<double>(const DevCsr &, const DevCsr &,
                                    const Iter<double> &, bool, int,
                                    const State *, int, int, double *, double *,
@@ -1296,70 +1452,99 @@ INST_HALPERN(float)
 #undef INST_HALPERN
 
 template void launch_primal<double>(const DevCsr &, const Iter<double> &, bool,
-                                    bool, const State *, int, hipStream_t);
+                                   const State *, int, hipStream_t);
 template void launch_primal<float>(const DevCsr &, const Iter<float> &, bool,
-                                   bool, const State *, int, hipStream_t);
-template void launch_dual<double>(const DevCsr &, const Iter<double> &, bool,
-                                  const State *, int, hipStream_t);
-template void launch_dual<float>(const DevCsr &, const Iter<float> &, bool,
+                                   const State *, int, hipStream_t);
+template void launch_dual<double>(const DevCsr &, const Iter<double> &,
+                                 const State *, int, hipStream_t);
+template void launch_dual<float>(const DevCsr &, const Iter<float> &,
                                  const State *, int, hipStream_t);
 
 // ============================================================ adjoint
 
+// One plain step from (x0, y0) to (v.x, v.y), A~x in v.ax.
 template <typename T>
-void launch_adj_dual_bwd(const DevCsr &At, const T *gy, const T *gx_in,
-                         const T *x1, const T *ls, bool has_l, T *gx_out,
-                         T *gv, T *gc, double tau, double sigma,
-                         hipStream_t s) {
+void launch_plain_step(const DevCsr &A, const DevCsr &At, const Iter<T> &v,
+                       const T *x0, const T *y0, bool has_l, const State *st,
+                       hipStream_t s) {
     if (has_l)
-        rbT<T>(At, gy, AdjDualEpi<T, true>{gx_in, x1, ls, gx_out, gv, gc, (T)tau, (T)sigma}, s);
+        rbT<T>(At, y0, PrimalEpi<T, true, false>{v.x, nullptr, x0, v.cs, v.ls, st, 0}, s);
     else
-        rbT<T>(At, gy, AdjDualEpi<T, false>{gx_in, x1, ls, gx_out, gv, gc, (T)tau, (T)sigma}, s);
+        rbT<T>(At, y0, PrimalEpi<T, false, false>{v.x, nullptr, x0, v.cs, v.ls, st, 0}, s);
+    rbT<T>(A, (const T *)v.x, DualEpi<T, false>{v.y, nullptr, v.ax, y0, v.bs, st, 0}, s);
 }
 
+// The reverse of one step k (slot: its place in the lines).
 template <typename T>
-void launch_adj_primal_bwd(const DevCsr &A, const T *gv, const T *gy_in,
-                           T *gy_out, T *gb, double tau, double sigma,
-                           hipStream_t s) {
-    rbT<T>(A, gv, AdjPrimalEpi<T>{gy_in, gy_out, gb, (T)tau, (T)sigma}, s);
+void launch_adj_step(const DevCsr &A, const DevCsr &At, const AdjVecs<T> &v,
+                     const T *x0, const T *x1, const T *y0, bool has_l,
+                     int slot, double tau, double sigma, hipStream_t s) {
+    if (has_l)
+        rbT<T>(At, (const T *)v.gy,
+               AdjDualEpi<T, true>{v.gx, x1, x0, v.ls, v.gx, v.gv, v.gc, v.lj, slot, (T)tau, (T)sigma}, s);
+    else
+        rbT<T>(At, (const T *)v.gy,
+               AdjDualEpi<T, false>{v.gx, x1, x0, v.ls, v.gx, v.gv, v.gc, v.lj, slot, (T)tau, (T)sigma}, s);
+    rbT<T>(A, (const T *)v.gv,
+           AdjPrimalEpi<T>{v.gy, y0, v.gy, v.gb, v.li, slot, (T)tau, (T)sigma}, s);
 }
 
-// dA~_p += tau y_k,i gv_j - sigma gy_{k+1},i (2 x_{k+1},j - x_k,j), p = (i, j)
+// dA~_p += sum over the slots below cnt of tau y_k,i gv_j - sigma gy_{k+1},i
+// (2 x_{k+1},j - x_k,j), p = (i, j).  Eight lanes read the two lines of a
+// nonzero, 16 bytes each, so a random access brings a line that is used whole.
+// (One update per step, with five 8-byte gathers a nonzero, took 15 us a step
+// at 800k nonzeros.)
 template <typename T>
 __global__ __launch_bounds__(kWG) void k_adj_gA(
     const int32_t *__restrict__ rowidx, const int32_t *__restrict__ ci,
-    int64_t nnz, const T *__restrict__ y0, const T *__restrict__ gy1,
-    const T *__restrict__ gv, const T *__restrict__ x0,
-    const T *__restrict__ x1, T *__restrict__ gA, T tau, T sigma) {
-    for (int64_t p = blockIdx.x * (int64_t)kWG + threadIdx.x; p < nnz;
-         p += (int64_t)gridDim.x * kWG) {
-        const int i = rowidx[p], j = ci[p];
-        const T xb = (x1[j] + x1[j]) - x0[j];
-        gA[p] = gA[p] + (tau * y0[i] * gv[j] - sigma * gy1[i] * xb);
+    int64_t nnz, const T *__restrict__ li, const T *__restrict__ lj, int cnt,
+    T *__restrict__ gA) {
+    using Un = UnitOf<T>;
+    constexpr int U = 4, W = Un::W;
+    const int sub = threadIdx.x & 7;
+    const int64_t step = (int64_t)gridDim.x * (kWG / 8);
+    for (int64_t p0 = (int64_t)blockIdx.x * (kWG / 8) + (threadIdx.x >> 3);
+         p0 < nnz; p0 += U * step) {
+        typename Un::V a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int64_t p = p0 + u * step;
+            if (p >= nnz) p = p0;
+            a[u] = *((const typename Un::V *)(li + (int64_t)rowidx[p] * kAdjLine<T>) + sub);
+            b[u] = *((const typename Un::V *)(lj + (int64_t)ci[p] * kAdjLine<T>) + sub);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            T d = (T)0;
+#pragma unroll
+            for (int i = 0; i < W; i += 2)
+                if (W / 2 * sub + i / 2 < cnt) d += a[u][i] * b[u][i] - a[u][i + 1] * b[u][i + 1];
+            for (int o = 4; o > 0; o >>= 1) d += __shfl_xor(d, o);
+            const int64_t p = p0 + u * step;
+            if (sub == 0 && p < nnz) gA[p] += d;
+        }
     }
 }
 
 template <typename T>
-void launch_adj_gA(const DevCsr &A, const int32_t *rowidx, const T *y0,
-                   const T *gy1, const T *gv, const T *x0, const T *x1, T *gA,
-                   double tau, double sigma, hipStream_t s) {
-    hipLaunchKernelGGL(k_adj_gA<T>, dim3(grid_for(A.nnz, kWG, 16384)),
-                       dim3(kWG), 0, s, rowidx, A.ci, A.nnz, y0, gy1, gv, x0,
-                       x1, gA, (T)tau, (T)sigma);
+void launch_adj_gA(const DevCsr &A, const int32_t *rowidx, const AdjVecs<T> &v,
+                   int cnt, T *gA, hipStream_t s) {
+    hipLaunchKernelGGL(k_adj_gA<T>, dim3(grid_for(A.nnz, 32 * 4, 16384)),
+                       dim3(kWG), 0, s, rowidx, A.ci, A.nnz, (const T *)v.li,
+                       (const T *)v.lj, cnt, gA);
 }
 
 #define INST_ADJ(T)                                                          \
-    template void launch_adj_dual_bwd<T>(const DevCsr &, const T *,         \
-                                         const T *, const T *, const T *,   \
-                                         bool, T *, T *, T *, double,       \
-                                         double, hipStream_t);              \
-    template void launch_adj_primal_bwd<T>(const DevCsr &, const T *,       \
-                                           const T *, T *, T *, double,     \
-                                           double, hipStream_t);            \
+    template void launch_plain_step<T>(const DevCsr &, const DevCsr &,      \
+                                       const Iter<T> &, const T *,          \
+                                       const T *, bool, const State *,      \
+                                       hipStream_t);                        \
+    template void launch_adj_step<T>(const DevCsr &, const DevCsr &,        \
+                                     const AdjVecs<T> &, const T *,         \
+                                     const T *, const T *, bool, int,       \
+                                     double, double, hipStream_t);          \
     template void launch_adj_gA<T>(const DevCsr &, const int32_t *,         \
-                                   const T *, const T *, const T *,         \
-                                   const T *, const T *, T *, double,       \
-                                   double, hipStream_t);
+                                   const AdjVecs<T> &, int, T *, hipStream_t);
 INST_ADJ(double)
 INST_ADJ(float)
 #undef INST_ADJ

@@ -153,6 +153,7 @@ struct pdhg_ctx {
     int panels_a = 0, panels_at = 0;    // column panels per side; 0 = choose
     int layout_a = LAYOUT_CHOOSE, layout_at = LAYOUT_CHOOSE;   // per side
     int small = 1;                      // small LPs iterate in one workgroup
+    int64_t tape_bytes = (int64_t)256 << 20;    // tapes up to this keep every step
     int stream_nt = -1;                 // streamed-load kind; -1 = choose
     int sort_rows = -1, sort_cols = -1; // length sort of rows / columns; -1 = by skew
     int block_rows = kWG;               // row cap of multi-row blocks; 0 = tile
@@ -259,6 +260,7 @@ struct pdhg_tape {
     pdhg_ctx *ctx = nullptr;
     uint64_t data_gen = 0;      // the context's data_gen at the forward pass
     int K = 0, ck = 0, prec = PDHG_FP64, nseg = 0;
+    bool full = false;          // the checkpoints are the iterates of all steps
     double tau = 0, sigma = 0;
     void *ckx = nullptr, *cky = nullptr, *ckax = nullptr;
     State *st = nullptr;
@@ -1000,9 +1002,9 @@ void enqueue_iterations(pdhg_ctx *c, int first_off, int count) {
         else if (halpern)
             launch_primal_halpern<double>(c->At, c->v64, c->act_has_l, c->st, off, c->stream);
         else if (f32(c))
-            launch_primal<float>(c->At, c->v32, c->act_has_l, true, c->st, off, c->stream);
+            launch_primal<float>(c->At, c->v32, c->act_has_l, c->st, off, c->stream);
         else
-            launch_primal<double>(c->At, c->v64, c->act_has_l, true, c->st, off, c->stream);
+            launch_primal<double>(c->At, c->v64, c->act_has_l, c->st, off, c->stream);
         if (c->profile) {
             HIPC(hipEventRecord(r0.b, c->stream));
             r1.a = pool_event(c);
@@ -1014,9 +1016,9 @@ void enqueue_iterations(pdhg_ctx *c, int first_off, int count) {
         else if (halpern)
             launch_dual_halpern<double>(c->A, c->v64, c->st, off, c->stream);
         else if (f32(c))
-            launch_dual<float>(c->A, c->v32, true, c->st, off, c->stream);
+            launch_dual<float>(c->A, c->v32, c->st, off, c->stream);
         else
-            launch_dual<double>(c->A, c->v64, true, c->st, off, c->stream);
+            launch_dual<double>(c->A, c->v64, c->st, off, c->stream);
         if (c->profile) {
             HIPC(hipEventRecord(r1.b, c->stream));
             c->prof.push_back(r0);
@@ -1486,6 +1488,10 @@ int pdhg_set_tuning(pdhg_ctx *c, const char *key, int64_t value) {
     }
     if (std::strcmp(key, "layout_at") == 0 && lv) {
         c->layout_at = (int)value;
+        return PDHG_OK;
+    }
+    if (std::strcmp(key, "tape_bytes") == 0 && value >= 0) {
+        c->tape_bytes = value;
         return PDHG_OK;
     }
     if (std::strcmp(key, "small") == 0 && (value == 0 || value == 1)) {
@@ -2778,21 +2784,65 @@ int pdhg_refine_log(pdhg_ctx *c, double *out, int cap, int *count) {
 namespace {
 
 template <typename T>
-void unrolled_forward_T(pdhg_ctx *c, pdhg_tape *tp, const double *x0,
-                        const double *y0, double *xK, int mem) {
-    const int64_t m = c->m, n = c->n;
-    const int nck = tp->nseg;
-    tp->ckx = dmalloc<T>((int64_t)nck * n);
-    tp->cky = dmalloc<T>((int64_t)nck * m);
-    tp->ckax = dmalloc<T>((int64_t)nck * m);
+Iter<T> plain_data(pdhg_ctx *c) {
     Iter<T> w;
-    w.x = dmalloc<T>(n);
-    w.y = dmalloc<T>(m);
-    w.ax = dmalloc<T>(m);
     if constexpr (sizeof(T) == 8) {
         w.bs = c->bs; w.cs = c->cs; w.ls = c->ls;
     } else {
         w.bs = c->bs32; w.cs = c->cs32; w.ls = c->ls32;
+    }
+    return w;
+}
+
+// `count` plain steps from X[0], Y[0] on, step t writing X[t + 1], Y[t + 1]
+// (n and m apart); ax: A~x of the first x, then of the last.
+template <typename T>
+void plain_steps(pdhg_ctx *c, Iter<T> w, T *X, T *Y, T *ax, int count, const State *st) {
+    const int64_t m = c->m, n = c->n;
+    w.ax = ax;
+    if (sizeof(T) == 8 ? c->small64 : c->small32) {
+        // (the kernel's final iterate goes where its last step went)
+        for (int t = 0; t < count; t += kSmallSteps) {
+            const int k = std::min(kSmallSteps, count - t);
+            HIPC(hipMemcpyAsync(X + (int64_t)(t + k) * n, X + (int64_t)t * n, n * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
+            HIPC(hipMemcpyAsync(Y + (int64_t)(t + k) * m, Y + (int64_t)t * m, m * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
+            w.x = X + (int64_t)(t + k) * n;
+            w.y = Y + (int64_t)(t + k) * m;
+            launch_small<T>(c->A, c->At, w, c->has_l, SMALL_PLAIN, st, 0, k,
+                            X + (int64_t)(t + 1) * n, Y + (int64_t)(t + 1) * m, c->stream);
+        }
+        return;
+    }
+    for (int t = 0; t < count; ++t) {
+        w.x = X + (int64_t)(t + 1) * n;
+        w.y = Y + (int64_t)(t + 1) * m;
+        launch_plain_step<T>(c->A, c->At, w, X + (int64_t)t * n, Y + (int64_t)t * m,
+                             c->has_l, st, c->stream);
+    }
+}
+
+template <typename T>
+void unrolled_forward_T(pdhg_ctx *c, pdhg_tape *tp, const double *x0,
+                        const double *y0, double *xK, int mem) {
+    const int64_t m = c->m, n = c->n;
+    // a tape of few bytes keeps the iterates of every step, so that its reverse
+    // pass recomputes nothing
+    tp->full = ((int64_t)tp->K + 1) <= c->tape_bytes / ((m + n) * (int64_t)sizeof(T));
+    // iterates of a checkpoint segment at a time, the last of them its result
+    const int seg = tp->full ? tp->K : 1, nck = tp->full ? tp->K + 1 : tp->nseg;
+    tp->ckx = dmalloc<T>((int64_t)nck * n);
+    tp->cky = dmalloc<T>((int64_t)nck * m);
+    if (!tp->full) tp->ckax = dmalloc<T>((int64_t)nck * m);
+    Iter<T> w = plain_data<T>(c);
+    T *X = (T *)tp->ckx, *Y = (T *)tp->cky;
+    struct Work {
+        T *x = nullptr, *y = nullptr, *ax = nullptr;
+        ~Work() { dfree(x); dfree(y); dfree(ax); }
+    } k;
+    k.ax = dmalloc<T>(m);
+    if (!tp->full) {
+        X = k.x = dmalloc<T>((seg + 1) * n);
+        Y = k.y = dmalloc<T>((seg + 1) * m);
     }
     // scaled start
     if (x0) {
@@ -2808,36 +2858,57 @@ void unrolled_forward_T(pdhg_ctx *c, pdhg_tape *tp, const double *x0,
         launch_fill(c->yo, 0.0, m, c->stream);
     }
     if constexpr (sizeof(T) == 8) {
-        HIPC(hipMemcpyAsync(w.x, c->xo, n * 8, hipMemcpyDeviceToDevice, c->stream));
-        HIPC(hipMemcpyAsync(w.y, c->yo, m * 8, hipMemcpyDeviceToDevice, c->stream));
-        spmv_f64(c->A, c->A.v64, w.x, w.ax, c->stream);
+        HIPC(hipMemcpyAsync(X, c->xo, n * 8, hipMemcpyDeviceToDevice, c->stream));
+        HIPC(hipMemcpyAsync(Y, c->yo, m * 8, hipMemcpyDeviceToDevice, c->stream));
+        spmv_f64(c->A, c->A.v64, X, k.ax, c->stream);
     } else {
-        launch_to_f32(w.x, c->xo, n, c->stream);
-        launch_to_f32(w.y, c->yo, m, c->stream);
-        spmv_f32(c->A, w.x, w.ax, c->stream);
+        launch_to_f32(X, c->xo, n, c->stream);
+        launch_to_f32(Y, c->yo, m, c->stream);
+        spmv_f32(c->A, X, k.ax, c->stream);
     }
-    for (int k = 0; k < tp->K; ++k) {
-        if (k % tp->ck == 0) {
-            const int s = k / tp->ck;
-            HIPC(hipMemcpyAsync((T *)tp->ckx + (int64_t)s * n, w.x, n * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
-            HIPC(hipMemcpyAsync((T *)tp->cky + (int64_t)s * m, w.y, m * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
-            HIPC(hipMemcpyAsync((T *)tp->ckax + (int64_t)s * m, w.ax, m * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
+    if (tp->full) {
+        plain_steps<T>(c, w, X, Y, k.ax, tp->K, tp->st);
+        X += (int64_t)tp->K * n;
+    } else {
+        // two iterates that take turns (one, where a workgroup runs several
+        // steps), copied out at the checkpoints
+        const bool small = sizeof(T) == 8 ? c->small64 : c->small32;
+        int cur = 0;
+        w.ax = k.ax;
+        for (int t = 0; t < tp->K;) {
+            T *xc = X + cur * n, *yc = Y + cur * m;
+            if (t % tp->ck == 0) {
+                const int s = t / tp->ck;
+                HIPC(hipMemcpyAsync((T *)tp->ckx + (int64_t)s * n, xc, n * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
+                HIPC(hipMemcpyAsync((T *)tp->cky + (int64_t)s * m, yc, m * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
+                HIPC(hipMemcpyAsync((T *)tp->ckax + (int64_t)s * m, k.ax, m * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
+            }
+            if (small) {
+                const int count = std::min(std::min(tp->ck - t % tp->ck, tp->K - t), kSmallSteps);
+                w.x = xc;
+                w.y = yc;
+                launch_small<T>(c->A, c->At, w, c->has_l, SMALL_PLAIN, tp->st, 0, count,
+                                nullptr, nullptr, c->stream);
+                t += count;
+                continue;
+            }
+            cur ^= 1;
+            w.x = X + cur * n;
+            w.y = Y + cur * m;
+            launch_plain_step<T>(c->A, c->At, w, xc, yc, c->has_l, tp->st, c->stream);
+            ++t;
         }
-        launch_primal<T>(c->At, w, c->has_l, false, tp->st, 0, c->stream);
-        launch_dual<T>(c->A, w, false, tp->st, 0, c->stream);
+        X += cur * n;
     }
     // x_K unscaled
     double *xd = c->xo;
     if constexpr (sizeof(T) == 8)
-        HIPC(hipMemcpyAsync(xd, w.x, n * 8, hipMemcpyDeviceToDevice, c->stream));
+        HIPC(hipMemcpyAsync(xd, X, n * 8, hipMemcpyDeviceToDevice, c->stream));
     else
-        launch_to_f64(xd, w.x, n, c->stream);
+        launch_to_f64(xd, X, n, c->stream);
     launch_ew(xd, xd, c->dc, n, 0, c->stream);
     vec_out(c, xK, xd, false, mem);
     sync(c);
-    dfree(w.x);
-    dfree(w.y);
-    dfree(w.ax);
 }
 
 template <typename T>
@@ -2845,14 +2916,23 @@ void unrolled_backward_T(pdhg_tape *tp, const double *gxK, double *gc,
                          double *gb, double *gA, int mem) {
     pdhg_ctx *c = tp->ctx;
     const int64_t m = c->m, n = c->n, nnz = c->nnz;
-    const int ck = tp->ck;
-    T *X = dmalloc<T>((int64_t)(ck + 1) * n);
-    T *Y = dmalloc<T>((int64_t)(ck + 1) * m);
-    T *axw = dmalloc<T>(m);
-    T *gx = dmalloc<T>(n), *gx2 = dmalloc<T>(n), *gv = dmalloc<T>(n);
-    T *gy = dmalloc<T>(m), *gy2 = dmalloc<T>(m);
-    T *gcs = dmalloc<T>(n), *gbs = dmalloc<T>(m), *gAs = dmalloc<T>(nnz);
-    HIPC(hipMemsetAsync(gy, 0, m * sizeof(T), c->stream));
+    const int ck = tp->full ? tp->K : tp->ck, nseg = tp->full ? 1 : tp->nseg;
+    const bool small = sizeof(T) == 8 ? c->small64 : c->small32;
+    constexpr int S = kAdjSteps<T>;
+    T *X = (T *)tp->ckx, *Y = (T *)tp->cky, *axw = nullptr;
+    if (!tp->full) {
+        X = dmalloc<T>((int64_t)(ck + 1) * n);
+        Y = dmalloc<T>((int64_t)(ck + 1) * m);
+        axw = dmalloc<T>(m);
+    }
+    AdjVecs<T> v;
+    v.gx = dmalloc<T>(n);
+    v.gv = dmalloc<T>(n);
+    v.gy = dmalloc<T>(m);
+    v.li = dmalloc<T>(m * 2 * S);
+    v.lj = dmalloc<T>(n * 2 * S);
+    T *gcs = v.gc = dmalloc<T>(n), *gbs = v.gb = dmalloc<T>(m), *gAs = dmalloc<T>(nnz);
+    HIPC(hipMemsetAsync(v.gy, 0, m * sizeof(T), c->stream));
     HIPC(hipMemsetAsync(gcs, 0, n * sizeof(T), c->stream));
     HIPC(hipMemsetAsync(gbs, 0, m * sizeof(T), c->stream));
     HIPC(hipMemsetAsync(gAs, 0, nnz * sizeof(T), c->stream));
@@ -2860,46 +2940,36 @@ void unrolled_backward_T(pdhg_tape *tp, const double *gxK, double *gc,
     vec_in(c, c->xo, gxK, false, mem);
     launch_ew(c->xo, c->xo, c->dc, n, 0, c->stream);
     if constexpr (sizeof(T) == 8)
-        HIPC(hipMemcpyAsync(gx, c->xo, n * 8, hipMemcpyDeviceToDevice, c->stream));
+        HIPC(hipMemcpyAsync(v.gx, c->xo, n * 8, hipMemcpyDeviceToDevice, c->stream));
     else
-        launch_to_f32(gx, c->xo, n, c->stream);
-    const T *ls = nullptr;
-    if constexpr (sizeof(T) == 8) ls = c->ls; else ls = c->ls32;
-    Iter<T> w;
-    if constexpr (sizeof(T) == 8) {
-        w.bs = c->bs; w.cs = c->cs; w.ls = c->ls;
-    } else {
-        w.bs = c->bs32; w.cs = c->cs32; w.ls = c->ls32;
-    }
-    w.ax = axw;
-    for (int seg = tp->nseg - 1; seg >= 0; --seg) {
+        launch_to_f32(v.gx, c->xo, n, c->stream);
+    const Iter<T> w = plain_data<T>(c);
+    v.ls = w.ls;
+    for (int seg = nseg - 1; seg >= 0; --seg) {
         const int s0 = seg * ck, s1 = std::min(tp->K, s0 + ck);
-        HIPC(hipMemcpyAsync(X, (T *)tp->ckx + (int64_t)seg * n, n * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
-        HIPC(hipMemcpyAsync(Y, (T *)tp->cky + (int64_t)seg * m, m * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
-        HIPC(hipMemcpyAsync(axw, (T *)tp->ckax + (int64_t)seg * m, m * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
-        for (int t = 0; t < s1 - s0; ++t) {
-            T *xt = X + (int64_t)t * n, *xt1 = X + (int64_t)(t + 1) * n;
-            T *yt = Y + (int64_t)t * m, *yt1 = Y + (int64_t)(t + 1) * m;
-            HIPC(hipMemcpyAsync(xt1, xt, n * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
-            w.x = xt1;
-            w.y = yt;
-            launch_primal<T>(c->At, w, c->has_l, false, tp->st, 0, c->stream);
-            HIPC(hipMemcpyAsync(yt1, yt, m * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
-            w.y = yt1;
-            launch_dual<T>(c->A, w, false, tp->st, 0, c->stream);
+        if (!tp->full) {
+            HIPC(hipMemcpyAsync(X, (T *)tp->ckx + (int64_t)seg * n, n * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
+            HIPC(hipMemcpyAsync(Y, (T *)tp->cky + (int64_t)seg * m, m * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
+            HIPC(hipMemcpyAsync(axw, (T *)tp->ckax + (int64_t)seg * m, m * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
+            plain_steps<T>(c, w, X, Y, axw, s1 - s0, tp->st);
         }
-        for (int k = s1 - 1; k >= s0; --k) {
-            const int t = k - s0;
-            const T *xk = X + (int64_t)t * n, *xk1 = X + (int64_t)(t + 1) * n;
-            const T *yk = Y + (int64_t)t * m;
-            launch_adj_dual_bwd<T>(c->At, gy, gx, xk1, ls, c->has_l, gx2, gv,
-                                   gcs, tp->tau, tp->sigma, c->stream);
-            launch_adj_gA<T>(c->A, c->rowidx, yk, gy, gv, xk, xk1, gAs,
-                             tp->tau, tp->sigma, c->stream);
-            launch_adj_primal_bwd<T>(c->A, gv, gy, gy2, gbs, tp->tau,
-                                     tp->sigma, c->stream);
-            std::swap(gx, gx2);
-            std::swap(gy, gy2);
+        // step k sits in slot k % S, and dL/dA~ is updated when slot 0 is
+        // written: sums do not depend on where segments end
+        for (int k1 = s1; k1 > s0;) {
+            const int k0 = std::max(s0, (k1 - 1) / S * S);
+            if (small) {
+                launch_small_adj<T>(c->A, c->At, v, X, Y, c->has_l, k0 - s0, k1 - s0,
+                                    (k1 - 1) % S, tp->tau, tp->sigma, c->stream);
+            } else {
+                for (int k = k1 - 1; k >= k0; --k) {
+                    const int64_t t = k - s0;
+                    launch_adj_step<T>(c->A, c->At, v, X + t * n, X + (t + 1) * n, Y + t * m,
+                                       c->has_l, k % S, tp->tau, tp->sigma, c->stream);
+                }
+            }
+            if (k0 % S == 0)
+                launch_adj_gA<T>(c->A, c->rowidx, v, std::min(tp->K - k0, S), gAs, c->stream);
+            k1 = k0;
         }
     }
     // unscale: dL/dc = D_c dL/dc~, dL/db = D_r dL/db~,
@@ -2927,14 +2997,16 @@ void unrolled_backward_T(pdhg_tape *tp, const double *gxK, double *gc,
     sync(c);
     dfree(g64);
     dfree(out);
-    dfree(X);
-    dfree(Y);
-    dfree(axw);
-    dfree(gx);
-    dfree(gx2);
-    dfree(gv);
-    dfree(gy);
-    dfree(gy2);
+    if (!tp->full) {
+        dfree(X);
+        dfree(Y);
+        dfree(axw);
+    }
+    dfree(v.gx);
+    dfree(v.gv);
+    dfree(v.gy);
+    dfree(v.li);
+    dfree(v.lj);
     dfree(gcs);
     dfree(gbs);
     dfree(gAs);

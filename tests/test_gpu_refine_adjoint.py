@@ -263,6 +263,32 @@ def test_unrolled_fp32_within_gate(Solver, oracle):
     assert rel(gc, gc_or) <= 1e-3 and rel(gb, gb_or) <= 1e-3 and rel(gA, gA_or) <= 1e-3
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("shape", [(300, 700, 5), (1501, 3500, 5), (9000, 21_000, 4)])
+def test_unrolled_checkpoints_do_not_change_results(Solver, oracle, precision, shape):
+    """Gradients from a tape of all iterates and from checkpoints (7, 16 and K
+    steps apart) have the same bits, whether the steps run in one workgroup or
+    in row blocks, and match the oracle's reverse pass."""
+    m, n, k = shape
+    lp = lpgen.planted_uniform(m=m, n=n, k=k, seed=m)
+    dr, dc, eta = _adjoint_setup(oracle, lp)
+    K = 37
+    xt = lpgen.target_vector(lp.n, 1)
+    ref = oracle.unrolled(lp, dr, dc, eta, eta, K, xt)
+    for small in (1, 0):
+        out = []
+        for tape_bytes, ck in ((1 << 28, 5), (0, 7), (0, 16), (0, K)):
+            with Solver.from_lp(lp, tuning={"small": small, "tape_bytes": tape_bytes}) as s:
+                s.configure(ruiz_passes=10, power_iters=5)
+                xK, tape = s.unrolled_forward(K, ck, eta, eta, precision=precision)
+                out.append((xK,) + tuple(tape.backward(2 * (xK - xt))))
+        for o in out[1:]:
+            assert all(np.array_equal(a, b) for a, b in zip(out[0], o))
+        tol = 1e-9 if precision == 0 else 1e-3
+        for a, b in zip(out[0], (ref[0],) + tuple(ref[2:])):
+            assert rel(a, b) <= tol
+
+
 @pytest.mark.timeout(900)
 def test_adjoint_full_size_vs_oracle_and_fd(Solver, oracle):
     """The adjoint workload at full size: m=50k, n=100k, 8 nonzeros per
