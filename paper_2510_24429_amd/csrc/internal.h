@@ -87,7 +87,7 @@ constexpr int kBktThreads = 1024;
 // in row blocks | tiles, by nonzeros: FP64 55k 8.5 | 9.3, 480k 11.4 | 11.9,
 // 800k 17.0 | 15.8; FP32 55k 9.6 | 8.4, 300k 11.3 | 9.7, 800k 15.7 | 12.6.
 constexpr int64_t kTileMin64 = 700000, kTileMin32 = 50000;
-// Quads [q0, q1) of the push order, all of column block cb (q0 == q1: padding).
+// Quads [q0, q1) of the push order, all of column block cb.
 struct PushItem {
     int32_t cb, q0, q1, pad;
 };
@@ -99,7 +99,8 @@ struct Bucket {
 struct HostBuckets {
     bool fragmented = false;          // row lengths too mixed to fill buckets
     int64_t quads = 0;                // groups of four products, runs padded
-    std::vector<PushItem> items;
+    std::vector<PushItem> items;      // in the order of their workgroups
+    std::vector<int32_t> first;       // workgroups + 1: first item of each
     std::vector<Bucket> buckets;
     std::vector<SplitRow> splits;
     int maxparts = 1;
@@ -120,10 +121,11 @@ int choose_layout(int64_t rows, int64_t cols, int64_t nnz, int P);
 
 // The same on the device.
 struct DevBuckets {
-    int nitems = 0, nbuckets = 0, nsplit = 0, maxparts = 1;
+    int ngroups = 0, nbuckets = 0, nsplit = 0, maxparts = 1;
     bool f64 = true;                  // FP64 products run here too
     int64_t quads = 0;
     PushItem *items = nullptr;
+    int32_t *first = nullptr;
     Bucket *buckets = nullptr;
     SplitRow *split = nullptr;
     uint16_t *col = nullptr, *pos = nullptr;

@@ -409,6 +409,7 @@ void free_csr(DevCsr &M) {
     }
     if (DevBuckets *k = M.bkt) {
         dfree(k->items);
+        dfree(k->first);
         dfree(k->buckets);
         dfree(k->split);
         dfree(k->col);
@@ -574,7 +575,6 @@ DevBuckets *upload_buckets(const HostBuckets &H, bool f64, bool force) {
     DevBuckets *K = new DevBuckets();
     K->f64 = f64;
     K->quads = H.quads;
-    K->nitems = (int)H.items.size();
     K->nbuckets = (int)H.buckets.size();
     K->nsplit = (int)H.splits.size();
     K->maxparts = H.maxparts;
@@ -589,6 +589,8 @@ DevBuckets *upload_buckets(const HostBuckets &H, bool f64, bool force) {
         K->gcol = upload(H.gcol);
     } else {
         K->items = upload(H.items);
+        K->first = upload(H.first);
+        K->ngroups = (int)H.first.size() - 1;
         K->col = upload(H.col);
         K->dest = upload(H.dest);
     }

@@ -89,7 +89,8 @@ int main() {
                    Case{40000, 3000, 3, 0}, Case{200, 100000, 300, 1},
                    Case{100000, 50000, 2, 2}, Case{1, 50000, 40000, 0},
                    Case{30000, kBktCols, 9, 1}, Case{30000, kBktCols + 1, 0.3, 0},
-                   Case{20000, 70001, 3, 3}, Case{300000, 400000, 12, 0}}) {
+                   Case{20000, 70001, 3, 3}, Case{300000, 400000, 12, 0},
+                   Case{2000, 300 * kBktCols, 100, 0}}) {
         const Csr A = make(c.m, c.n, c.avg, c.kind, g);
         const int64_t nnz = (int64_t)A.ci.size();
         std::vector<double> x(c.n), v(nnz), ref(c.m);
@@ -102,8 +103,10 @@ int main() {
             std::vector<double> prod(4 * B.quads, NAN), y(c.m, NAN);
             std::vector<char> written(B.quads, 0), seen(nnz, 0);
             int64_t covered = 0;
+            CHECK(!B.first.empty() && B.first[0] == 0 &&
+                  B.first.back() == (int32_t)B.items.size() &&
+                  std::is_sorted(B.first.begin(), B.first.end()));
             for (const PushItem &it : B.items) {
-                if (it.q0 == it.q1) continue;
                 CHECK(it.q0 >= 0 && it.q0 < it.q1 && it.q1 <= B.quads);
                 const int64_t c0 = (int64_t)it.cb * kBktCols;
                 CHECK(it.cb >= 0 && c0 < c.n);
