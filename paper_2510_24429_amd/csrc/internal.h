@@ -298,6 +298,10 @@ struct Iter {
 // out = M in  (M = A~ / A / A~32 chosen by the caller through `vals`)
 void spmv_f64(const DevCsr &M, const double *vals, const double *in,
               double *out, hipStream_t s);
+// ... with M's scaled values, over sqrt(*norm2) (over 1 where that is not
+// positive)
+void spmv_f64_normed(const DevCsr &M, const double *in, const double *norm2,
+                     double *out, hipStream_t s);
 void spmv_f64_in32(const DevCsr &M, const double *vals, const float *in,
                    double *out, hipStream_t s);
 void spmv_f32(const DevCsr &M, const float *in, float *out, hipStream_t s);
@@ -372,18 +376,17 @@ void launch_ruiz_rowmax(const DevCsr &M, const double *d_row,
                         hipStream_t s);
 void launch_ruiz_update(double *d, const double *rho, int64_t k,
                         hipStream_t s);
-// Entries of the rows of A scaled by fixed factors:
-// out[p] = (rs[row] * v[p]) * cs[col]; out32 (optional) gets the FP32 copy.
-void launch_scale_values(const DevCsr &M, const double *v, const double *rs,
-                         const double *cs, double *out, float *out32,
-                         hipStream_t s);
+// Entries scaled by the factors in the order of the entry (i, j) of A:
+// out[p] = (D_r,i * v[p]) * D_c,j; out32 (optional) gets the FP32 copy.  M and
+// transposed as above.
+void launch_scale_values(const DevCsr &M, const double *v, const double *d_row,
+                         const double *d_col, int transposed, double *out,
+                         float *out32, hipStream_t s);
 
 // Deterministic FP64 reductions: partial sums of squares / dot products by
 // blocks, then a fixed-order finish in one workgroup.
 void launch_dot(const double *a, const double *b, int64_t k, double *partial,
                 double *result, hipStream_t s);
-void launch_scale_vec(double *dst, const double *src, const double *factor,
-                      int64_t k, int mode, hipStream_t s);
 void launch_fill(double *p, double v, int64_t k, hipStream_t s);
 void launch_fill32(float *p, float v, int64_t k, hipStream_t s);
 void launch_to_f32(float *dst, const double *src, int64_t k, hipStream_t s);

@@ -148,6 +148,19 @@ struct StoreEpi {
     }
 };
 
+// out = row sum / sqrt(*norm2), or the sum itself where that is not positive.
+struct StoreNormedEpi {
+    double *out;
+    const double *norm2;
+    double nrm;
+    __device__ __forceinline__ bool begin() {
+        nrm = sqrt(*norm2);
+        if (!(nrm > 0.0)) nrm = 1.0;
+        return true;
+    }
+    __device__ __forceinline__ void operator()(int r, double s) const { out[r] = s / nrm; }
+};
+
 // Panel pass: row r of the stacked panel matrix stores its partial sum; the
 // wrapped epilogue's begin() still decides whether the pass runs at all.
 template <class Epi, typename Acc>
@@ -985,6 +998,11 @@ void rb_spmv(const DevCsr &M, const MT *vals, const VT *in, Epi e,
 void spmv_f64(const DevCsr &M, const double *vals, const double *in,
               double *out, hipStream_t s) {
     rb_spmv<double>(M, vals, in, StoreEpi<double, double>{out}, s);
+}
+
+void spmv_f64_normed(const DevCsr &M, const double *in, const double *norm2,
+                     double *out, hipStream_t s) {
+    rb_spmv<double>(M, (const double *)M.v64, in, StoreNormedEpi{out, norm2, 1.0}, s);
 }
 
 void spmv_f64_in32(const DevCsr &M, const double *vals, const float *in,
@@ -1940,34 +1958,105 @@ void launch_snapshot_pack(const State *st, bool f32, const void *x0,
 
 namespace {
 
-// G lanes per row; rho_r = max over the row of |(rs * v) * cs| where for the
-// rows of A (transposed = 0) rs = d_row[r], cs = d_col[ci]; for the rows of
-// A^T (transposed = 1) the first factor is the column's: (d_col[ci] * v) *
-// d_row[r].  Both orders are (D_r,i * a_ij) * D_c,j for entry (i, j).
-template <int G>
+// rho_r = max over row r of |(D_r,i a_ij) D_c,j|, over the row blocks: for the
+// rows of A (TR false) the row's factor comes first, so values and gathered
+// factors are staged and combined row by row; for the rows of A^T the
+// gathered factor comes first and the row's can multiply the maximum
+// (rounding is monotone).  Bound by the gathers, as the steps are.  (A group
+// of lanes per row, sized to the mean length, left skewed rows to few lanes:
+// 145 us a pass on the power-law columns, 4.7M nonzeros, and 3.2 ms on the
+// coupled LP's 55M.)
+template <bool TR>
 __global__ __launch_bounds__(kWG) void k_ruiz_rowmax(
-    const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
-    const double *__restrict__ v, const double *__restrict__ d_row,
-    const double *__restrict__ d_col, int transposed, int64_t rows,
-    double *__restrict__ rho) {
-    const int64_t g = ((int64_t)blockIdx.x * kWG + threadIdx.x) / G;
-    const int lane = threadIdx.x & (G - 1);
-    const int64_t ngroups = (int64_t)gridDim.x * kWG / G;
-    // every lane runs the same number of rounds so the shuffles are uniform
-    for (int64_t base = 0; base < rows; base += ngroups) {
-        const int64_t r = base + g;
+    const RowBlock *__restrict__ blks, const int32_t *__restrict__ rp,
+    const int32_t *__restrict__ ci, const double *__restrict__ v,
+    const double *__restrict__ d_row, const double *__restrict__ d_col,
+    double *__restrict__ rho, double *__restrict__ part, int maxparts) {
+    constexpr int U = kTile64 / kWG;
+    __shared__ double s_v[kTile64];
+    __shared__ double s_d[TR ? 1 : kTile64];
+    __shared__ double s_red[4];
+    const RowBlock b = blks[blockIdx.x];
+    const int tid = threadIdx.x, R = b.r1 - b.r0;
+    if (R == 1) {
+        int p0 = b.p0, p1 = b.p1;
+        if (b.nparts > 1) {
+            const int chunk = (p1 - p0 + b.nparts - 1) / b.nparts;
+            p0 = p0 + b.part * chunk;
+            p1 = min(p1, p0 + chunk);
+        }
+        const double dr = d_row[b.r0];
         double mx = 0.0;
-        if (r < rows) {
-            const double dr = d_row[r];
-            for (int p = rp[r] + lane; p < rp[r + 1]; p += G) {
-                const double a = transposed ? (d_col[ci[p]] * v[p]) * dr
-                                            : (dr * v[p]) * d_col[ci[p]];
-                mx = fmax(mx, fabs(a));
+#pragma unroll 4
+        for (int p = p0 + tid; p < p1; p += kWG) {
+            const double a = TR ? (d_col[ci[p]] * v[p]) * dr : (dr * v[p]) * d_col[ci[p]];
+            mx = fmax(mx, fabs(a));
+        }
+        mx = wave_max(mx);
+        if ((tid & 63) == 0) s_red[tid >> 6] = mx;
+        __syncthreads();
+        if (tid == 0) {
+            mx = fmax(fmax(s_red[0], s_red[1]), fmax(s_red[2], s_red[3]));
+            if (b.nparts > 1)
+                part[b.slot * maxparts + b.part] = mx;
+            else
+                rho[b.r0] = mx;
+        }
+        return;
+    }
+    const int nz = b.p1 - b.p0;
+    {
+        int j[U];
+        double a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = tid + u * kWG;
+            if (q < nz) {
+                j[u] = ci[b.p0 + q];
+                a[u] = v[b.p0 + q];
             }
         }
-        for (int o = G >> 1; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
-        if (r < rows && lane == 0) rho[r] = mx;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = tid + u * kWG;
+            if (q < nz) {
+                if (TR) {
+                    s_v[q] = d_col[j[u]] * a[u];
+                } else {
+                    s_v[q] = a[u];
+                    s_d[q] = d_col[j[u]];
+                }
+            }
+        }
     }
+    int G = 64;
+    while (G > 1 && G * R > kWG) G >>= 1;
+    const int lane = tid & (G - 1);
+    __syncthreads();
+    for (int r0 = 0; r0 < R; r0 += kWG / G) {
+        const int r = r0 + tid / G;
+        double mx = 0.0;
+        if (r < R) {
+            const double dr = d_row[b.r0 + r];
+            const int q1 = rp[b.r0 + r + 1] - b.p0;
+            for (int q = rp[b.r0 + r] - b.p0 + lane; q < q1; q += G)
+                mx = fmax(mx, TR ? fabs(s_v[q]) : fabs((dr * s_v[q]) * s_d[q]));
+            if (TR) mx = fmax(0.0, mx * dr);
+        }
+        for (int o = G >> 1; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+        if (r < R && lane == 0) rho[b.r0 + r] = mx;
+    }
+}
+
+// Rows split over several workgroups: the maximum of their parts.
+__global__ __launch_bounds__(kFixThreads) void k_split_max(
+    const SplitRow *__restrict__ sp, int nsplit, const double *__restrict__ part,
+    int maxparts, double *__restrict__ rho) {
+    const int t = blockIdx.x * kFixThreads + threadIdx.x;
+    if (t >= nsplit) return;
+    double mx = 0.0;
+    for (int q = 0; q < sp[t].nparts; ++q) mx = fmax(mx, part[t * maxparts + q]);
+    rho[sp[t].row] = mx;
 }
 
 __global__ __launch_bounds__(kWG) void k_ruiz_update(double *d,
@@ -1981,33 +2070,41 @@ __global__ __launch_bounds__(kWG) void k_ruiz_update(double *d,
     }
 }
 
-template <int G>
+// out[p] = (D_r,i v[p]) * D_c,j over the row blocks (out32: its FP32 copy); an
+// entry's row comes from a search of the block's row pointers in LDS.
+template <bool TR>
 __global__ __launch_bounds__(kWG) void k_scale_values(
-    const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
-    const double *__restrict__ v, const double *__restrict__ d_row,
-    const double *__restrict__ d_col, int transposed, int64_t rows,
+    const RowBlock *__restrict__ blks, const int32_t *__restrict__ rp,
+    const int32_t *__restrict__ ci, const double *__restrict__ v,
+    const double *__restrict__ d_row, const double *__restrict__ d_col,
     double *__restrict__ out, float *__restrict__ out32) {
-    const int64_t g = ((int64_t)blockIdx.x * kWG + threadIdx.x) / G;
-    const int lane = threadIdx.x & (G - 1);
-    const int64_t ngroups = (int64_t)gridDim.x * kWG / G;
-    for (int64_t r = g; r < rows; r += ngroups) {
-        const double dr = d_row[r];
-        for (int p = rp[r] + lane; p < rp[r + 1]; p += G) {
-            const double a = transposed ? (d_col[ci[p]] * v[p]) * dr
-                                        : (dr * v[p]) * d_col[ci[p]];
-            out[p] = a;
-            if (out32) out32[p] = (float)a;
-        }
+    __shared__ int s_rp[kTile64 + 1];
+    __shared__ double s_dr[kTile64];
+    const RowBlock b = blks[blockIdx.x];
+    const int tid = threadIdx.x, R = b.r1 - b.r0;
+    int p0 = b.p0, p1 = b.p1;
+    if (b.nparts > 1) {
+        const int chunk = (p1 - p0 + b.nparts - 1) / b.nparts;
+        p0 = p0 + b.part * chunk;
+        p1 = min(p1, p0 + chunk);
     }
-}
-
-int lanes_for(const DevCsr &M) {
-    const double avg = M.rows ? (double)M.nnz / (double)M.rows : 1.0;
-    if (avg <= 4) return 4;
-    if (avg <= 8) return 8;
-    if (avg <= 16) return 16;
-    if (avg <= 32) return 32;
-    return 64;
+    for (int r = tid; r < R; r += kWG) {
+        s_rp[r + 1] = rp[b.r0 + r + 1];
+        s_dr[r] = d_row[b.r0 + r];
+    }
+    __syncthreads();
+    for (int p = p0 + tid; p < p1; p += kWG) {
+        // the first row that ends beyond p
+        int lo = 0, hi = R - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (s_rp[mid + 1] > p) hi = mid; else lo = mid + 1;
+        }
+        const double dr = s_dr[lo], dc = d_col[ci[p]];
+        const double a = TR ? (dc * v[p]) * dr : (dr * v[p]) * dc;
+        out[p] = a;
+        if (out32) out32[p] = (float)a;
+    }
 }
 
 }  // namespace
@@ -2015,15 +2112,22 @@ int lanes_for(const DevCsr &M) {
 void launch_ruiz_rowmax(const DevCsr &M, const double *d_row,
                         const double *d_col, int transposed, double *rho,
                         hipStream_t s) {
-    const int G = lanes_for(M);
-    const int g = grid_for(M.rows * G, kWG, 16384);
-    switch (G) {
-        case 4: hipLaunchKernelGGL(k_ruiz_rowmax<4>, dim3(g), dim3(kWG), 0, s, M.rp, M.ci, M.v_orig, d_row, d_col, transposed, M.rows, rho); break;
-        case 8: hipLaunchKernelGGL(k_ruiz_rowmax<8>, dim3(g), dim3(kWG), 0, s, M.rp, M.ci, M.v_orig, d_row, d_col, transposed, M.rows, rho); break;
-        case 16: hipLaunchKernelGGL(k_ruiz_rowmax<16>, dim3(g), dim3(kWG), 0, s, M.rp, M.ci, M.v_orig, d_row, d_col, transposed, M.rows, rho); break;
-        case 32: hipLaunchKernelGGL(k_ruiz_rowmax<32>, dim3(g), dim3(kWG), 0, s, M.rp, M.ci, M.v_orig, d_row, d_col, transposed, M.rows, rho); break;
-        default: hipLaunchKernelGGL(k_ruiz_rowmax<64>, dim3(g), dim3(kWG), 0, s, M.rp, M.ci, M.v_orig, d_row, d_col, transposed, M.rows, rho); break;
+    if (M.nblk64 > 0) {
+        auto run = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(M.nblk64), dim3(kWG), 0, s, M.blk64,
+                               M.rp, M.ci, M.v_orig, d_row, d_col, rho,
+                               M.part64, M.maxparts64);
+        };
+        if (transposed)
+            run(k_ruiz_rowmax<true>);
+        else
+            run(k_ruiz_rowmax<false>);
     }
+    if (M.nsplit64 > 0)
+        hipLaunchKernelGGL(k_split_max,
+                           dim3((M.nsplit64 + kFixThreads - 1) / kFixThreads),
+                           dim3(kFixThreads), 0, s, M.split64, M.nsplit64,
+                           M.part64, M.maxparts64, rho);
 }
 
 void launch_ruiz_update(double *d, const double *rho, int64_t k,
@@ -2032,18 +2136,18 @@ void launch_ruiz_update(double *d, const double *rho, int64_t k,
                        0, s, d, rho, k);
 }
 
-void launch_scale_values(const DevCsr &M, const double *v, const double *rs,
-                         const double *cs, double *out, float *out32,
-                         hipStream_t s) {
-    const int G = lanes_for(M);
-    const int g = grid_for(M.rows * G, kWG, 16384);
-    switch (G) {
-        case 4: hipLaunchKernelGGL(k_scale_values<4>, dim3(g), dim3(kWG), 0, s, M.rp, M.ci, v, rs, cs, 0, M.rows, out, out32); break;
-        case 8: hipLaunchKernelGGL(k_scale_values<8>, dim3(g), dim3(kWG), 0, s, M.rp, M.ci, v, rs, cs, 0, M.rows, out, out32); break;
-        case 16: hipLaunchKernelGGL(k_scale_values<16>, dim3(g), dim3(kWG), 0, s, M.rp, M.ci, v, rs, cs, 0, M.rows, out, out32); break;
-        case 32: hipLaunchKernelGGL(k_scale_values<32>, dim3(g), dim3(kWG), 0, s, M.rp, M.ci, v, rs, cs, 0, M.rows, out, out32); break;
-        default: hipLaunchKernelGGL(k_scale_values<64>, dim3(g), dim3(kWG), 0, s, M.rp, M.ci, v, rs, cs, 0, M.rows, out, out32); break;
-    }
+void launch_scale_values(const DevCsr &M, const double *v, const double *d_row,
+                         const double *d_col, int transposed, double *out,
+                         float *out32, hipStream_t s) {
+    if (M.nblk64 == 0) return;
+    auto run = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(M.nblk64), dim3(kWG), 0, s, M.blk64, M.rp,
+                           M.ci, v, d_row, d_col, out, out32);
+    };
+    if (transposed)
+        run(k_scale_values<true>);
+    else
+        run(k_scale_values<false>);
 }
 
 // ============================================================ vector kernels
@@ -2066,38 +2170,19 @@ __global__ __launch_bounds__(kWG) void k_dot_partial(const double *a,
 // mode 0: sum of partials; mode 1: max of partials
 __global__ __launch_bounds__(kWG) void k_finish(const double *partial, int np,
                                                 double *result, int mode) {
-    __shared__ double sred[kWG];
-    const int tid = threadIdx.x;
+    __shared__ double s_red[4];
     double v = 0.0;
-    for (int b = tid; b < np; b += kWG)
-        v = mode ? fmax(v, partial[b]) : v + partial[b];
-    sred[tid] = v;
+#pragma unroll 4
+    for (int b = threadIdx.x; b < np; b += kWG) {
+        const double p = partial[b];
+        v = mode ? fmax(v, p) : v + p;
+    }
+    v = mode ? wave_max(v) : wave_sum(v);
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = kWG / 2; s > 0; s >>= 1) {
-        if (tid < s)
-            sred[tid] = mode ? fmax(sred[tid], sred[tid + s])
-                             : sred[tid] + sred[tid + s];
-        __syncthreads();
-    }
-    if (tid == 0) *result = sred[0];
-}
-
-// dst = src / sqrt(*factor) (mode 0) ; dst = src * (*factor) (mode 1)
-__global__ __launch_bounds__(kWG) void k_scale_vec(double *dst,
-                                                   const double *src,
-                                                   const double *factor,
-                                                   int64_t k, int mode) {
-    const double f = *factor;
-    const double nrm = sqrt(f);
-    if (mode == 0 && !(nrm > 0.0)) {
-        for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < k;
-             i += (int64_t)gridDim.x * kWG)
-            dst[i] = src[i];
-        return;
-    }
-    for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < k;
-         i += (int64_t)gridDim.x * kWG)
-        dst[i] = mode == 0 ? src[i] / nrm : src[i] * f;
+    if (threadIdx.x == 0)
+        *result = mode ? fmax(fmax(s_red[0], s_red[1]), fmax(s_red[2], s_red[3]))
+                       : (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
 }
 
 template <typename T>
@@ -2247,12 +2332,6 @@ void launch_norm_unscaled(const double *vs, const double *d, int64_t k,
                        0, s, vs, d, k, partial);
     hipLaunchKernelGGL(k_finish, dim3(1), dim3(kWG), 0, s, partial,
                        red_blocks(k), result, 0);
-}
-
-void launch_scale_vec(double *dst, const double *src, const double *factor,
-                      int64_t k, int mode, hipStream_t s) {
-    hipLaunchKernelGGL(k_scale_vec, dim3(grid_for(k, kWG, 4096)), dim3(kWG), 0,
-                       s, dst, src, factor, k, mode);
 }
 
 void launch_fill(double *p, double v, int64_t k, hipStream_t s) {

@@ -756,9 +756,8 @@ double dev_norm(pdhg_ctx *c, const double *v, int64_t k) {
 
 // Scaled values of both CSRs from A's loaded values and the factors.
 void apply_scaling(pdhg_ctx *c) {
-    launch_scale_values(c->A, c->A.v_orig, c->dr, c->dc, c->A.v64, c->A.v32, c->stream);
-    launch_permute(c->At.v64, c->A.v64, c->perm, c->nnz, c->stream);
-    launch_to_f32(c->At.v32, c->At.v64, c->nnz, c->stream);
+    launch_scale_values(c->A, c->A.v_orig, c->dr, c->dc, 0, c->A.v64, c->A.v32, c->stream);
+    launch_scale_values(c->At, c->At.v_orig, c->dc, c->dr, 1, c->At.v64, c->At.v32, c->stream);
     for (DevCsr *M : {&c->A, &c->At}) {
         if (M->small)
             launch_gather_pad(M->small->v64, M->small->v32, M->v64, M->small->src, M->small->entries, c->stream);
@@ -811,15 +810,18 @@ void ruiz(pdhg_ctx *c, int passes) {
 }
 
 // Power iteration for sigma_hat ~ ||A~||_2: v0 = 1/sqrt(n) ones, `iters`
-// steps of w = A~^T A~ v, v = w / ||w||, then sqrt(||A~^T A~ v||).
+// steps of w = A~^T A~ v, v = w / ||w||, then sqrt(||A~^T A~ v||).  The
+// normalisation happens in the next product's epilogue.
 double power_iteration(pdhg_ctx *c, int iters) {
-    double *v = c->aty_avg, *u = c->ax_avg, *w = c->aty_cur;
-    launch_fill(v, 1.0 / std::sqrt((double)c->n), c->n, c->stream);
+    double *u = c->ax_avg, *w = c->aty_cur;
+    launch_fill(w, 1.0 / std::sqrt((double)c->n), c->n, c->stream);
     for (int it = 0; it <= iters; ++it) {
-        spmv_f64(c->A, c->A.v64, v, u, c->stream);
+        if (it == 0)
+            spmv_f64(c->A, c->A.v64, w, u, c->stream);
+        else
+            spmv_f64_normed(c->A, w, c->scal, u, c->stream);
         spmv_f64(c->At, c->At.v64, u, w, c->stream);
         launch_dot(w, w, c->n, c->partial, c->scal, c->stream);
-        if (it < iters) launch_scale_vec(v, w, c->scal, c->n, 0, c->stream);
     }
     double nw2 = read_scalar(c, c->scal);
     double s = std::sqrt(std::sqrt(nw2));
@@ -2993,7 +2995,7 @@ void unrolled_backward_T(pdhg_tape *tp, const double *gxK, double *gc,
     vec_out(c, gb, out, true, mem);
     sync(c);
     widen(gAs, nnz);
-    launch_scale_values(c->A, g64, c->dr, c->dc, out, nullptr, c->stream);
+    launch_scale_values(c->A, g64, c->dr, c->dc, 0, out, nullptr, c->stream);
     launch_permute(g64, out, c->apos, nnz, c->stream);   // A's original order
     copy_out(c, gA, g64, nnz, mem);
     sync(c);

@@ -183,6 +183,38 @@ def test_ruiz_factors_bitwise(Solver, oracle):
         assert np.array_equal(gdc, dc)
 
 
+@pytest.mark.parametrize("split", [False, True])
+def test_ruiz_and_scaled_values_over_all_row_kinds(Solver, oracle, split):
+    """Ruiz factors bitwise equal to the oracle's, and products with the scaled
+    values, where rows and columns are empty, fill or overflow a row block
+    (1,021 nonzeros) or are split over workgroups."""
+    rng = np.random.default_rng(8)
+    m, n = 40, 5000
+    lens = np.array([0, 1, 1020, 1021, 1022, 3000, 5000, 2] + [70] * 32)
+    lens = np.minimum(lens, n - 1)                  # column n - 1 is empty
+    rows = np.repeat(np.arange(m), lens)
+    cols = np.concatenate([np.sort(rng.choice(n - 1, L, replace=False)) for L in lens])
+    vals = rng.standard_normal(rows.size) * 10.0 ** rng.uniform(-3, 3, rows.size)
+    for t in (False, True):        # long rows of A, then of its transpose
+        lp = (lpgen.from_coo(n, m, cols, rows, vals, np.ones(n), np.ones(m)) if t
+              else lpgen.from_coo(m, n, rows, cols, vals, np.ones(m), np.ones(n)))
+        tuning = {"split_threshold": 2048, "split_chunk": 256} if split else None
+        odr, odc, _ = oracle.ruiz(lp, 10)
+        with Solver.from_lp(lp, tuning=tuning) as s:
+            s.configure()
+            dr, dc = s.get_scaling()
+            assert np.array_equal(dr, odr) and np.array_equal(dc, odc)
+            r = np.repeat(np.arange(lp.m), np.diff(lp.a_rp))
+            sv = (dr[r] * lp.a_v) * dc[lp.a_ci]
+            x, y = rng.standard_normal(lp.n), rng.standard_normal(lp.m)
+            for which, vec, ref_out in (
+                    (0, x, np.bincount(r, weights=sv * x[lp.a_ci], minlength=lp.m)),
+                    (1, y, np.bincount(lp.a_ci, weights=sv * y[r], minlength=lp.n))):
+                # at most 5,000 products a sum
+                assert rel(s.spmv(which, vec, scaled=True), ref_out) <= 1e-13
+                assert rel(s.spmv(which, vec, scaled=True, precision=1), ref_out) <= 1e-5
+
+
 def test_power_iteration_matches(Solver, oracle):
     lp = lpgen.make("uniform_m500_n1k")
     ref = oracle.solve(lp, eps_rel=1e-6, max_iters=0)
