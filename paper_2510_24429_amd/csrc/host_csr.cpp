@@ -654,15 +654,23 @@ static void over_buckets(int64_t nb, int64_t nnz, Fn fn) {
     for (auto &t : th) t.join();
 }
 
-// Push buckets.  Columns are cut into blocks of kBktCols.  The nonzeros of one
-// (column block, bucket) pair form a run, padded to whole quads: the push pass
-// walks the runs of a column block one after the other, and each run is
-// contiguous among its bucket's products.
+// Push buckets.  Columns are cut into blocks, as many as divide a round of one
+// workgroup per CU or are divided by it (303 blocks of 16,384 columns of the
+// multicommodity dual left the second round nearly empty, 114 us a step
+// against 99 with 256; 610 blocks of the 55M-nonzero coupled one 468 us
+// against 420 with 512).  The nonzeros of one (column block, bucket) pair form
+// a run, padded to whole quads: the push pass walks the runs of a column block
+// one after the other, and each run is contiguous among its bucket's products.
 HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
                        const int32_t *ci, bool force) {
     HostBuckets B;
     const int64_t nnz = rp[rows], cost = bucket_cost(rp, 0, rows);
-    const int64_t ncb = (cols + kBktCols - 1) / kBktCols;
+    constexpr int64_t kCus = 256;
+    int64_t ncb = 1;
+    while (ncb * kBktCols < cols) ncb = ncb < kCus ? 2 * ncb : ncb + kCus;
+    // (whole 16-byte units of the vector)
+    B.width = (int)std::min<int64_t>(kBktCols, ((cols + ncb - 1) / ncb + 3) / 4 * 4);
+    ncb = (cols + B.width - 1) / B.width;
     const int64_t fill = bucket_fill(cost, nnz);
     pack_buckets(B, 0, rows, rp, fill, false);
     const int64_t nb = (int64_t)B.buckets.size();
@@ -674,7 +682,7 @@ HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
         std::vector<int32_t> cnt((size_t)ncb);
         for (int64_t b = b0; b < b1; ++b) {
             std::fill(cnt.begin(), cnt.end(), 0);
-            for (int64_t p = B.buckets[b].p0; p < B.buckets[b].p1; ++p) ++cnt[ci[p] / kBktCols];
+            for (int64_t p = B.buckets[b].p0; p < B.buckets[b].p1; ++p) ++cnt[ci[p] / B.width];
             for (int64_t k = 0; k < ncb; ++k) run[k * nb + b] = (cnt[k] + 3) / 4;
         }
     });
@@ -711,20 +719,18 @@ HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
                 o += n;
             }
             for (int64_t p = K.p0; p < K.p1; ++p) {
-                const int64_t k = ci[p] / kBktCols;
-                B.col[c1[k]] = (uint16_t)(ci[p] % kBktCols);
+                const int64_t k = ci[p] / B.width;
+                B.col[c1[k]] = (uint16_t)(ci[p] % B.width);
                 B.src[c1[k]++] = (int32_t)p;
                 B.pos[c2[k]++] = (uint16_t)(p - K.p0);
             }
         }
     });
-    // Work of the push pass: slices of single column blocks, of equal size and
-    // as many as fill whole rounds (at most four) of one workgroup per CU.
-    // Where the blocks leave the last round nearly empty, each CU takes an
-    // equal share across blocks instead and loads a block of x more often
-    // (multicommodity dual, 303 blocks: 114 -> 106 us a step; otherwise slices
-    // are the faster: 55M-nonzero coupled iteration 917 us against 929).
-    constexpr int64_t kCus = 256, kXcd = 8;
+    // items: slices of single blocks, of equal size and as many as fill whole
+    // rounds (at most four); each XCD (workgroups go to the 8 XCDs
+    // round-robin) takes neighbouring ones, so that runs that share lines of
+    // the products are written through one L2
+    constexpr int64_t kXcd = 8;
     const int64_t want = kCus * std::max<int64_t>(1, std::min<int64_t>(4, B.quads / (kCus * 8192)));
     auto count = [&](int64_t S) {
         int64_t n = 0;
@@ -737,37 +743,16 @@ HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
         const int64_t mid = (lo + hi) / 2;
         if (count(mid) <= most) hi = mid; else lo = mid + 1;
     }
-    std::vector<std::vector<PushItem>> work;
-    const int64_t n = count(lo), rounds = (n + kCus - 1) / kCus;
-    if (rounds > 1 && (double)n < 0.75 * (double)(rounds * kCus)) {
-        for (int64_t w = 0; w < kCus; ++w) {
-            const int64_t a = B.quads * w / kCus, e = B.quads * (w + 1) / kCus;
-            std::vector<PushItem> g;
-            int64_t k = std::upper_bound(cq.begin(), cq.end(), a) - cq.begin() - 1;
-            for (int64_t q0 = a; q0 < e; q0 = cq[++k]) {
-                const int64_t q1 = std::min(e, cq[k + 1]);
-                if (q1 > q0) g.push_back({(int32_t)k, (int32_t)q0, (int32_t)q1, 0});
-            }
-            work.push_back(g);
-        }
-    } else {
-        for (int64_t k = 0; k < ncb; ++k) {
-            const int64_t len = cq[k + 1] - cq[k], ns = (len + lo - 1) / lo;
-            for (int64_t i = 0; i < ns; ++i)
-                work.push_back({{(int32_t)k, (int32_t)(cq[k] + len * i / ns), (int32_t)(cq[k] + len * (i + 1) / ns), 0}});
-        }
+    std::vector<PushItem> it;
+    for (int64_t k = 0; k < ncb; ++k) {
+        const int64_t len = cq[k + 1] - cq[k], ns = (len + lo - 1) / lo;
+        for (int64_t i = 0; i < ns; ++i)
+            it.push_back({(int32_t)k, (int32_t)(cq[k] + len * i / ns), (int32_t)(cq[k] + len * (i + 1) / ns), 0});
     }
-    // each XCD (workgroups go to the 8 XCDs round-robin) takes neighbouring
-    // work, so that runs that share lines of the products are written through
-    // one L2
-    const int64_t per = ((int64_t)work.size() + kXcd - 1) / kXcd;
-    B.first.assign(1, 0);
+    const int64_t ni = (int64_t)it.size(), per = (ni + kXcd - 1) / kXcd;
     for (int64_t i = 0; i < per; ++i)
-        for (int64_t x = 0; x < kXcd; ++x) {
-            if (x * per + i < (int64_t)work.size())
-                B.items.insert(B.items.end(), work[x * per + i].begin(), work[x * per + i].end());
-            B.first.push_back((int32_t)B.items.size());
-        }
+        for (int64_t x = 0; x < kXcd; ++x)
+            B.items.push_back(x * per + i < ni ? it[x * per + i] : PushItem{0, 0, 0, 0});
     return B;
 }
 
@@ -895,15 +880,15 @@ HostSmall build_small(int64_t rows, int64_t cols, const int64_t *rp,
 //   1M x 400k dual, 8M, 8 MB, 20 a row:       72 | 62 | 55;  54 | 46 | 38
 //   ... primal, 3.2 MB:                       65 | 57 | 58;  51 | 44 | 36
 //   multicommodity primal, 14.6M, 10.8 MB:   133 | 118 | 119;  98 | 79 | 69
-//   ... dual, 40 MB in 8 panels:             143 | 142 | 115; 100 | 93 | 66
+//   ... dual, 40 MB in 8 panels:             143 | 142 |  99; 100 | 93 | 58
 //   840k-column one, dual, 2.4M, 6.7 MB:      30 | 26 | 26;  21 | 21 | 18
 //   ... primal, 1.9 MB:                       24 | 20 | 27;  21 | 15 | 19
 //   600k x 200k dual, 2.4M, 4.8 MB:           28 | 22 | 25;  21 | 18 | 17
 //   power-law 300k dual, 2.8M, 2.4 MB:        21 | 17 | 25;  17 | 14 | 17
 //   400k x 160k dual, 1.2M, 3.2 MB:           16 | 15 | 19;  14 | 12 | 14
 //   2M x 1M dual, 24M, 16 MB:                199 | 178 | 147; 152 | 134 | 84
-//   coupled dual, 55M, 80 MB in 8 panels:    708 | 563 | 467; 431 | 406 | 241
-//   ... 110M, 160 MB:                       1764 |  -  | 1011; 1260 | - | 566
+//   coupled dual, 55M, 80 MB in 8 panels:    708 | 563 | 420; 431 | 406 | 212
+//   ... 110M, 160 MB:                       1764 |  -  |  985; 1260 | - | 547
 int choose_layout(int64_t rows, int64_t cols, int64_t nnz, int P) {
     constexpr double kMiB = 1048576.0;
     const double panel = 8.0 * (double)cols / P;
@@ -911,7 +896,7 @@ int choose_layout(int64_t rows, int64_t cols, int64_t nnz, int P) {
     if (panel <= (nnz < 6000000 ? 6.0 : 2.25) * kMiB &&
         (P == 1 || nnz >= 8 * (int64_t)P * rows))
         return LAYOUT_TILES;
-    // runs of eight nonzeros or more (33M columns)
+    // runs of eight nonzeros or more (41M columns)
     const bool runs = (cols + kBktCols - 1) / kBktCols <= kBktCap / 8;
     return nnz >= 2000000 && runs ? LAYOUT_PUSH : LAYOUT_ROWS;
 }

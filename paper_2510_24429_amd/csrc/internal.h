@@ -76,18 +76,18 @@ HostBins build_panel_blocks(int64_t rows, const int64_t *srp, int P, int tile,
 
 // Buckets of one SpMV side (see host_csr.cpp): consecutive rows whose products
 // one workgroup sums in LDS.  A tile's nonzeros gather the vector themselves;
-// otherwise a push pass multiplies the nonzeros of one block of kBktCols
+// otherwise a push pass multiplies the nonzeros of one block of up to kBktCols
 // columns, its part of the vector in LDS, and writes the products to the
 // buckets of their rows.
 enum { LAYOUT_CHOOSE = -1, LAYOUT_ROWS = 0, LAYOUT_TILES = 1, LAYOUT_PUSH = 2 };
 constexpr int kBktCap = 1 << 14;      // most nonzeros of a bucket (128 KB of FP64)
-constexpr int kBktCols = 1 << 14;     // columns per block (the same)
+constexpr int kBktCols = 20000;       // most columns of a block (160 KB of FP64)
 constexpr int kBktThreads = 1024;
 // Fewest nonzeros that run in tiles, FP64 and FP32.  Measured, us an iteration
 // in row blocks | tiles, by nonzeros: FP64 55k 8.5 | 9.3, 480k 11.4 | 11.9,
 // 800k 17.0 | 15.8; FP32 55k 9.6 | 8.4, 300k 11.3 | 9.7, 800k 15.7 | 12.6.
 constexpr int64_t kTileMin64 = 700000, kTileMin32 = 50000;
-// Quads [q0, q1) of the push order, all of column block cb.
+// Quads [q0, q1) of the push order, all of column block cb (q0 == q1: padding).
 struct PushItem {
     int32_t cb, q0, q1, pad;
 };
@@ -99,8 +99,8 @@ struct Bucket {
 struct HostBuckets {
     bool fragmented = false;          // row lengths too mixed to fill buckets
     int64_t quads = 0;                // groups of four products, runs padded
-    std::vector<PushItem> items;      // in the order of their workgroups
-    std::vector<int32_t> first;       // workgroups + 1: first item of each
+    int width = 0;                    // columns per block
+    std::vector<PushItem> items;
     std::vector<Bucket> buckets;
     std::vector<SplitRow> splits;
     int maxparts = 1;
@@ -121,11 +121,10 @@ int choose_layout(int64_t rows, int64_t cols, int64_t nnz, int P);
 
 // The same on the device.
 struct DevBuckets {
-    int ngroups = 0, nbuckets = 0, nsplit = 0, maxparts = 1;
+    int width = 0, nitems = 0, nbuckets = 0, nsplit = 0, maxparts = 1;
     bool f64 = true;                  // FP64 products run here too
     int64_t quads = 0;
     PushItem *items = nullptr;
-    int32_t *first = nullptr;
     Bucket *buckets = nullptr;
     SplitRow *split = nullptr;
     uint16_t *col = nullptr, *pos = nullptr;

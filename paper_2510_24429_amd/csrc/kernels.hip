@@ -592,15 +592,14 @@ struct UnitOf<float> {
     using I = v4i;
 };
 
-// Push pass: each workgroup multiplies the quads of its items with their column
+// Push pass: each workgroup multiplies the quads of its item with their column
 // block of x, which sits in LDS, into their buckets.  Bound by streaming 19
 // (FP64) or 11 (FP32) bytes a nonzero, at about 4 TB/s.
 template <typename MT, typename VT, typename Acc>
 __global__ __launch_bounds__(kBktThreads) void k_bkt_push(
-    const PushItem *__restrict__ items, const int32_t *__restrict__ first,
-    const uint16_t *__restrict__ col, const MT *__restrict__ val,
-    const int32_t *__restrict__ dest, const VT *__restrict__ x, int64_t cols,
-    Acc *__restrict__ prod) {
+    const PushItem *__restrict__ items, const uint16_t *__restrict__ col,
+    const MT *__restrict__ val, const int32_t *__restrict__ dest,
+    const VT *__restrict__ x, int64_t cols, int width, Acc *__restrict__ prod) {
     __shared__ __align__(16) VT s_x[kBktCols];
     using Un = UnitOf<MT>;
     using X = UnitOf<VT>;
@@ -623,43 +622,41 @@ __global__ __launch_bounds__(kBktThreads) void k_bkt_push(
         for (int i = 0; i < Un::W; ++i) o[i] = (Acc)r.a[i] * (Acc)s_x[r.j[i]];
         *(Out *)(prod + 4 * (int64_t)r.d + Un::W * (p % F)) = o;
     };
-    for (int s = first[blockIdx.x]; s < first[blockIdx.x + 1]; ++s) {
-        const PushItem it = items[s];
-        // whole rounds of U units per lane without a bound check, the next
-        // round's loads issued ahead of this round's products; then the rest
-        const int64_t end = (int64_t)F * it.q1;
-        int64_t h = (int64_t)F * it.q0 + tid;
-        const int rounds = (int)((end - (h - tid)) / (U * kBktThreads));
-        Regs r[U];
-        if (rounds > 0)
+    const PushItem it = items[blockIdx.x];
+    if (it.q0 == it.q1) return;
+    // whole rounds of U units per lane without a bound check, the next round's
+    // loads issued ahead of this round's products; then the rest
+    const int64_t end = (int64_t)F * it.q1;
+    int64_t h = (int64_t)F * it.q0 + tid;
+    const int rounds = (int)((end - (h - tid)) / (U * kBktThreads));
+    Regs r[U];
+    if (rounds > 0)
 #pragma unroll
-            for (int u = 0; u < U; ++u) fetch(h + u * kBktThreads, r[u]);
-        const int64_t c0 = (int64_t)it.cb * kBktCols;
-        const int nc = (int)(cols - c0 < kBktCols ? cols - c0 : kBktCols);
-        __syncthreads();                 // the previous block is done with s_x
-        for (int i = X::W * tid; i < nc; i += X::W * kBktThreads) {
-            if (i + X::W <= nc) {
-                *(typename X::V *)(s_x + i) = *(const typename X::V *)(x + c0 + i);
-            } else {
-                for (int u = i; u < nc; ++u) s_x[u] = x[c0 + u];
-            }
+        for (int u = 0; u < U; ++u) fetch(h + u * kBktThreads, r[u]);
+    const int64_t c0 = (int64_t)it.cb * width;
+    const int nc = (int)(cols - c0 < width ? cols - c0 : width);
+    for (int i = X::W * tid; i < nc; i += X::W * kBktThreads) {
+        if (i + X::W <= nc) {
+            *(typename X::V *)(s_x + i) = *(const typename X::V *)(x + c0 + i);
+        } else {
+            for (int u = i; u < nc; ++u) s_x[u] = x[c0 + u];
         }
-        __syncthreads();
-        for (int k = 1; k <= rounds; ++k, h += U * kBktThreads) {
-            Regs n[U];
-            if (k < rounds) {
+    }
+    __syncthreads();
+    for (int k = 1; k <= rounds; ++k, h += U * kBktThreads) {
+        Regs n[U];
+        if (k < rounds) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) fetch(h + (U + u) * kBktThreads, n[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) store(h + u * kBktThreads, r[u]);
-#pragma unroll
-            for (int u = 0; u < U; ++u) r[u] = n[u];
+            for (int u = 0; u < U; ++u) fetch(h + (U + u) * kBktThreads, n[u]);
         }
-        for (; h < end; h += kBktThreads) {
-            fetch(h, r[0]);
-            store(h, r[0]);
-        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) store(h + u * kBktThreads, r[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = n[u];
+    }
+    for (; h < end; h += kBktThreads) {
+        fetch(h, r[0]);
+        store(h, r[0]);
     }
 }
 
@@ -897,10 +894,10 @@ void run_buckets(const DevCsr &M, const MT *vals, const VT *in, Epi e,
         return;
     }
     Acc *prod = (Acc *)K.prod;
-    if (K.ngroups > 0)
-        hipLaunchKernelGGL((k_bkt_push<MT, VT, Acc>), dim3(K.ngroups),
-                           dim3(kBktThreads), 0, s, K.items, K.first, K.col,
-                           vals, K.dest, in, M.cols, prod);
+    if (K.nitems > 0)
+        hipLaunchKernelGGL((k_bkt_push<MT, VT, Acc>), dim3(K.nitems),
+                           dim3(kBktThreads), 0, s, K.items, K.col, vals, K.dest,
+                           in, M.cols, K.width, prod);
     run_sum<Acc>(M, PushedUnits<Acc>{prod}, e, s);
 }
 

@@ -409,7 +409,6 @@ void free_csr(DevCsr &M) {
     }
     if (DevBuckets *k = M.bkt) {
         dfree(k->items);
-        dfree(k->first);
         dfree(k->buckets);
         dfree(k->split);
         dfree(k->col);
@@ -589,8 +588,8 @@ DevBuckets *upload_buckets(const HostBuckets &H, bool f64, bool force) {
         K->gcol = upload(H.gcol);
     } else {
         K->items = upload(H.items);
-        K->first = upload(H.first);
-        K->ngroups = (int)H.first.size() - 1;
+        K->nitems = (int)H.items.size();
+        K->width = H.width;
         K->col = upload(H.col);
         K->dest = upload(H.dest);
     }

@@ -103,19 +103,18 @@ int main() {
             std::vector<double> prod(4 * B.quads, NAN), y(c.m, NAN);
             std::vector<char> written(B.quads, 0), seen(nnz, 0);
             int64_t covered = 0;
-            CHECK(!B.first.empty() && B.first[0] == 0 &&
-                  B.first.back() == (int32_t)B.items.size() &&
-                  std::is_sorted(B.first.begin(), B.first.end()));
+            CHECK(B.width > 0 && B.width <= kBktCols && (B.width % 4 == 0 || B.width == kBktCols));
             for (const PushItem &it : B.items) {
+                if (it.q0 == it.q1) continue;
                 CHECK(it.q0 >= 0 && it.q0 < it.q1 && it.q1 <= B.quads);
-                const int64_t c0 = (int64_t)it.cb * kBktCols;
+                const int64_t c0 = (int64_t)it.cb * B.width;
                 CHECK(it.cb >= 0 && c0 < c.n);
                 for (int64_t q = it.q0; q < it.q1; ++q, ++covered) {
                     CHECK(B.dest[q] >= 0 && B.dest[q] < B.quads && !written[B.dest[q]]);
                     written[B.dest[q]] = 1;
                     for (int i = 0; i < 4; ++i) {
                         const int64_t e = 4 * q + i, p = B.src[e];
-                        CHECK(B.col[e] < kBktCols && p < nnz);
+                        CHECK(B.col[e] < B.width && p < nnz);
                         if (p >= 0) {
                             CHECK(!seen[p] && A.ci[p] == c0 + B.col[e]);
                             seen[p] = 1;

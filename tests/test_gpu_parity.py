@@ -123,11 +123,11 @@ LAYOUT_KINDS = {"tiles": {"layout_a": 1, "layout_at": 1},
 def test_bucketed_spmv_bitwise_on_integers(Solver, kind):
     """Products through tiles and through pushed products equal numpy exactly
     on integers, in both precisions: rows from empty to longer than a bucket
-    (16,384), column counts on both sides of a column block, and buckets of one
+    (16,384), column counts on both sides of a column block (20,000), and buckets of one
     row, of fewer rows than lanes and of more."""
     rng = np.random.default_rng(5)
     for m, n, lens in ((7, 40_000, [0, 1, 16_384, 16_385, 40_000, 0, 3]),
-                       (3, 16_384, [5, 16_384, 16_383]), (4, 16_385, [16_385, 1, 0, 9]),
+                       (3, 20_000, [5, 16_384, 16_383]), (4, 20_001, [16_385, 1, 0, 9]),
                        (30_000, 900, rng.integers(0, 4, 30_000)),
                        (2_000, 33_000, rng.integers(60, 140, 2_000)),
                        (1, 1, [1])):
