@@ -569,34 +569,38 @@ HostBins build_panel_blocks(int64_t rows, const int64_t *srp, int P, int tile,
     return out;
 }
 
+constexpr int64_t kBktCus = 256;
+
 // Cost of rows [r0, r1) to a bucket: its nonzeros, and the epilogue's operands
 // of a row (40 to 56 bytes) as three more.
 static int64_t bucket_cost(const int64_t *rp, int64_t r0, int64_t r1) {
     return rp[r1] - rp[r0] + 3 * (r1 - r0);
 }
 
-// Cost per bucket: equal shares of whole rounds of one bucket on each CU.
-static int64_t bucket_fill(int64_t cost, int64_t nnz) {
-    constexpr int64_t kCus = 256, most = 2 * (int64_t)kBktCap;
-    const int64_t nr = std::max<int64_t>(
-        1, std::max((nnz + kCus * kBktCap - 1) / (kCus * kBktCap),
-                    (cost + kCus * most - 1) / (kCus * most)));
-    return (int64_t)(1.01 * (double)cost / (double)(kCus * nr)) + 64;
+// Rounds of one bucket of at most `cap` nonzeros on each CU.
+static int64_t bucket_rounds(int64_t cost, int64_t nnz, int64_t cap) {
+    const int64_t round = kBktCus * cap;
+    return std::max<int64_t>(1, std::max((nnz + round - 1) / round, (cost + 2 * round - 1) / (2 * round)));
+}
+
+// Cost per bucket: equal shares of whole rounds.
+static int64_t bucket_fill(int64_t cost, int64_t rounds) {
+    return (int64_t)(1.01 * (double)cost / (double)(kBktCus * rounds)) + 64;
 }
 
 // Consecutive rows of [row0, row1) packed into buckets of about cost `fill`
-// and at most kBktCap nonzeros; a longer row is cut into parts.  skip_empty:
+// and at most `cap` nonzeros; a longer row is cut into parts.  skip_empty:
 // no bucket starts at an empty row.
 static void pack_buckets(HostBuckets &B, int64_t row0, int64_t row1,
-                         const int64_t *rp, int64_t fill, bool skip_empty) {
+                         const int64_t *rp, int64_t fill, int64_t cap, bool skip_empty) {
     for (int64_t r = row0; r < row1;) {
         const int64_t len = rp[r + 1] - rp[r];
         if (skip_empty && len == 0) {
             ++r;
             continue;
         }
-        if (len > kBktCap) {
-            const int np = (int)((len + kBktCap - 1) / kBktCap);
+        if (len > cap) {
+            const int np = (int)((len + cap - 1) / cap);
             const int64_t chunk = (len + np - 1) / np;
             const int slot = (int)B.splits.size();
             for (int q = 0; q < np; ++q) {
@@ -612,7 +616,7 @@ static void pack_buckets(HostBuckets &B, int64_t row0, int64_t row1,
         // G lanes (a power of two, at most 64) sum each of R rows: no row may
         // keep its lanes longer than 64 steps because of many short ones
         int64_t r1 = r + 1, longest = len;
-        while (r1 < row1 && rp[r1 + 1] - rp[r] <= kBktCap &&
+        while (r1 < row1 && rp[r1 + 1] - rp[r] <= cap &&
                bucket_cost(rp, r, r1 + 1) <= fill) {
             const int64_t mx = std::max(longest, rp[r1 + 1] - rp[r1]);
             const int64_t G = std::min<int64_t>(64, kBktThreads / (r1 + 1 - r));
@@ -665,14 +669,13 @@ HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
                        const int32_t *ci, bool force) {
     HostBuckets B;
     const int64_t nnz = rp[rows], cost = bucket_cost(rp, 0, rows);
-    constexpr int64_t kCus = 256;
     int64_t ncb = 1;
-    while (ncb * kBktCols < cols) ncb = ncb < kCus ? 2 * ncb : ncb + kCus;
+    while (ncb * kBktCols < cols) ncb = ncb < kBktCus ? 2 * ncb : ncb + kBktCus;
     // (whole 16-byte units of the vector)
     B.width = (int)std::min<int64_t>(kBktCols, ((cols + ncb - 1) / ncb + 3) / 4 * 4);
     ncb = (cols + B.width - 1) / B.width;
-    const int64_t fill = bucket_fill(cost, nnz);
-    pack_buckets(B, 0, rows, rp, fill, false);
+    const int64_t fill = bucket_fill(cost, bucket_rounds(cost, nnz, kBktCap));
+    pack_buckets(B, 0, rows, rp, fill, kBktCap, false);
     const int64_t nb = (int64_t)B.buckets.size();
     B.fragmented = nb > 2 * (cost / fill) + 64;
     if (B.fragmented && !force) return B;
@@ -731,7 +734,7 @@ HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
     // round-robin) takes neighbouring ones, so that runs that share lines of
     // the products are written through one L2
     constexpr int64_t kXcd = 8;
-    const int64_t want = kCus * std::max<int64_t>(1, std::min<int64_t>(4, B.quads / (kCus * 8192)));
+    const int64_t want = kBktCus * std::max<int64_t>(1, std::min<int64_t>(4, B.quads / (kBktCus * 8192)));
     auto count = [&](int64_t S) {
         int64_t n = 0;
         for (int64_t k = 0; k < ncb; ++k) n += (cq[k + 1] - cq[k] + S - 1) / S;
@@ -758,7 +761,9 @@ HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
 
 // Tiles.  A tile's nonzeros are kept in column order, so that neighbouring
 // lanes gather from neighbouring lines; its products go to their CSR positions
-// in LDS.  Within a group of 64 quads lane l's quad holds the entries l,
+// in LDS.  Position and column share 32 bits, the column relative to a base
+// per group of 64 quads (48 bits: 9M nonzeros 53 us a step against 46, FP32 36
+// against 26, 16,384 nonzeros a tile included).  Within a group of 64 quads lane l's quad holds the entries l,
 // l + 64, l + 128 and l + 192 of that order: each of the four gathers of a
 // wave then covers 64 neighbours.  Tiles of panel p are dealt to the XCDs x
 // with x % P == p (r0 == r1 pads queues of unequal length).
@@ -767,46 +772,67 @@ HostBuckets build_tiles(int64_t rows, const int64_t *rp, const int32_t *ci,
     constexpr int kXcd = 8;
     HostBuckets B;
     const int64_t nnz = rp[P * rows], cost = bucket_cost(rp, 0, P * rows);
-    const int64_t fill = bucket_fill(cost, nnz);
     std::vector<int64_t> first;
-    for (int p = 0; p < P; ++p) {
-        first.push_back((int64_t)B.buckets.size());
-        pack_buckets(B, p * rows, (p + 1) * rows, rp, fill, P > 1);
+    int64_t fill = 0, nb = 0;
+    // one round more where long rows fill more buckets than the rounds hold
+    for (int64_t nr = bucket_rounds(cost, nnz, kTileCap), k = 0; k < 2; ++k) {
+        fill = bucket_fill(cost, nr + k);
+        B = HostBuckets();
+        first.clear();
+        for (int p = 0; p < P; ++p) {
+            first.push_back((int64_t)B.buckets.size());
+            pack_buckets(B, p * rows, (p + 1) * rows, rp, fill, kTileCap, P > 1);
+        }
+        nb = (int64_t)B.buckets.size();
+        first.push_back(nb);
+        if (nb <= kBktCus * (nr + k)) break;
     }
-    first.push_back((int64_t)B.buckets.size());
-    const int64_t nb = (int64_t)B.buckets.size();
     B.fragmented = nb > 2 * (cost / fill) + 64;
     if (B.fragmented && !force) return B;
+    // groups of 64 quads: a full one, one that the next column's offset does
+    // not fit, or the last
+    constexpr int64_t kGroup = 256, kSpan = (int64_t)1 << (32 - kTilePos);
+    over_buckets(nb, nnz, [&](int64_t b0, int64_t b1) {
+        for (int64_t b = b0; b < b1; ++b) {
+            Bucket &K = B.buckets[b];
+            const auto mm = std::minmax_element(ci + K.p0, ci + K.p1);
+            K.q1 = K.p0 == K.p1 ? 0 : (int32_t)(64 * ((K.p1 - K.p0) / kGroup + (*mm.second - *mm.first) / kSpan + 1));
+        }
+    });
     int64_t q = 0;
     for (auto &b : B.buckets) {
         b.q0 = (int32_t)q;
-        q += (b.p1 - b.p0 + 3) / 4;
-        b.q1 = (int32_t)q;
+        q += b.q1;
     }
     B.quads = q;
-    B.gcol.assign((size_t)(4 * q), 0);
-    B.pos.assign((size_t)(4 * q), (uint16_t)kBktCap);
+    B.word.assign((size_t)(4 * q), 0);
+    B.base.assign((size_t)(q / 64), 0);
     B.src.assign((size_t)(4 * q), -1);
     over_buckets(nb, nnz, [&](int64_t b0, int64_t b1) {
         std::vector<uint64_t> key, tmp;
         for (int64_t b = b0; b < b1; ++b) {
-            const Bucket &K = B.buckets[b];
-            const int64_t nz = K.p1 - K.p0, nq = K.q1 - K.q0;
+            Bucket &K = B.buckets[b];
+            const int64_t nz = K.p1 - K.p0;
             key.resize((size_t)nz);
             for (int64_t t = 0; t < nz; ++t)
                 key[t] = (uint64_t)(uint32_t)ci[K.p0 + t] << 32 | (uint64_t)t;
             sort_high(key, tmp);
-            for (int64_t t = 0; t < 4 * nq; ++t) {
-                // entry t of the order: group g of up to 64 quads
-                const int64_t g = t / 256, L = std::min<int64_t>(64, nq - 64 * g);
-                const int64_t i = t - 256 * g;
-                const int64_t o = 4 * (K.q0 + 64 * g + i % L) + i / L;
-                const uint64_t e = key[std::min(t, nz - 1)];
-                B.gcol[o] = (int32_t)(e >> 32);
-                if (t < nz) {
-                    B.src[o] = (int32_t)(K.p0 + (int64_t)(e & 0xffffffffu));
-                    B.pos[o] = (uint16_t)(e & 0xffffffffu);
+            K.q1 = K.q0;
+            for (int64_t t = 0; t < nz;) {
+                const int64_t c0 = (int64_t)(key[t] >> 32);
+                int64_t n = 1;
+                while (n < kGroup && t + n < nz && (int64_t)(key[t + n] >> 32) - c0 < kSpan) ++n;
+                // neighbours in the order on neighbouring lanes (L of them)
+                const int64_t L = t + n < nz ? 64 : (n + 3) / 4;
+                for (int64_t i = 0; i < 4 * L; ++i) {
+                    const uint64_t e = key[t + std::min(i, n - 1)];
+                    const int64_t o = 4 * (K.q1 + i % L) + i / L, p = (int64_t)(e & 0xffffffffu);
+                    B.word[o] = (int32_t)((uint32_t)((int64_t)(e >> 32) - c0) << kTilePos | (uint32_t)p);
+                    B.src[o] = (int32_t)(K.p0 + p);
                 }
+                B.base[K.q1 / 64] = (int32_t)c0;
+                K.q1 += (int32_t)L;
+                t += n;
             }
         }
     });
@@ -875,25 +901,29 @@ HostSmall build_small(int64_t rows, int64_t cols, const int64_t *rp,
 // products costs 17 (FP64) or 9 (FP32) more bytes per nonzero and a second
 // launch, but gathers from LDS only; its runs shorten as the columns grow.
 // Measured, us a step, rows | tiles | push (FP64; FP32):
-//   power-law primal, 9.4M nonzeros, 1.6 MB:  64 | 54 | 66;  51 | 38 | 41
-//   ... dual, 8 MB in 4 panels, 47 a row:     61 | 53 | 64;  43 | 39 | 45
-//   1M x 400k dual, 8M, 8 MB, 20 a row:       72 | 62 | 55;  54 | 46 | 38
-//   ... primal, 3.2 MB:                       65 | 57 | 58;  51 | 44 | 36
-//   multicommodity primal, 14.6M, 10.8 MB:   133 | 118 | 119;  98 | 79 | 69
-//   ... dual, 40 MB in 8 panels:             143 | 142 |  99; 100 | 93 | 58
-//   840k-column one, dual, 2.4M, 6.7 MB:      30 | 26 | 26;  21 | 21 | 18
-//   ... primal, 1.9 MB:                       24 | 20 | 27;  21 | 15 | 19
-//   600k x 200k dual, 2.4M, 4.8 MB:           28 | 22 | 25;  21 | 18 | 17
-//   power-law 300k dual, 2.8M, 2.4 MB:        21 | 17 | 25;  17 | 14 | 17
-//   400k x 160k dual, 1.2M, 3.2 MB:           16 | 15 | 19;  14 | 12 | 14
-//   2M x 1M dual, 24M, 16 MB:                199 | 178 | 147; 152 | 134 | 84
+//   power-law primal, 9.4M nonzeros, 1.6 MB:  65 | 51 | 65;  51 | 31 | 40
+//   ... dual, 8 MB in 4 panels, 47 a row:     63 | 45 | 65;  47 | 29 | 40
+//   1M x 400k primal, 8M, 3.2 MB:             65 | 50 | 56;  51 | 32 | 35
+//   ... dual, 8 MB, 20 a row:                 72 | 55 | 55;  54 | 37 | 34
+//   700k x 600k primal, 9.8M, 4.8 MB:         83 | 59 | 65;  62 | 38 | 41
+//   ... dual, 5.6 MB:                         89 | 65 | 67;  63 | 41 | 40
+//   multicommodity primal, 14.6M, 10.8 MB:   134 | 117 | 120;  98 | 73 | 71
+//   ... dual, 40 MB in 8 panels:             145 | 141 | 100; 100 | 98 | 58
+//   840k-column one, dual, 2.4M, 6.7 MB:      30 | 25 | 26;  21 | 19 | 18
+//   ... primal, 1.9 MB:                       23 | 19 | 28;  21 | 14 | 19
+//   600k x 200k dual, 2.4M, 4.8 MB:           28 | 21 | 26;  21 | 17 | 18
+//   power-law 300k dual, 2.8M, 2.4 MB:        21 | 16 | 26;  18 | 13 | 19
+//   400k x 160k dual, 1.2M, 3.2 MB:           16 | 14 | 18;  14 | 12 | 13
+//   2M x 1M dual, 24M, 16 MB:                199 | 165 | 148; 151 | 115 | 83
+//   ... primal, 8 MB:                        200 | 166 | 143; 151 | 118 | 83
 //   coupled dual, 55M, 80 MB in 8 panels:    708 | 563 | 420; 431 | 406 | 212
 //   ... 110M, 160 MB:                       1764 |  -  |  985; 1260 | - | 547
+// (the last two with tiles of 16,384 nonzeros and 48-bit entries).
 int choose_layout(int64_t rows, int64_t cols, int64_t nnz, int P) {
     constexpr double kMiB = 1048576.0;
     const double panel = 8.0 * (double)cols / P;
     if (nnz < kTileMin32) return LAYOUT_ROWS;
-    if (panel <= (nnz < 6000000 ? 6.0 : 2.25) * kMiB &&
+    if (panel <= (P == 1 || nnz < 6000000 ? 5.5 : 2.25) * kMiB &&
         (P == 1 || nnz >= 8 * (int64_t)P * rows))
         return LAYOUT_TILES;
     // runs of eight nonzeros or more (41M columns)

@@ -80,13 +80,18 @@ HostBins build_panel_blocks(int64_t rows, const int64_t *srp, int P, int tile,
 // columns, its part of the vector in LDS, and writes the products to the
 // buckets of their rows.
 enum { LAYOUT_CHOOSE = -1, LAYOUT_ROWS = 0, LAYOUT_TILES = 1, LAYOUT_PUSH = 2 };
-constexpr int kBktCap = 1 << 14;      // most nonzeros of a bucket (128 KB of FP64)
+constexpr int kBktCap = 1 << 14;      // most nonzeros of a pushed bucket (128 KB of FP64)
+constexpr int kTileCap = 19200;       // ... of a tile (150 KB)
+constexpr int kTilePos = 15;          // a tile's nonzero in 32 bits: its CSR position
+                                      // in the tile, and in the bits above its column
+                                      // less the base of its group of 64 quads
 constexpr int kBktCols = 20000;       // most columns of a block (160 KB of FP64)
 constexpr int kBktThreads = 1024;
 // Fewest nonzeros that run in tiles, FP64 and FP32.  Measured, us an iteration
-// in row blocks | tiles, by nonzeros: FP64 55k 8.5 | 9.3, 480k 11.4 | 11.9,
-// 800k 17.0 | 15.8; FP32 55k 9.6 | 8.4, 300k 11.3 | 9.7, 800k 15.7 | 12.6.
-constexpr int64_t kTileMin64 = 700000, kTileMin32 = 50000;
+// in row blocks | tiles, by nonzeros: FP64 55k 8.7 | 9.4, 480k 11.2 | 11.7,
+// 640k 13.6 | 12.7, 800k 17.0 | 14.6; FP32 55k 9.8 | 8.4, 300k 11.5 | 9.6,
+// 800k 15.8 | 12.0.
+constexpr int64_t kTileMin64 = 550000, kTileMin32 = 50000;
 // Quads [q0, q1) of the push order, all of column block cb (q0 == q1: padding).
 struct PushItem {
     int32_t cb, q0, q1, pad;
@@ -109,7 +114,9 @@ struct HostBuckets {
                                       // (kBktCap: padding)
     std::vector<int32_t> src;         // 4 * quads: position in the CSR (-1: padding)
     std::vector<int32_t> dest;        // quads: quad of the products
-    std::vector<int32_t> gcol;        // tiles: 4 * quads columns
+    std::vector<int32_t> word;        // tiles: 4 * quads positions and columns
+                                      // (padding: the entry before it again)
+    std::vector<int32_t> base;        // tiles: quads / 64 bases
 };
 // Unless forced, both stop at a fragmented matrix.
 HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
@@ -129,7 +136,7 @@ struct DevBuckets {
     SplitRow *split = nullptr;
     uint16_t *col = nullptr, *pos = nullptr;
     int32_t *src = nullptr, *dest = nullptr;
-    int32_t *gcol = nullptr;          // tiles (no push pass)
+    int32_t *word = nullptr, *base = nullptr;   // tiles (no push pass)
     double *v64 = nullptr;            // scaled values in the order of src
     float *v32 = nullptr;
     void *prod = nullptr;             // products of either precision, shared by

@@ -661,65 +661,77 @@ __global__ __launch_bounds__(kBktThreads) void k_bkt_push(
 }
 
 // Where a bucket's products come from: fetch() issues the streamed loads of
-// one unit, mul() forms its products.
+// one unit, mul() forms its products, place() has their CSR positions.
 template <typename Acc>
 struct PushedUnits {                  // written by the push pass
-    static constexpr int W = UnitOf<Acc>::W;
+    static constexpr int W = UnitOf<Acc>::W, kCap = kBktCap;
     static constexpr int kWaves = sizeof(Acc) == 4 ? 8 : 4;   // per SIMD
+    static constexpr int kDepth = kCap / W / kBktThreads;     // units per lane
+    using H = typename UnitOf<Acc>::H;
     const Acc *prod;
+    const uint16_t *pos;
     struct Regs {
         typename UnitOf<Acc>::V a;
+        H j;
     };
     __device__ __forceinline__ void fetch(int64_t p, Regs &r) const {
         r.a = __builtin_nontemporal_load((const typename UnitOf<Acc>::V *)prod + p);
+        r.j = __builtin_nontemporal_load((const H *)pos + p);
     }
     __device__ __forceinline__ Acc mul(const Regs &r, int i) const { return r.a[i]; }
+    __device__ __forceinline__ int place(const Regs &r, int i) const { return r.j[i]; }
 };
+// Values times gathers of the vector.  Bound by streaming 12 (FP64) or 8 (FP32)
+// bytes a nonzero and by the lines the gathers bring from L2 (0.5 a nonzero on
+// 200,000 FP64 columns): 9M nonzeros in random columns take 46 us, in
+// neighbouring ones 33; FP32 26 and 19.  Two FP32 tiles fit in a CU's LDS, and
+// one's stream overlaps the other's gathers, if few registers hold loads
+// ahead: power-law primal 38 us a step with one workgroup per CU, 36 with two
+// and three units ahead, 31 with one.  In FP64 the depth makes no difference.
 template <typename MT, typename VT, typename Acc>
-struct GatheredUnits {                // values times gathers of the vector
-    static constexpr int W = 4;       // (a wave gathers 64 neighbours at a time)
-    static constexpr int kWaves = 4;
-    const int32_t *col;
+struct GatheredUnits {
+    static constexpr int W = 4, kCap = kTileCap;   // (a wave gathers 64 neighbours at a time)
+    static constexpr int kWaves = sizeof(Acc) == 4 ? 8 : 4;
+    static constexpr int kDepth = sizeof(Acc) == 4 ? 1 : 3;
+    const int32_t *word, *base;
     const MT *val;
     const VT *x;
     struct Regs {
         MT a[4];
-        int j[4];
+        int w[4], b;
     };
     __device__ __forceinline__ void fetch(int64_t p, Regs &r) const {
-        ld4<false>(col + 4 * p, r.j);
+        ld4<false>(word + 4 * p, r.w);
         ld4<false>(val + 4 * p, r.a);
+        // (a wave's units lie in one group)
+        r.b = base[__builtin_amdgcn_readfirstlane((int)(p >> 6))];
     }
     __device__ __forceinline__ Acc mul(const Regs &r, int i) const {
-        return (Acc)r.a[i] * (Acc)x[r.j[i]];
+        return (Acc)r.a[i] * (Acc)x[r.b + (int)((unsigned)r.w[i] >> kTilePos)];
+    }
+    __device__ __forceinline__ int place(const Regs &r, int i) const {
+        return r.w[i] & ((1 << kTilePos) - 1);
     }
 };
 
 // Streamed loads of the units h, h + NT, ... (U of them; past the end the last
 // one again, so that no branch separates them), and their products to their
-// places in LDS (past the end to the spare slot).
+// places in LDS.
 template <int U, class Units>
 struct UnitRegs {
     typename Units::Regs a[U];
-    unsigned short __attribute__((ext_vector_type(Units::W))) j[U];
 };
 template <int U, class Units>
-__device__ __forceinline__ void bkt_fetch(const Units &units,
-                                          const uint16_t *__restrict__ pos,
-                                          int64_t h, int64_t end,
-                                          UnitRegs<U, Units> &r) {
-    using H = unsigned short __attribute__((ext_vector_type(Units::W)));
+__device__ __forceinline__ void bkt_fetch(const Units &units, int64_t h,
+                                          int64_t end, UnitRegs<U, Units> &r) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        int64_t p = h + u * kBktThreads;
-        p = p < end ? p : end - 1;
-        units.fetch(p, r.a[u]);
-        r.j[u] = __builtin_nontemporal_load((const H *)pos + p);
+        const int64_t p = h + u * kBktThreads;
+        units.fetch(p < end ? p : end - 1, r.a[u]);
     }
 }
 template <int U, class Units, typename Acc>
-__device__ __forceinline__ void bkt_store(const Units &units, int64_t h,
-                                          int64_t end,
+__device__ __forceinline__ void bkt_store(const Units &units,
                                           const UnitRegs<U, Units> &r,
                                           Acc *__restrict__ s_prod) {
     constexpr int W = Units::W;
@@ -731,24 +743,22 @@ __device__ __forceinline__ void bkt_store(const Units &units, int64_t h,
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int i = 0; i < W; ++i)
-            s_prod[h + u * kBktThreads < end ? (int)r.j[u][i] : kBktCap] = o[u][i];
+        for (int i = 0; i < W; ++i) s_prod[units.place(r.a[u], i)] = o[u][i];
 }
 // All units [h - tid, end) of a bucket, at most U per lane at a time and no
 // more than there are.
 template <int U, class Units, typename Acc>
 __device__ __forceinline__ void bkt_fill(const Units &units,
-                                         const uint16_t *__restrict__ pos,
                                          int64_t h, int64_t end,
                                          Acc *__restrict__ s_prod) {
     const int64_t tid = threadIdx.x;
     for (; end - (h - tid) > (U - 1) * kBktThreads; h += U * kBktThreads) {
         UnitRegs<U, Units> r;
-        bkt_fetch(units, pos, h, end, r);
-        bkt_store(units, h, end, r, s_prod);
+        bkt_fetch(units, h, end, r);
+        bkt_store(units, r, s_prod);
     }
     if constexpr (U > 1)
-        if (h - tid < end) bkt_fill<U - 1>(units, pos, h, end, s_prod);
+        if (h - tid < end) bkt_fill<U - 1>(units, h, end, s_prod);
 }
 
 // Sum pass: a bucket's products go to their CSR positions in LDS, then a
@@ -759,13 +769,12 @@ __device__ __forceinline__ void bkt_fill(const Units &units,
 template <typename Acc, bool LOOP, class Units, class Epi>
 __global__ __launch_bounds__(kBktThreads, Units::kWaves) void k_bkt_sum(
     const Bucket *__restrict__ buckets, int nbuckets,
-    const int32_t *__restrict__ rp, const uint16_t *__restrict__ pos,
-    Units units, Acc *__restrict__ part, int maxparts, Epi epi_in) {
+    const int32_t *__restrict__ rp, Units units, Acc *__restrict__ part, int maxparts, Epi epi_in) {
     constexpr int NT = kBktThreads;
-    __shared__ Acc s_prod[kBktCap + 1];
+    __shared__ Acc s_prod[Units::kCap + 1];
     __shared__ Acc s_sum[NT];
     constexpr int F = 4 / Units::W, KP = 3;
-    constexpr int U = kBktCap / Units::W / NT;
+    constexpr int U = Units::kDepth;
     Epi epi = epi_in;
     int t = blockIdx.x;
     Bucket b = buckets[t];
@@ -773,7 +782,7 @@ __global__ __launch_bounds__(kBktThreads, Units::kWaves) void k_bkt_sum(
     const int tid = threadIdx.x;
     UnitRegs<LOOP ? U : 1, Units> regs;
     int64_t h = (int64_t)F * b.q0 + tid, end = (int64_t)F * b.q1;
-    if (LOOP && b.q0 < b.q1) bkt_fetch(units, pos, h, end, regs);
+    if (LOOP && b.q0 < b.q1) bkt_fetch(units, h, end, regs);
     for (;;) {
         const bool more = LOOP && t + (int)gridDim.x < nbuckets;
         t = more ? t + (int)gridDim.x : t;
@@ -800,15 +809,15 @@ __global__ __launch_bounds__(kBktThreads, Units::kWaves) void k_bkt_sum(
         }
         if constexpr (LOOP) {
             if (b.q0 < b.q1) {
-                bkt_store(units, h, end, regs, s_prod);
+                bkt_store(units, regs, s_prod);
                 // units beyond the registers (the padding of short runs)
-                bkt_fill<1>(units, pos, h + U * NT, end, s_prod);
+                bkt_fill<1>(units, h + U * NT, end, s_prod);
             }
             h = (int64_t)F * nb.q0 + tid;
             end = (int64_t)F * nb.q1;
-            if (more && nb.q0 < nb.q1) bkt_fetch(units, pos, h, end, regs);
+            if (more && nb.q0 < nb.q1) bkt_fetch(units, h, end, regs);
         } else {
-            bkt_fill<U>(units, pos, h, end, s_prod);
+            bkt_fill<U>(units, h, end, s_prod);
         }
         __syncthreads();
         if (R == 1) {
@@ -877,7 +886,7 @@ void run_sum(const DevCsr &M, const Units &units, Epi e, hipStream_t s) {
         hipLaunchKernelGGL((k_bkt_sum<Acc, loop, Units, Epi>),
                            dim3(loop && K.nbuckets > kCus ? kCus : K.nbuckets),
                            dim3(kBktThreads), 0, s, K.buckets, K.nbuckets, M.rp,
-                           K.pos, units, part, K.maxparts, e);
+                           units, part, K.maxparts, e);
     if (K.nsplit > 0)
         hipLaunchKernelGGL((k_split_fix<Acc, Epi>),
                            dim3((K.nsplit + kFixThreads - 1) / kFixThreads),
@@ -889,8 +898,8 @@ template <typename Acc, typename MT, typename VT, class Epi>
 void run_buckets(const DevCsr &M, const MT *vals, const VT *in, Epi e,
                  hipStream_t s) {
     const DevBuckets &K = *M.bkt;
-    if (K.gcol) {
-        run_sum<Acc>(M, GatheredUnits<MT, VT, Acc>{K.gcol, vals, in}, e, s);
+    if (K.word) {
+        run_sum<Acc>(M, GatheredUnits<MT, VT, Acc>{K.word, K.base, vals, in}, e, s);
         return;
     }
     Acc *prod = (Acc *)K.prod;
@@ -898,7 +907,7 @@ void run_buckets(const DevCsr &M, const MT *vals, const VT *in, Epi e,
         hipLaunchKernelGGL((k_bkt_push<MT, VT, Acc>), dim3(K.nitems),
                            dim3(kBktThreads), 0, s, K.items, K.col, vals, K.dest,
                            in, M.cols, K.width, prod);
-    run_sum<Acc>(M, PushedUnits<Acc>{prod}, e, s);
+    run_sum<Acc>(M, PushedUnits<Acc>{prod, K.pos}, e, s);
 }
 
 template <typename Acc, int TILE, class Elem, class Epi>

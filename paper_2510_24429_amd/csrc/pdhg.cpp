@@ -415,7 +415,8 @@ void free_csr(DevCsr &M) {
         dfree(k->pos);
         dfree(k->src);
         dfree(k->dest);
-        dfree(k->gcol);
+        dfree(k->word);
+        dfree(k->base);
         dfree(k->v64);
         dfree(k->v32);
         dfree(k->part);
@@ -579,14 +580,15 @@ DevBuckets *upload_buckets(const HostBuckets &H, bool f64, bool force) {
     K->maxparts = H.maxparts;
     K->buckets = upload(H.buckets);
     K->split = upload(H.splits);
-    K->pos = upload(H.pos);
     K->src = upload(H.src);
     K->v64 = dmalloc<double>(4 * K->quads);
     K->v32 = dmalloc<float>(4 * K->quads);
     K->part = dmalloc<double>((int64_t)K->nsplit * K->maxparts);
-    if (!H.gcol.empty()) {
-        K->gcol = upload(H.gcol);
+    if (!H.word.empty()) {
+        K->word = upload(H.word);
+        K->base = upload(H.base);
     } else {
+        K->pos = upload(H.pos);
         K->items = upload(H.items);
         K->nitems = (int)H.items.size();
         K->width = H.width;

@@ -87,7 +87,7 @@ int main() {
     };
     for (Case c : {Case{1, 1, 1, 0}, Case{5, 3, 0, 0}, Case{3000, 40000, 7, 0},
                    Case{40000, 3000, 3, 0}, Case{200, 100000, 300, 1},
-                   Case{100000, 50000, 2, 2}, Case{1, 50000, 40000, 0},
+                   Case{100000, 50000, 2, 2}, Case{1, 50000, 40000, 0}, Case{2, 700000, 600, 0},
                    Case{30000, kBktCols, 9, 1}, Case{30000, kBktCols + 1, 0.3, 0},
                    Case{20000, 70001, 3, 3}, Case{300000, 400000, 12, 0},
                    Case{2000, 300 * kBktCols, 100, 0}}) {
@@ -151,24 +151,21 @@ int main() {
             const HostBuckets B = build_tiles(c.m, S.rp.data(), S.ci.data(), P, true);
             std::vector<double> part(B.splits.size() * B.maxparts, NAN), ys(P * c.m, NAN), y(c.m, 0.0);
             std::vector<char> seen(nnz, 0);
-            CHECK((int64_t)B.gcol.size() == 4 * B.quads && B.pos.size() == B.gcol.size() &&
-                  B.src.size() == B.gcol.size());
+            CHECK((int64_t)B.word.size() == 4 * B.quads && B.src.size() == B.word.size() &&
+                  64 * (int64_t)B.base.size() == B.quads);
             for (size_t w = 0; w < B.buckets.size(); ++w) {
                 const Bucket &b = B.buckets[w];
                 if (b.r0 == b.r1) continue;
                 CHECK(b.r0 / c.m == (b.r1 - 1) / c.m && (int)(w % 8) % P == b.r0 / c.m);
-                CHECK(b.p1 - b.p0 <= kBktCap && b.q0 >= 0 && b.q0 <= b.q1 && b.q1 <= B.quads);
-                std::vector<double> s(kBktCap + 1, NAN);
+                CHECK(b.p1 - b.p0 <= kTileCap && b.q0 >= 0 && b.q0 % 64 == 0 && b.q0 <= b.q1 && b.q1 <= B.quads);
+                std::vector<double> s(kTileCap + 1, NAN);
                 for (int64_t e = 4 * (int64_t)b.q0; e < 4 * (int64_t)b.q1; ++e) {
                     const int32_t p = B.src[e];
-                    CHECK(B.gcol[e] >= 0 && B.gcol[e] < c.n);
-                    if (p >= 0) {
-                        CHECK(!seen[p] && S.ci[p] == B.gcol[e] && B.pos[e] == p - b.p0);
-                        seen[p] = 1;
-                    } else {
-                        CHECK(B.pos[e] == kBktCap);
-                    }
-                    s[B.pos[e]] = p < 0 ? 0.0 : v[S.src[p]] * x[B.gcol[e]];
+                    const int64_t pos = B.word[e] & ((1 << kTilePos) - 1),
+                                  col = B.base[e / 256] + (int64_t)((uint32_t)B.word[e] >> kTilePos);
+                    CHECK(p >= 0 && p < nnz && S.ci[p] == col && pos == p - b.p0);
+                    seen[p] = 1;
+                    s[pos] = v[S.src[p]] * x[col];
                 }
                 sum_rows(B, b, s, S.rp, part, ys);
             }

@@ -18,7 +18,7 @@ def test_bucket_plans_give_the_csr_product(tmp_path):
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-2000:]
     lines = r.stdout.strip().splitlines()
-    assert lines[-1] == "done" and len(lines) == 12 * 4 + 8 + 1
+    assert lines[-1] == "done" and len(lines) == 13 * 4 + 8 + 1
     # rows of 4,500 entries among rows of 3 do not fill buckets (the library
     # keeps row blocks there); even rows do
     by = [dict(zip(ln.split()[1::2], ln.split()[2::2])) | {"layout": ln.split()[0]}

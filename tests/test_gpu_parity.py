@@ -123,11 +123,13 @@ LAYOUT_KINDS = {"tiles": {"layout_a": 1, "layout_at": 1},
 def test_bucketed_spmv_bitwise_on_integers(Solver, kind):
     """Products through tiles and through pushed products equal numpy exactly
     on integers, in both precisions: rows from empty to longer than a bucket
-    (16,384), column counts on both sides of a column block (20,000), and buckets of one
-    row, of fewer rows than lanes and of more."""
+    (16,384) and a tile (19,200), column counts on both sides of a column block
+    (20,000), columns further apart than an offset reaches (131,072), and
+    buckets of one row, of fewer rows than lanes and of more."""
     rng = np.random.default_rng(5)
     for m, n, lens in ((7, 40_000, [0, 1, 16_384, 16_385, 40_000, 0, 3]),
-                       (3, 20_000, [5, 16_384, 16_383]), (4, 20_001, [16_385, 1, 0, 9]),
+                       (3, 20_000, [5, 16_384, 19_200]), (4, 20_001, [19_201, 1, 0, 9]),
+                       (5, 700_000, [3, 300, 0, 1, 900]),
                        (30_000, 900, rng.integers(0, 4, 30_000)),
                        (2_000, 33_000, rng.integers(60, 140, 2_000)),
                        (1, 1, [1])):
