@@ -589,7 +589,9 @@ int pdhg_spmv_noalloc(pdhg_ctx *ctx, int which, int scaled, int precision,
  *      which a panel count other than 0 also selects under -1;
  *  "tape_bytes": pdhg_unrolled_forward keeps the iterates of every step when
  *      they take at most this many bytes (256 MiB by default; at once, not
- *      at the next load), and the checkpoints otherwise;
+ *      at the next load), and the checkpoints otherwise.  The memory of a
+ *      freed tape and of a finished pass, each up to as many bytes, stays with
+ *      the context for the next ones until a load, pdhg_destroy or this key;
  *  "small": 1 (default) lets an LP of at most about 4,000 columns, 2,000 rows
  *      and 25,000 nonzeros iterate in one workgroup when none of the layout,
  *      panel, split, stream or block keys is set; 0 does not;

@@ -289,6 +289,40 @@ def test_unrolled_checkpoints_do_not_change_results(Solver, oracle, precision, s
             assert rel(a, b) <= tol
 
 
+@pytest.mark.parametrize("tape_bytes", [1 << 28, 1 << 20, 0])
+def test_unrolled_passes_share_kept_memory(Solver, oracle, tape_bytes):
+    """Passes of several lengths and precisions, with tapes that live at the
+    same time and are freed in another order and new values in between, give
+    the bits of a context of their own; a freed tape's bits do not leak into
+    the next one's."""
+    lp = lpgen.planted_uniform(m=900, n=2000, k=5, seed=8)
+    dr, dc, eta = _adjoint_setup(oracle, lp)
+    g = np.random.default_rng(1).standard_normal(lp.n)
+    passes = [(30, 7, 0), (5, 5, 1), (60, 16, 0), (30, 30, 1), (3, 1, 0)]
+
+    def one(s, p):
+        x, tape = s.unrolled_forward(p[0], p[1], eta, eta, precision=p[2])
+        return tape, x
+
+    def fresh(p):
+        with Solver.from_lp(lp, tuning={"tape_bytes": tape_bytes}) as s:
+            s.configure(ruiz_passes=10, power_iters=5)
+            tape, x = one(s, p)
+            return (x,) + tuple(tape.backward(g))
+
+    ref = [fresh(p) for p in passes]
+    with Solver.from_lp(lp, tuning={"tape_bytes": tape_bytes}) as s:
+        s.configure(ruiz_passes=10, power_iters=5)
+        for _ in range(2):
+            s.set_values(lp.a_v)
+            live = [one(s, p) for p in passes]
+            for i in (2, 0, 4, 1, 3):
+                tape, x = live[i]
+                got = (x,) + tuple(tape.backward(g))
+                assert all(np.array_equal(a, b) for a, b in zip(got, ref[i])), passes[i]
+                tape.free()
+
+
 @pytest.mark.timeout(900)
 def test_adjoint_full_size_vs_oracle_and_fd(Solver, oracle):
     """The adjoint workload at full size: m=50k, n=100k, 8 nonzeros per
