@@ -395,6 +395,9 @@ void launch_dot(const double *a, const double *b, int64_t k, double *partial,
                 double *result, hipStream_t s);
 void launch_fill(double *p, double v, int64_t k, hipStream_t s);
 void launch_fill32(float *p, float v, int64_t k, hipStream_t s);
+template <typename T>
+void launch_start(const double *xs, const double *ys, int64_t n, int64_t m,
+                  const Iter<T> &v, hipStream_t s);
 void launch_to_f32(float *dst, const double *src, int64_t k, hipStream_t s);
 void launch_to_f64(double *dst, const float *src, int64_t k, hipStream_t s);
 // elementwise: out = a * b (mode 0), a / b (mode 1), a * b with b a scalar

@@ -2206,6 +2206,25 @@ __global__ __launch_bounds__(kWG) void k_convert(D *dst, const S *src,
         dst[i] = (D)src[i];
 }
 
+// The start of a solve from the scaled pair (xs, ys): iterate and restart point
+// take it, the averages start at zero.  One launch for what small LPs pay for
+// as eight fills and four copies (about 70 us of a 3.6 ms solve).
+template <typename T>
+__global__ __launch_bounds__(kWG) void k_start(const double *__restrict__ xs,
+                                               const double *__restrict__ ys,
+                                               int64_t n, int64_t m, Iter<T> v) {
+    for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < n + m;
+         i += (int64_t)gridDim.x * kWG) {
+        if (i < n) {
+            v.x[i] = v.xl[i] = (T)xs[i];
+            v.xbar[i] = (T)0;
+        } else {
+            v.y[i - n] = v.yl[i - n] = (T)ys[i - n];
+            v.ybar[i - n] = (T)0;
+        }
+    }
+}
+
 __global__ __launch_bounds__(kWG) void k_ew(double *out, const double *a,
                                             const double *b, int64_t k,
                                             int mode) {
@@ -2349,6 +2368,17 @@ void launch_fill32(float *p, float v, int64_t k, hipStream_t s) {
     hipLaunchKernelGGL(k_fill<float>, dim3(grid_for(k, kWG, 4096)), dim3(kWG),
                        0, s, p, v, k);
 }
+
+template <typename T>
+void launch_start(const double *xs, const double *ys, int64_t n, int64_t m,
+                  const Iter<T> &v, hipStream_t s) {
+    hipLaunchKernelGGL(k_start<T>, dim3(grid_for(n + m, kWG, 4096)), dim3(kWG),
+                       0, s, xs, ys, n, m, v);
+}
+template void launch_start<double>(const double *, const double *, int64_t,
+                                   int64_t, const Iter<double> &, hipStream_t);
+template void launch_start<float>(const double *, const double *, int64_t,
+                                  int64_t, const Iter<float> &, hipStream_t);
 
 void launch_to_f32(float *dst, const double *src, int64_t k, hipStream_t s) {
     hipLaunchKernelGGL((k_convert<float, double>), dim3(grid_for(k, kWG, 4096)),

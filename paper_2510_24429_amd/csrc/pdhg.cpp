@@ -1780,20 +1780,13 @@ namespace {
 // The start of a solve from the scaled FP64 pair (xo, yo): iterate, restart
 // point, A~x and the Halpern anchor in the active precision.
 void start_iterate(pdhg_ctx *c) {
+    // (the products write all of A~x)
     if (f32(c)) {
-        zero_iter(c, c->v32);
-        launch_to_f32(c->v32.x, c->xo, c->n, c->stream);
-        launch_to_f32(c->v32.y, c->yo, c->m, c->stream);
-        HIPC(hipMemcpyAsync(c->v32.xl, c->v32.x, c->n * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
-        HIPC(hipMemcpyAsync(c->v32.yl, c->v32.y, c->m * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+        launch_start<float>(c->xo, c->yo, c->n, c->m, c->v32, c->stream);
         spmv_f32(c->A, c->v32.x, c->v32.ax, c->stream);
         HIPC(hipMemcpyAsync(c->v32.ax0, c->v32.ax, c->m * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
     } else {
-        zero_iter(c, c->v64);
-        HIPC(hipMemcpyAsync(c->v64.x, c->xo, c->n * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-        HIPC(hipMemcpyAsync(c->v64.y, c->yo, c->m * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-        HIPC(hipMemcpyAsync(c->v64.xl, c->xo, c->n * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-        HIPC(hipMemcpyAsync(c->v64.yl, c->yo, c->m * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+        launch_start<double>(c->xo, c->yo, c->n, c->m, c->v64, c->stream);
         spmv_f64(c->A, c->A.v64, c->v64.x, c->v64.ax, c->stream);
         HIPC(hipMemcpyAsync(c->v64.ax0, c->v64.ax, c->m * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
     }
