@@ -571,7 +571,8 @@ __global__ __launch_bounds__(kWG) void k_panel_combine(
 
 // Streamed entries come in 16-byte units of values (2 FP64 or 4 FP32), one
 // unit per lane, so that a wave's load or store covers whole lines in order;
-// their indices and positions come in units of as many.
+// their indices and positions come in units of as many.  (Any: a unit that may
+// start at any element.)
 typedef unsigned short v2us __attribute__((ext_vector_type(2)));
 typedef unsigned short v4us __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
@@ -581,6 +582,7 @@ template <>
 struct UnitOf<double> {
     static constexpr int W = 2;
     using V = v2d;
+    using Any = double __attribute__((ext_vector_type(2), aligned(8)));
     using H = v2us;
     using I = v2i;
 };
@@ -588,13 +590,15 @@ template <>
 struct UnitOf<float> {
     static constexpr int W = 4;
     using V = v4f;
+    using Any = float __attribute__((ext_vector_type(4), aligned(4)));
     using H = v4us;
     using I = v4i;
 };
 
 // Push pass: each workgroup multiplies the quads of its item with their column
 // block of x, which sits in LDS, into their buckets.  Bound by streaming 19
-// (FP64) or 11 (FP32) bytes a nonzero, at about 4 TB/s.
+// (FP64) or 11 (FP32) bytes a nonzero, at about 4 TB/s.  x may start at any
+// element: the iterates of an unrolled pass lie n or m elements apart.
 template <typename MT, typename VT, typename Acc>
 __global__ __launch_bounds__(kBktThreads) void k_bkt_push(
     const PushItem *__restrict__ items, const uint16_t *__restrict__ col,
@@ -637,7 +641,7 @@ __global__ __launch_bounds__(kBktThreads) void k_bkt_push(
     const int nc = (int)(cols - c0 < width ? cols - c0 : width);
     for (int i = X::W * tid; i < nc; i += X::W * kBktThreads) {
         if (i + X::W <= nc) {
-            *(typename X::V *)(s_x + i) = *(const typename X::V *)(x + c0 + i);
+            *(typename X::V *)(s_x + i) = *(const typename X::Any *)(x + c0 + i);
         } else {
             for (int u = i; u < nc; ++u) s_x[u] = x[c0 + u];
         }

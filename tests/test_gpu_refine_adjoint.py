@@ -289,6 +289,31 @@ def test_unrolled_checkpoints_do_not_change_results(Solver, oracle, precision, s
             assert rel(a, b) <= tol
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("shape", [(301, 702, 5), (1503, 3501, 5), (20_006, 45_003, 3)])
+def test_unrolled_pushed_products_at_odd_sizes(Solver, oracle, precision, shape):
+    """The gathered vectors of unrolled steps are slices of one array, n or m
+    entries apart: at sizes that are no multiple of a 16-byte unit (one and
+    several column blocks of 20,000) pushed products read them from any
+    element on, from a tape of all iterates and from checkpoints."""
+    m, n, k = shape
+    lp = lpgen.planted_uniform(m=m, n=n, k=k, seed=m)
+    dr, dc, eta = _adjoint_setup(oracle, lp)
+    K = 19
+    xt = lpgen.target_vector(lp.n, 1)
+    ref = oracle.unrolled(lp, dr, dc, eta, eta, K, xt)
+    out = []
+    for tape_bytes, ck in ((1 << 28, 5), (0, 7)):
+        with Solver.from_lp(lp, tuning={"layout_a": 2, "layout_at": 2, "tape_bytes": tape_bytes}) as s:
+            s.configure(ruiz_passes=10, power_iters=5)
+            xK, tape = s.unrolled_forward(K, ck, eta, eta, precision=precision)
+            out.append((xK,) + tuple(tape.backward(2 * (xK - xt))))
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
+    tol = 1e-9 if precision == 0 else 1e-3
+    for a, b in zip(out[0], (ref[0],) + tuple(ref[2:])):
+        assert rel(a, b) <= tol
+
+
 @pytest.mark.parametrize("tape_bytes", [1 << 28, 1 << 20, 0])
 def test_unrolled_passes_share_kept_memory(Solver, oracle, tape_bytes):
     """Passes of several lengths and precisions, with tapes that live at the
