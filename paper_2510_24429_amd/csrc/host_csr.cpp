@@ -257,7 +257,6 @@ HostBins build_row_blocks(int64_t rows, const int64_t *rp, int tile,
     const int64_t row_cap = max_rows > 0 ? std::min<int64_t>(tile, max_rows) : tile;
     std::vector<RowBlock> longb, multi;
     std::vector<std::pair<int64_t, int64_t>> singles;  // (len, row)
-    int slot = 0;
     int64_t r = 0;
     while (r < rows) {
         int64_t len = rp[r + 1] - rp[r];
@@ -270,11 +269,10 @@ HostBins build_row_blocks(int64_t rows, const int64_t *rp, int tile,
                 int nparts = (int)((len + split_chunk - 1) / split_chunk);
                 for (int q = 0; q < nparts; ++q)
                     longb.push_back({(int32_t)r, (int32_t)(r + 1), q, nparts,
-                                     slot, 0, 0, 0});
-                hb.splits.push_back({(int32_t)r, nparts});
-                hb.maxparts = std::max(hb.maxparts, nparts);
+                                     hb.parts, 0, 0, 0});
+                hb.splits.push_back({(int32_t)r, nparts, hb.parts});
+                hb.parts += nparts;
                 hb.counts[2] += nparts;
-                ++slot;
             } else {
                 singles.push_back({len, r});
             }
@@ -543,12 +541,13 @@ HostBins build_panel_blocks(int64_t rows, const int64_t *srp, int P, int tile,
                                        split_threshold, split_chunk, max_rows,
                                        true);
         const int32_t roff = (int32_t)((int64_t)p * rows);
-        const int slot0 = (int)out.splits.size();
+        const int32_t slot0 = out.parts;
         for (auto sp : hb.splits) {
             sp.row += roff;
+            sp.first += slot0;
             out.splits.push_back(sp);
         }
-        out.maxparts = std::max(out.maxparts, hb.maxparts);
+        out.parts += hb.parts;
         for (int k = 0; k < 3; ++k) out.counts[k] += hb.counts[k];
         const int per = kXcd / P;     // XCDs serving this panel
         for (size_t b = 0; b < hb.blocks.size(); ++b) {
@@ -602,14 +601,13 @@ static void pack_buckets(HostBuckets &B, int64_t row0, int64_t row1,
         if (len > cap) {
             const int np = (int)((len + cap - 1) / cap);
             const int64_t chunk = (len + np - 1) / np;
-            const int slot = (int)B.splits.size();
             for (int q = 0; q < np; ++q) {
                 const int64_t a = rp[r] + q * chunk, e = std::min(rp[r + 1], a + chunk);
                 B.buckets.push_back({(int32_t)r, (int32_t)(r + 1), (int32_t)a,
-                                     (int32_t)e, 0, 0, slot, q});
+                                     (int32_t)e, 0, 0, B.parts, q});
             }
-            B.splits.push_back({(int32_t)r, np});
-            B.maxparts = std::max(B.maxparts, np);
+            B.splits.push_back({(int32_t)r, np, B.parts});
+            B.parts += np;
             ++r;
             continue;
         }

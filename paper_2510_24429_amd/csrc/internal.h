@@ -35,23 +35,26 @@ inline int red_blocks(int64_t k) {
 //    through LDS and summed by groups of lanes per row;
 //  - one row (r1 - r0 == 1, nparts == 1): all 256 lanes stride the row and
 //    reduce across the workgroup;
-//  - one row split over nparts workgroups: part `part` writes a partial sum
-//    to slot `slot`; a fix-up pass adds the parts in order.
+//  - one row split over nparts workgroups: part `part` writes partial sum
+//    slot + part; a fix-up pass adds the parts in order.
 // A workgroup's rows [r0, r1) and their nonzeros [p0, p1) (the whole row
-// for a split row, whose part `part` of `nparts` the workgroup sums into
-// partial slot `slot`); r0 == r1 marks an empty padding block.
+// for a split row, whose part `part` of `nparts` the workgroup sums);
+// r0 == r1 marks an empty padding block.
 struct RowBlock {
     int32_t r0, r1, part, nparts, slot, p0, p1, pad;
 };
 
+// Partial sums [first, first + nparts) of a row.  (Indexed one row after the
+// other: rows times the most parts of any would exceed 32 bits with one row of
+// 1e9 nonzeros beside 35,000 split ones.)
 struct SplitRow {
-    int32_t row, nparts;
+    int32_t row, nparts, first;
 };
 
 struct HostBins {
     std::vector<RowBlock> blocks;
     std::vector<SplitRow> splits;
-    int maxparts = 1;
+    int32_t parts = 0;               // partial sums of all split rows
     int64_t counts[3] = {0, 0, 0};   // multi-row, single-row, split parts
 };
 
@@ -97,7 +100,7 @@ struct PushItem {
     int32_t cb, q0, q1, pad;
 };
 // Rows [r0, r1) with nonzeros [p0, p1) and products at quads [q0, q1), or
-// (slot >= 0) part `part` of row r0, whose sum goes to partial slot `slot`.
+// (slot >= 0) part `part` of row r0, whose sum is partial slot + part.
 struct Bucket {
     int32_t r0, r1, p0, p1, q0, q1, slot, part;
 };
@@ -108,7 +111,7 @@ struct HostBuckets {
     std::vector<PushItem> items;
     std::vector<Bucket> buckets;
     std::vector<SplitRow> splits;
-    int maxparts = 1;
+    int32_t parts = 0;                // partial sums of all split rows
     std::vector<uint16_t> col, pos;   // 4 * quads: column in its block (push
                                       // order), CSR position in its bucket
                                       // (kBktCap: padding)
@@ -128,7 +131,7 @@ int choose_layout(int64_t rows, int64_t cols, int64_t nnz, int P);
 
 // The same on the device.
 struct DevBuckets {
-    int width = 0, nitems = 0, nbuckets = 0, nsplit = 0, maxparts = 1;
+    int width = 0, nitems = 0, nbuckets = 0, nsplit = 0;
     bool f64 = true;                  // FP64 products run here too
     int64_t quads = 0;
     PushItem *items = nullptr;
@@ -224,7 +227,7 @@ struct DevCsr {
     RowBlock *blk32 = nullptr;
     int nblk32 = 0;
     SplitRow *split64 = nullptr, *split32 = nullptr;
-    int nsplit64 = 0, nsplit32 = 0, maxparts64 = 1, maxparts32 = 1;
+    int nsplit64 = 0, nsplit32 = 0;
     double *part64 = nullptr;   // split partial sums
     float *part32 = nullptr;
     int64_t counts64[3] = {0, 0, 0};

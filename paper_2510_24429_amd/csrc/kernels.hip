@@ -405,7 +405,7 @@ struct AdjPrimalEpi {
 template <typename Acc, int TILE, class Elem, class Epi>
 __global__ __launch_bounds__(kWG) void k_rowblock(
     const RowBlock *__restrict__ blks, const int32_t *__restrict__ rp,
-    Elem elem, Epi epi_in, Acc *__restrict__ part, int maxparts) {
+    Elem elem, Epi epi_in, Acc *__restrict__ part) {
     constexpr int U = TILE / kWG;     // nonzeros per thread in a full tile
     using MT = decltype(elem.v[0] + 0);
     __shared__ Acc s_prod[TILE];
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(kWG) void k_rowblock(
         Acc s = block_sum(s0 + s1, s_red);
         if (tid == 0) {
             if (b.nparts > 1)
-                part[b.slot * maxparts + b.part] = s;
+                part[b.slot + b.part] = s;
             else
                 epi(b.r0, s);
         }
@@ -536,14 +536,14 @@ __global__ __launch_bounds__(kWG) void k_rowblock(
 template <typename Acc, class Epi>
 __global__ __launch_bounds__(kFixThreads) void k_split_fix(
     const SplitRow *__restrict__ sp, int nsplit, const Acc *__restrict__ part,
-    int maxparts, Epi epi_in) {
+    Epi epi_in) {
     Epi epi = epi_in;
     if (!epi.begin()) return;
     const int t = blockIdx.x * kFixThreads + threadIdx.x;
     if (t >= nsplit) return;
     Acc s = (Acc)0;
     const SplitRow r = sp[t];
-    for (int q = 0; q < r.nparts; ++q) s += part[t * maxparts + q];
+    for (int q = 0; q < r.nparts; ++q) s += part[r.first + q];
     epi(r.row, s);
 }
 
@@ -773,7 +773,7 @@ __device__ __forceinline__ void bkt_fill(const Units &units,
 template <typename Acc, bool LOOP, class Units, class Epi>
 __global__ __launch_bounds__(kBktThreads, Units::kWaves) void k_bkt_sum(
     const Bucket *__restrict__ buckets, int nbuckets,
-    const int32_t *__restrict__ rp, Units units, Acc *__restrict__ part, int maxparts, Epi epi_in) {
+    const int32_t *__restrict__ rp, Units units, Acc *__restrict__ part, Epi epi_in) {
     constexpr int NT = kBktThreads;
     __shared__ Acc s_prod[Units::kCap + 1];
     __shared__ Acc s_sum[NT];
@@ -834,7 +834,7 @@ __global__ __launch_bounds__(kBktThreads, Units::kWaves) void k_bkt_sum(
                 s = s_sum[0];
                 for (int w = 1; w < NT / 64; ++w) s += s_sum[w];
                 if (b.slot >= 0)
-                    part[b.slot * maxparts + b.part] = s;
+                    part[b.slot + b.part] = s;
                 else
                     epi(b.r0, s);
             }
@@ -890,12 +890,12 @@ void run_sum(const DevCsr &M, const Units &units, Epi e, hipStream_t s) {
         hipLaunchKernelGGL((k_bkt_sum<Acc, loop, Units, Epi>),
                            dim3(loop && K.nbuckets > kCus ? kCus : K.nbuckets),
                            dim3(kBktThreads), 0, s, K.buckets, K.nbuckets, M.rp,
-                           units, part, K.maxparts, e);
+                           units, part, e);
     if (K.nsplit > 0)
         hipLaunchKernelGGL((k_split_fix<Acc, Epi>),
                            dim3((K.nsplit + kFixThreads - 1) / kFixThreads),
                            dim3(kFixThreads), 0, s, K.split, K.nsplit, part,
-                           K.maxparts, e);
+                           e);
 }
 
 template <typename Acc, typename MT, typename VT, class Epi>
@@ -916,17 +916,16 @@ void run_buckets(const DevCsr &M, const MT *vals, const VT *in, Epi e,
 
 template <typename Acc, int TILE, class Elem, class Epi>
 void run_rowblock(const RowBlock *blk, int nblk, const SplitRow *split,
-                  int nsplit, Acc *part, int maxparts, const int32_t *rp,
+                  int nsplit, Acc *part, const int32_t *rp,
                   Elem elem, Epi epi, hipStream_t s) {
     if (nblk > 0)
         hipLaunchKernelGGL((k_rowblock<Acc, TILE, Elem, Epi>), dim3(nblk),
-                           dim3(kWG), 0, s, blk, rp, elem, epi, part,
-                           maxparts);
+                           dim3(kWG), 0, s, blk, rp, elem, epi, part);
     if (nsplit > 0)
         hipLaunchKernelGGL((k_split_fix<Acc, Epi>),
                            dim3((nsplit + kFixThreads - 1) / kFixThreads),
                            dim3(kFixThreads), 0, s, split, nsplit, part,
-                           maxparts, epi);
+                           epi);
 }
 
 int grid_for(int64_t k, int per = kWG, int cap = 8192) {
@@ -942,10 +941,10 @@ template <typename Acc, class Elem, class Epi>
 void run_bins(const DevCsr &M, Elem e, Epi p, hipStream_t s) {
     if constexpr (std::is_same<Acc, double>::value)
         run_rowblock<double, kTile64>(M.blk64, M.nblk64, M.split64, M.nsplit64,
-                                      M.part64, M.maxparts64, M.rp, e, p, s);
+                                      M.part64, M.rp, e, p, s);
     else
         run_rowblock<float, kTile32>(M.blk32, M.nblk32, M.split32, M.nsplit32,
-                                     M.part32, M.maxparts32, M.rp, e, p, s);
+                                     M.part32, M.rp, e, p, s);
 }
 
 // out-row r of M x epilogue, with M's values `vals` (its scaled FP64 or FP32
@@ -1981,7 +1980,7 @@ __global__ __launch_bounds__(kWG) void k_ruiz_rowmax(
     const RowBlock *__restrict__ blks, const int32_t *__restrict__ rp,
     const int32_t *__restrict__ ci, const double *__restrict__ v,
     const double *__restrict__ d_row, const double *__restrict__ d_col,
-    double *__restrict__ rho, double *__restrict__ part, int maxparts) {
+    double *__restrict__ rho, double *__restrict__ part) {
     constexpr int U = kTile64 / kWG;
     __shared__ double s_v[kTile64];
     __shared__ double s_d[TR ? 1 : kTile64];
@@ -2008,7 +2007,7 @@ __global__ __launch_bounds__(kWG) void k_ruiz_rowmax(
         if (tid == 0) {
             mx = fmax(fmax(s_red[0], s_red[1]), fmax(s_red[2], s_red[3]));
             if (b.nparts > 1)
-                part[b.slot * maxparts + b.part] = mx;
+                part[b.slot + b.part] = mx;
             else
                 rho[b.r0] = mx;
         }
@@ -2061,12 +2060,13 @@ __global__ __launch_bounds__(kWG) void k_ruiz_rowmax(
 // Rows split over several workgroups: the maximum of their parts.
 __global__ __launch_bounds__(kFixThreads) void k_split_max(
     const SplitRow *__restrict__ sp, int nsplit, const double *__restrict__ part,
-    int maxparts, double *__restrict__ rho) {
+    double *__restrict__ rho) {
     const int t = blockIdx.x * kFixThreads + threadIdx.x;
     if (t >= nsplit) return;
     double mx = 0.0;
-    for (int q = 0; q < sp[t].nparts; ++q) mx = fmax(mx, part[t * maxparts + q]);
-    rho[sp[t].row] = mx;
+    const SplitRow r = sp[t];
+    for (int q = 0; q < r.nparts; ++q) mx = fmax(mx, part[r.first + q]);
+    rho[r.row] = mx;
 }
 
 __global__ __launch_bounds__(kWG) void k_ruiz_update(double *d,
@@ -2126,7 +2126,7 @@ void launch_ruiz_rowmax(const DevCsr &M, const double *d_row,
         auto run = [&](auto kern) {
             hipLaunchKernelGGL(kern, dim3(M.nblk64), dim3(kWG), 0, s, M.blk64,
                                M.rp, M.ci, M.v_orig, d_row, d_col, rho,
-                               M.part64, M.maxparts64);
+                               M.part64);
         };
         if (transposed)
             run(k_ruiz_rowmax<true>);
@@ -2137,7 +2137,7 @@ void launch_ruiz_rowmax(const DevCsr &M, const double *d_row,
         hipLaunchKernelGGL(k_split_max,
                            dim3((M.nsplit64 + kFixThreads - 1) / kFixThreads),
                            dim3(kFixThreads), 0, s, M.split64, M.nsplit64,
-                           M.part64, M.maxparts64, rho);
+                           M.part64, rho);
 }
 
 void launch_ruiz_update(double *d, const double *rho, int64_t k,

@@ -624,14 +624,12 @@ void upload_bins(DevCsr &M, const HostBins &b64, const HostBins &b32) {
     if (M.nblk32) HIPC(hipMemcpy(M.blk32, b32.blocks.data(), M.nblk32 * sizeof(RowBlock), hipMemcpyHostToDevice));
     M.nsplit64 = (int)b64.splits.size();
     M.nsplit32 = (int)b32.splits.size();
-    M.maxparts64 = b64.maxparts;
-    M.maxparts32 = b32.maxparts;
     M.split64 = dmalloc<SplitRow>(M.nsplit64);
     M.split32 = dmalloc<SplitRow>(M.nsplit32);
     if (M.nsplit64) HIPC(hipMemcpy(M.split64, b64.splits.data(), M.nsplit64 * sizeof(SplitRow), hipMemcpyHostToDevice));
     if (M.nsplit32) HIPC(hipMemcpy(M.split32, b32.splits.data(), M.nsplit32 * sizeof(SplitRow), hipMemcpyHostToDevice));
-    M.part64 = dmalloc<double>((int64_t)M.nsplit64 * M.maxparts64);
-    M.part32 = dmalloc<float>((int64_t)M.nsplit32 * M.maxparts32);
+    M.part64 = dmalloc<double>(b64.parts);
+    M.part32 = dmalloc<float>(b32.parts);
     for (int q = 0; q < 3; ++q) M.counts64[q] = b64.counts[q];
 }
 
@@ -656,13 +654,12 @@ DevBuckets *upload_buckets(const HostBuckets &H, bool f64, bool force) {
     K->quads = H.quads;
     K->nbuckets = (int)H.buckets.size();
     K->nsplit = (int)H.splits.size();
-    K->maxparts = H.maxparts;
     K->buckets = upload(H.buckets);
     K->split = upload(H.splits);
     K->src = upload(H.src);
     K->v64 = dmalloc<double>(4 * K->quads);
     K->v32 = dmalloc<float>(4 * K->quads);
-    K->part = dmalloc<double>((int64_t)K->nsplit * K->maxparts);
+    K->part = dmalloc<double>(H.parts);
     if (!H.word.empty()) {
         K->word = upload(H.word);
         K->base = upload(H.base);

@@ -50,13 +50,15 @@ Csr make(int64_t m, int64_t n, double avg, int kind, std::mt19937_64 &g) {
 }
 
 // Rows of a bucket summed from its products in LDS order.
-void sum_rows(const HostBuckets &B, const Bucket &b, const std::vector<double> &s,
+void sum_rows(const Bucket &b, const std::vector<double> &s,
               const std::vector<int64_t> &rp, std::vector<double> &part,
               std::vector<double> &y) {
     if (b.slot >= 0) {
         double t = 0;
         for (int64_t p = 0; p < b.p1 - b.p0; ++p) t += s[p];
-        part[b.slot * B.maxparts + b.part] = t;
+        const size_t k = (size_t)(b.slot + b.part);
+        CHECK(k < part.size() && std::isnan(part[k]));
+        part[k] = t;
         return;
     }
     for (int64_t r = b.r0; r < b.r1; ++r) {
@@ -68,12 +70,32 @@ void sum_rows(const HostBuckets &B, const Bucket &b, const std::vector<double> &
     }
 }
 
-void finish(const HostBuckets &B, const std::vector<double> &part, std::vector<double> &y) {
-    for (size_t t = 0; t < B.splits.size(); ++t) {
+// Every partial sum belongs to one row, none is left over.
+void finish(const std::vector<SplitRow> &splits, const std::vector<double> &part, std::vector<double> &y) {
+    size_t used = 0;
+    for (const SplitRow &r : splits) {
         double q = 0;
-        for (int k = 0; k < B.splits[t].nparts; ++k) q += part[t * B.maxparts + k];
-        y[B.splits[t].row] = q;
+        CHECK((size_t)r.first == used && used + r.nparts <= part.size());
+        for (int k = 0; k < r.nparts; ++k) q += part[r.first + k];
+        used += r.nparts;
+        y[r.row] = q;
     }
+    CHECK(used == part.size());
+}
+
+// The same of the row blocks' split rows.
+void check_blocks(const HostBins &H) {
+    std::vector<double> part(H.parts, NAN);
+    for (const RowBlock &b : H.blocks)
+        if (b.nparts > 1) {
+            const size_t k = (size_t)(b.slot + b.part);
+            CHECK(k < part.size() && std::isnan(part[k]));
+            part[k] = b.r0;
+        }
+    size_t used = 0;
+    for (const SplitRow &r : H.splits)
+        for (int k = 0; k < r.nparts; ++k, ++used) CHECK(part[r.first + k] == r.row);
+    CHECK(used == part.size());
 }
 
 }  // namespace
@@ -98,6 +120,7 @@ int main() {
         for (auto &t : v) t = (double)(int64_t)(g() % 201) - 100;
         for (int64_t i = 0; i < c.m; ++i)
             for (int64_t p = A.rp[i]; p < A.rp[i + 1]; ++p) ref[i] += v[p] * x[A.ci[p]];
+        check_blocks(build_row_blocks(c.m, A.rp.data(), kTile64 - 3, 4096, 1000));
         {
             const HostBuckets B = build_push(c.m, c.n, A.rp.data(), A.ci.data(), true);
             std::vector<double> prod(4 * B.quads, NAN), y(c.m, NAN);
@@ -127,7 +150,7 @@ int main() {
             }
             CHECK(covered == B.quads);
             CHECK(std::count(seen.begin(), seen.end(), 1) == nnz);
-            std::vector<double> part(B.splits.size() * B.maxparts, NAN);
+            std::vector<double> part(B.parts, NAN);
             for (const Bucket &b : B.buckets) {
                 std::vector<double> s(kBktCap + 1, NAN);
                 CHECK(b.r0 >= 0 && b.r0 < b.r1 && b.r1 <= c.m && b.p1 - b.p0 <= kBktCap);
@@ -136,9 +159,9 @@ int main() {
                     CHECK(B.pos[e] <= kBktCap);
                     s[B.pos[e]] = prod[e];
                 }
-                sum_rows(B, b, s, A.rp, part, y);
+                sum_rows(b, s, A.rp, part, y);
             }
-            finish(B, part, y);
+            finish(B.splits, part, y);
             CHECK(y == ref);
             std::printf("push m %ld n %ld nnz %ld kind %d quads %ld buckets %zu splits %zu fragmented %d\n",
                         (long)c.m, (long)c.n, (long)nnz, c.kind, (long)B.quads,
@@ -148,8 +171,9 @@ int main() {
             std::vector<int64_t> cut;
             for (int p = 0; p <= P; ++p) cut.push_back(c.n * p / P);
             const Panels S = build_panels(c.m, A.rp.data(), A.ci.data(), P, cut);
+            check_blocks(build_panel_blocks(c.m, S.rp.data(), P, kTile64 - 3, 4096, 1000));
             const HostBuckets B = build_tiles(c.m, S.rp.data(), S.ci.data(), P, true);
-            std::vector<double> part(B.splits.size() * B.maxparts, NAN), ys(P * c.m, NAN), y(c.m, 0.0);
+            std::vector<double> part(B.parts, NAN), ys(P * c.m, NAN), y(c.m, 0.0);
             std::vector<char> seen(nnz, 0);
             CHECK((int64_t)B.word.size() == 4 * B.quads && B.src.size() == B.word.size() &&
                   64 * (int64_t)B.base.size() == B.quads);
@@ -167,10 +191,10 @@ int main() {
                     seen[p] = 1;
                     s[pos] = v[S.src[p]] * x[col];
                 }
-                sum_rows(B, b, s, S.rp, part, ys);
+                sum_rows(b, s, S.rp, part, ys);
             }
             CHECK(std::count(seen.begin(), seen.end(), 1) == nnz);
-            finish(B, part, ys);
+            finish(B.splits, part, ys);
             for (int64_t i = 0; i < c.m; ++i)
                 for (int p = 0; p < P; ++p)
                     if (P == 1 || (S.mask[i] >> p & 1)) y[i] += ys[(int64_t)p * c.m + i];
