@@ -58,6 +58,20 @@ T *dmalloc(int64_t count) {
     return (T *)p;
 }
 
+// Runs fn, and where it runs out of memory (of the device or the host), back.
+template <class Fn, class Back>
+void out_of_memory(Fn fn, Back back) {
+    try {
+        fn();
+        return;
+    } catch (const DevError &e) {
+        if (e.code != PDHG_E_OOM) throw;
+        (void)hipGetLastError();
+    } catch (const std::bad_alloc &) {
+    }
+    back();
+}
+
 template <typename T>
 void dfree(T *&p) {
     if (p) (void)hipFree((void *)p);
@@ -480,26 +494,30 @@ std::vector<T> to_host(pdhg_ctx *c, const T *p, int64_t count, int mem) {
     return h;
 }
 
+void free_buckets(DevBuckets *&k) {
+    if (!k) return;
+    dfree(k->items);
+    dfree(k->buckets);
+    dfree(k->split);
+    dfree(k->col);
+    dfree(k->pos);
+    dfree(k->src);
+    dfree(k->dest);
+    dfree(k->word);
+    dfree(k->base);
+    dfree(k->v64);
+    dfree(k->v32);
+    dfree(k->part);
+    delete k;
+    k = nullptr;
+}
+
 void free_csr(DevCsr &M) {
     if (M.pan) {
         free_csr(*M.pan);
         delete M.pan;
     }
-    if (DevBuckets *k = M.bkt) {
-        dfree(k->items);
-        dfree(k->buckets);
-        dfree(k->split);
-        dfree(k->col);
-        dfree(k->pos);
-        dfree(k->src);
-        dfree(k->dest);
-        dfree(k->word);
-        dfree(k->base);
-        dfree(k->v64);
-        dfree(k->v32);
-        dfree(k->part);
-        delete k;
-    }
+    free_buckets(M.bkt);
     if (DevSmall *k = M.small) {
         dfree(k->base);
         delete k;
@@ -639,39 +657,38 @@ int64_t padded(int64_t nnz) { return ((nnz + 3) & ~(int64_t)3) + 4; }
 
 // A vector to a device array of its own.
 template <typename T>
-T *upload(const std::vector<T> &h) {
-    T *d = dmalloc<T>((int64_t)h.size());
+void upload(T *&d, const std::vector<T> &h) {
+    d = dmalloc<T>((int64_t)h.size());
     if (!h.empty()) HIPC(hipMemcpy(d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
-    return d;
 }
 
-// Buckets or tiles to the device (their values are filled by apply_scaling);
-// null when their rows do not fill them.
-DevBuckets *upload_buckets(const HostBuckets &H, bool f64, bool force) {
-    if (H.fragmented && !force) return nullptr;
-    DevBuckets *K = new DevBuckets();
+// Buckets or tiles of M to the device (their values are filled by
+// apply_scaling); none when their rows do not fill them.  What was allocated
+// when an exception leaves here belongs to M.
+void upload_buckets(DevCsr &M, const HostBuckets &H, bool f64, bool force) {
+    if (H.fragmented && !force) return;
+    DevBuckets *K = M.bkt = new DevBuckets();
     K->f64 = f64;
     K->quads = H.quads;
     K->nbuckets = (int)H.buckets.size();
     K->nsplit = (int)H.splits.size();
-    K->buckets = upload(H.buckets);
-    K->split = upload(H.splits);
-    K->src = upload(H.src);
+    upload(K->buckets, H.buckets);
+    upload(K->split, H.splits);
+    upload(K->src, H.src);
     K->v64 = dmalloc<double>(4 * K->quads);
     K->v32 = dmalloc<float>(4 * K->quads);
     K->part = dmalloc<double>(H.parts);
     if (!H.word.empty()) {
-        K->word = upload(H.word);
-        K->base = upload(H.base);
+        upload(K->word, H.word);
+        upload(K->base, H.base);
     } else {
-        K->pos = upload(H.pos);
-        K->items = upload(H.items);
+        upload(K->pos, H.pos);
+        upload(K->items, H.items);
         K->nitems = (int)H.items.size();
         K->width = H.width;
-        K->col = upload(H.col);
-        K->dest = upload(H.dest);
+        upload(K->col, H.col);
+        upload(K->dest, H.dest);
     }
-    return K;
 }
 
 // The panel twin of M (P > 1): the stacked panel matrix with its own index
@@ -712,16 +729,16 @@ void upload_panels(pdhg_ctx *c, DevCsr &M, const std::vector<int64_t> &rp,
         HIPC(hipMemcpy(M.pan_mask, S.mask.data(), M.rows * sizeof(uint8_t), hipMemcpyHostToDevice));
     }
     if (layout == LAYOUT_TILES)
-        T.bkt = upload_buckets(build_tiles(M.rows, S.rp.data(), S.ci.data(), P, force),
-                               force || M.nnz >= kTileMin64, force);
+        upload_buckets(T, build_tiles(M.rows, S.rp.data(), S.ci.data(), P, force),
+                       force || M.nnz >= kTileMin64, force);
     M.q64 = dmalloc<double>(T.rows);
     M.q32 = dmalloc<float>(T.rows);
 }
 
 // The one-workgroup layout: one allocation and one copy (values behind the
 // plan), since loading a small LP is mostly such calls.
-DevSmall *upload_small(const HostSmall &H) {
-    DevSmall *S = new DevSmall();
+void upload_small(DevCsr &M, const HostSmall &H) {
+    DevSmall *S = M.small = new DevSmall();
     S->G = H.G;
     S->K = H.K;
     S->entries = (int64_t)H.src.size();
@@ -745,7 +762,6 @@ DevSmall *upload_small(const HostSmall &H) {
     S->col = (uint16_t *)(S->base + o_col);
     S->v64 = (double *)(S->base + plan);
     S->v32 = (float *)(S->base + o_v32);
-    return S;
 }
 
 // Upload one CSR (int64 row pointers on the host) and build both bin sets;
@@ -781,13 +797,13 @@ void upload_csr(pdhg_ctx *c, DevCsr &M, int64_t rows, int64_t cols,
     upload_bins(M, build_row_blocks(rows, rp.data(), kTile64 - 3, c->split_threshold, c->split_chunk, c->block_rows),
                 build_row_blocks(rows, rp.data(), kTile32 - 3, c->split_threshold, c->split_chunk, c->block_rows));
     if (layout == LAYOUT_PUSH)
-        M.bkt = upload_buckets(build_push(rows, cols, rp.data(), ci.data(), force), true, force);
+        upload_buckets(M, build_push(rows, cols, rp.data(), ci.data(), force), true, force);
     if (M.bkt)
         M.P = P;
     else if (P > 1)
         upload_panels(c, M, rp, ci, P, cut, layout, force);
     else if (tiles.valid())
-        M.bkt = upload_buckets(tiles.get(), true, force);
+        upload_buckets(M, tiles.get(), true, force);
     // stream the CSR non-temporally when the FP64 gather table each XCD
     // works on exceeds 3 MiB, so that streaming does not evict it from L2
     M.stream_nt = c->stream_nt >= 0 ? c->stream_nt
@@ -849,13 +865,16 @@ void apply_scaling(pdhg_ctx *c) {
     }
 }
 
-// The tiles of sides that only FP32 products run in, before the first of them.
+// The tiles of sides that only FP32 products run in, before the first of them
+// (without memory for them these products stay in row blocks).
 void ensure_f32_tiles(pdhg_ctx *c) {
     for (int k = 0; k < 2; ++k) {
         auto &l = c->later[k];
         if (l.rp.empty()) continue;
         DevCsr &M = k ? c->At : c->A;
-        M.bkt = upload_buckets(build_tiles(M.rows, l.rp.data(), l.ci.data(), 1, false), false, false);
+        out_of_memory([&] {
+            upload_buckets(M, build_tiles(M.rows, l.rp.data(), l.ci.data(), 1, false), false, false);
+        }, [&] { free_buckets(M.bkt); });
         l = {};
         if (M.bkt)
             launch_gather_pad(M.bkt->v64, M.bkt->v32, M.v64, M.bkt->src, 4 * M.bkt->quads, c->stream);
@@ -1634,103 +1653,114 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
     // stacked panel rows are indexed in int32: keep P * rows below 2^31
     while (pa > 1 && (int64_t)pa * m >= ((int64_t)1 << 31)) pa /= 2;
     while (pat > 1 && (int64_t)pat * n >= ((int64_t)1 << 31)) pat /= 2;
-    // a panel count that the caller asked for runs as row blocks
-    auto layout = [&](int asked, int panels, int64_t rows, int64_t cols, int P) {
-        return asked != LAYOUT_CHOOSE ? asked : panels ? LAYOUT_ROWS : choose_layout(rows, cols, nnz, P);
-    };
     Relabeled R = relabel(m, n, nnz, h_arp.data(), h_aci.data(), h_av.data(),
                           h_atrp.data(), pa, pat, c->sort_rows, c->sort_cols);
     std::vector<int32_t>().swap(h_aci);
     std::vector<double>().swap(h_av);
-    const int la = layout(c->layout_a, c->panels_a, m, n, pa);
-    const int lat = layout(c->layout_at, c->panels_at, n, m, pat);
-    const bool fa = c->layout_a != LAYOUT_CHOOSE, fat = c->layout_at != LAYOUT_CHOOSE;
-    // tiles of an unpanelled side: planned while the arrays are uploaded, or,
-    // where only FP32 products use them, kept for the first FP32 iteration
-    const bool ta = la == LAYOUT_TILES && pa == 1, tat = lat == LAYOUT_TILES && pat == 1;
-    auto plan = [&](bool on, int64_t rows, const std::vector<int64_t> &rp,
-                    const std::vector<int32_t> &ci, bool force) {
-        return on && (force || nnz >= kTileMin64)
-                   ? std::async(std::launch::async, [&rp, &ci, rows, force] {
-                         return build_tiles(rows, rp.data(), ci.data(), 1, force);
-                     })
-                   : std::future<HostBuckets>();
+    // everything on the device; lean: with row blocks alone where no layout was
+    // asked for
+    auto fill = [&](bool lean) {
+        // a panel count that the caller asked for runs as row blocks, and so does a
+        // lean load
+        auto layout = [&](int asked, int panels, int64_t rows, int64_t cols, int P) {
+            return asked != LAYOUT_CHOOSE ? asked : panels || lean ? LAYOUT_ROWS : choose_layout(rows, cols, nnz, P);
+        };
+        const int la = layout(c->layout_a, c->panels_a, m, n, pa);
+        const int lat = layout(c->layout_at, c->panels_at, n, m, pat);
+        const bool fa = c->layout_a != LAYOUT_CHOOSE, fat = c->layout_at != LAYOUT_CHOOSE;
+        // tiles of an unpanelled side: planned while the arrays are uploaded, or,
+        // where only FP32 products use them, kept for the first FP32 iteration
+        const bool ta = la == LAYOUT_TILES && pa == 1, tat = lat == LAYOUT_TILES && pat == 1;
+        auto plan = [&](bool on, int64_t rows, const std::vector<int64_t> &rp,
+                        const std::vector<int32_t> &ci, bool force) {
+            return on && (force || nnz >= kTileMin64)
+                       ? std::async(std::launch::async, [&rp, &ci, rows, force] {
+                             return build_tiles(rows, rp.data(), ci.data(), 1, force);
+                         })
+                       : std::future<HostBuckets>();
+        };
+        auto plan_a = plan(ta, m, R.a_rp, R.a_ci, fa);
+        auto plan_at = plan(tat, n, R.at_rp, R.at_ci, fat);
+        upload_csr(c, c->A, m, n, nnz, R.a_rp, R.a_ci, R.a_v, pa, R.a_cut, la, fa, std::move(plan_a));
+        upload_csr(c, c->At, n, m, nnz, R.at_rp, R.at_ci, R.at_v, pat, R.at_cut, lat, fat, std::move(plan_at));
+        // a small LP iterates in one workgroup unless row blocks, a layout or panels
+        // were asked for
+        const bool plain = !lean && c->small != 0 && !fa && !fat && !c->panels_a &&
+                           !c->panels_at && c->split_threshold == kSplitThreshold && c->split_chunk == kSplitChunk &&
+                           c->block_rows == kWG && c->stream_nt < 0;
+        auto longest = [](const std::vector<int64_t> &rp) {
+            int64_t k = 0;
+            for (size_t i = 1; i < rp.size(); ++i) k = std::max(k, rp[i] - rp[i - 1]);
+            return k;
+        };
+        const int64_t longest_a = plain ? longest(R.a_rp) : 0, longest_at = plain ? longest(R.at_rp) : 0;
+        c->small64 = plain && small_fits<double>(m, n, nnz, longest_a, longest_at);
+        c->small32 = plain && small_fits<float>(m, n, nnz, longest_a, longest_at);
+        if (c->small64 || c->small32) {
+            upload_small(c->A, build_small(m, n, R.a_rp.data(), R.a_ci.data()));
+            upload_small(c->At, build_small(n, m, R.at_rp.data(), R.at_ci.data()));
+        }
+        // one product buffer for the push passes of both sides
+        int64_t prods = 0;
+        for (DevCsr *M : {&c->A, &c->At})
+            if (M->bkt && M->bkt->items) prods = std::max(prods, 4 * M->bkt->quads);
+        if (prods) c->prod = dmalloc<double>(prods);
+        for (DevCsr *M : {&c->A, &c->At})
+            if (M->bkt) M->bkt->prod = c->prod;
+        std::vector<int32_t> ridx((size_t)nnz);
+        for (int64_t i = 0; i < m; ++i)
+            for (int64_t p = R.a_rp[i]; p < R.a_rp[i + 1]; ++p) ridx[p] = (int32_t)i;
+        c->perm = dmalloc<int32_t>(nnz);
+        c->rowidx = dmalloc<int32_t>(nnz);
+        c->apos = dmalloc<int32_t>(nnz);
+        c->pr = dmalloc<int32_t>(m);
+        c->pc = dmalloc<int32_t>(n);
+        if (nnz) {
+            HIPC(hipMemcpy(c->perm, R.perm.data(), nnz * sizeof(int32_t), hipMemcpyHostToDevice));
+            HIPC(hipMemcpy(c->rowidx, ridx.data(), nnz * sizeof(int32_t), hipMemcpyHostToDevice));
+            HIPC(hipMemcpy(c->apos, R.apos.data(), nnz * sizeof(int32_t), hipMemcpyHostToDevice));
+        }
+        HIPC(hipMemcpy(c->pr, R.pr.data(), m * sizeof(int32_t), hipMemcpyHostToDevice));
+        HIPC(hipMemcpy(c->pc, R.pc.data(), n * sizeof(int32_t), hipMemcpyHostToDevice));
+        if (ta && !c->A.bkt && !fa && nnz < kTileMin64) c->later[0] = {R.a_rp, R.a_ci};
+        if (tat && !c->At.bkt && !fat && nnz < kTileMin64) c->later[1] = {R.at_rp, R.at_ci};
+        c->tmp_m = dmalloc<double>(m);
+        c->tmp_n = dmalloc<double>(n);
+        c->b_orig = dmalloc<double>(m);
+        c->c_orig = dmalloc<double>(n);
+        vec_in(c, c->b_orig, b, true, mem);
+        vec_in(c, c->c_orig, cvec, false, mem);
+        c->has_l = lb != nullptr;
+        if (c->has_l) {
+            c->l_orig = dmalloc<double>(n);
+            vec_in(c, c->l_orig, lb, false, mem);
+        }
+        c->dr = dmalloc<double>(m);
+        c->dc = dmalloc<double>(n);
+        c->bs = dmalloc<double>(m);
+        c->cs = dmalloc<double>(n);
+        c->ls = dmalloc<double>(n);
+        c->bs32 = dmalloc<float>(m);
+        c->cs32 = dmalloc<float>(n);
+        c->ls32 = dmalloc<float>(n);
+        c->aty_cur = dmalloc<double>(n);
+        c->aty_avg = dmalloc<double>(n);
+        c->ax_avg = dmalloc<double>(m);
+        c->ax_cur = dmalloc<double>(m);
+        c->xo = dmalloc<double>(n);
+        c->yo = dmalloc<double>(m);
+        c->rho = dmalloc<double>(m);
+        c->kap = dmalloc<double>(n);
+        c->partial = dmalloc<double>(2 * Q_NQ * kRedBlocks);
+        c->scal = dmalloc<double>(16);
+        c->log = dmalloc<double>(8 * (int64_t)c->log_cap);
     };
-    auto plan_a = plan(ta, m, R.a_rp, R.a_ci, fa);
-    auto plan_at = plan(tat, n, R.at_rp, R.at_ci, fat);
-    upload_csr(c, c->A, m, n, nnz, R.a_rp, R.a_ci, R.a_v, pa, R.a_cut, la, fa, std::move(plan_a));
-    upload_csr(c, c->At, n, m, nnz, R.at_rp, R.at_ci, R.at_v, pat, R.at_cut, lat, fat, std::move(plan_at));
-    // a small LP iterates in one workgroup unless row blocks, a layout or panels
-    // were asked for
-    const bool plain = c->small != 0 && !fa && !fat && !c->panels_a && !c->panels_at &&
-                       c->split_threshold == kSplitThreshold && c->split_chunk == kSplitChunk &&
-                       c->block_rows == kWG && c->stream_nt < 0;
-    auto longest = [](const std::vector<int64_t> &rp) {
-        int64_t k = 0;
-        for (size_t i = 1; i < rp.size(); ++i) k = std::max(k, rp[i] - rp[i - 1]);
-        return k;
-    };
-    const int64_t longest_a = plain ? longest(R.a_rp) : 0, longest_at = plain ? longest(R.at_rp) : 0;
-    c->small64 = plain && small_fits<double>(m, n, nnz, longest_a, longest_at);
-    c->small32 = plain && small_fits<float>(m, n, nnz, longest_a, longest_at);
-    if (c->small64 || c->small32) {
-        c->A.small = upload_small(build_small(m, n, R.a_rp.data(), R.a_ci.data()));
-        c->At.small = upload_small(build_small(n, m, R.at_rp.data(), R.at_ci.data()));
-    }
-    // one product buffer for the push passes of both sides
-    int64_t prods = 0;
-    for (DevCsr *M : {&c->A, &c->At})
-        if (M->bkt && M->bkt->items) prods = std::max(prods, 4 * M->bkt->quads);
-    if (prods) c->prod = dmalloc<double>(prods);
-    for (DevCsr *M : {&c->A, &c->At})
-        if (M->bkt) M->bkt->prod = c->prod;
-    std::vector<int32_t> ridx((size_t)nnz);
-    for (int64_t i = 0; i < m; ++i)
-        for (int64_t p = R.a_rp[i]; p < R.a_rp[i + 1]; ++p) ridx[p] = (int32_t)i;
-    c->perm = dmalloc<int32_t>(nnz);
-    c->rowidx = dmalloc<int32_t>(nnz);
-    c->apos = dmalloc<int32_t>(nnz);
-    c->pr = dmalloc<int32_t>(m);
-    c->pc = dmalloc<int32_t>(n);
-    if (nnz) {
-        HIPC(hipMemcpy(c->perm, R.perm.data(), nnz * sizeof(int32_t), hipMemcpyHostToDevice));
-        HIPC(hipMemcpy(c->rowidx, ridx.data(), nnz * sizeof(int32_t), hipMemcpyHostToDevice));
-        HIPC(hipMemcpy(c->apos, R.apos.data(), nnz * sizeof(int32_t), hipMemcpyHostToDevice));
-    }
-    HIPC(hipMemcpy(c->pr, R.pr.data(), m * sizeof(int32_t), hipMemcpyHostToDevice));
-    HIPC(hipMemcpy(c->pc, R.pc.data(), n * sizeof(int32_t), hipMemcpyHostToDevice));
-    if (ta && !c->A.bkt && !fa && nnz < kTileMin64) c->later[0] = {R.a_rp, R.a_ci};
-    if (tat && !c->At.bkt && !fat && nnz < kTileMin64) c->later[1] = {R.at_rp, R.at_ci};
-    c->tmp_m = dmalloc<double>(m);
-    c->tmp_n = dmalloc<double>(n);
-    c->b_orig = dmalloc<double>(m);
-    c->c_orig = dmalloc<double>(n);
-    vec_in(c, c->b_orig, b, true, mem);
-    vec_in(c, c->c_orig, cvec, false, mem);
-    c->has_l = lb != nullptr;
-    if (c->has_l) {
-        c->l_orig = dmalloc<double>(n);
-        vec_in(c, c->l_orig, lb, false, mem);
-    }
-    c->dr = dmalloc<double>(m);
-    c->dc = dmalloc<double>(n);
-    c->bs = dmalloc<double>(m);
-    c->cs = dmalloc<double>(n);
-    c->ls = dmalloc<double>(n);
-    c->bs32 = dmalloc<float>(m);
-    c->cs32 = dmalloc<float>(n);
-    c->ls32 = dmalloc<float>(n);
-    c->aty_cur = dmalloc<double>(n);
-    c->aty_avg = dmalloc<double>(n);
-    c->ax_avg = dmalloc<double>(m);
-    c->ax_cur = dmalloc<double>(m);
-    c->xo = dmalloc<double>(n);
-    c->yo = dmalloc<double>(m);
-    c->rho = dmalloc<double>(m);
-    c->kap = dmalloc<double>(n);
-    c->partial = dmalloc<double>(2 * Q_NQ * kRedBlocks);
-    c->scal = dmalloc<double>(16);
-    c->log = dmalloc<double>(8 * (int64_t)c->log_cap);
+    // without memory for buckets (up to 29 bytes a nonzero and side) the lean
+    // form may still fit
+    out_of_memory([&] { fill(false); }, [&] {
+        free_problem(c);
+        fill(true);
+    });
     // until configure: unit scaling so that pdhg_spmv works on A~ = A
     launch_fill(c->dr, 1.0, m, c->stream);
     launch_fill(c->dc, 1.0, n, c->stream);
