@@ -5,8 +5,8 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <future>
 #include <numeric>
-#include <thread>
 
 #include "internal.h"
 
@@ -314,6 +314,18 @@ HostBins build_row_blocks(int64_t rows, const int64_t *rp, int tile,
     return hb;
 }
 
+// fn(t) for every t below nt, on threads beside the caller's.  What one of them
+// throws (it may run out of memory) reaches the caller once all have ended, and
+// where no thread is to be had the caller does its share.
+template <class Fn>
+static void on_threads(int nt, Fn fn) {
+    std::vector<std::future<void>> th;
+    for (int t = 1; t < nt; ++t)
+        th.push_back(std::async(std::launch::async | std::launch::deferred, [&fn, t] { fn(t); }));
+    fn(0);
+    for (auto &t : th) t.get();
+}
+
 // Internal relabeling: rows of A and columns of A in order of decreasing
 // length (stable).  With rows sorted, the row-length bins of both A and A^T
 // are contiguous runs; with columns sorted, the most-referenced entries of x
@@ -418,10 +430,7 @@ Relabeled relabel(int64_t m, int64_t n, int64_t nnz, const int64_t *a_rp,
     if (nt == 1) {
         fill_rows(0, m);
     } else {
-        std::vector<std::thread> th;
-        for (int t = 0; t < nt; ++t)
-            th.emplace_back(fill_rows, m * t / nt, m * (t + 1) / nt);
-        for (auto &t : th) t.join();
+        on_threads(nt, [&](int t) { fill_rows(m * t / nt, m * (t + 1) / nt); });
     }
     R.at_rp.assign((size_t)n + 1, 0);
     for (int64_t j = 0; j < n; ++j)
@@ -650,10 +659,7 @@ static void sort_high(std::vector<uint64_t> &key, std::vector<uint64_t> &tmp) {
 template <class Fn>
 static void over_buckets(int64_t nb, int64_t nnz, Fn fn) {
     const int nt = (int)std::max<int64_t>(1, std::min<int64_t>(8, nnz / 100000));
-    std::vector<std::thread> th;
-    for (int t = 1; t < nt; ++t) th.emplace_back(fn, nb * t / nt, nb * (t + 1) / nt);
-    fn((int64_t)0, nb / nt);
-    for (auto &t : th) t.join();
+    on_threads(nt, [&](int t) { fn(nb * t / nt, nb * (t + 1) / nt); });
 }
 
 // Push buckets.  Columns are cut into blocks, as many as divide a round of one

@@ -1674,7 +1674,7 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
         auto plan = [&](bool on, int64_t rows, const std::vector<int64_t> &rp,
                         const std::vector<int32_t> &ci, bool force) {
             return on && (force || nnz >= kTileMin64)
-                       ? std::async(std::launch::async, [&rp, &ci, rows, force] {
+                       ? std::async(std::launch::async | std::launch::deferred, [&rp, &ci, rows, force] {
                              return build_tiles(rows, rp.data(), ci.data(), 1, force);
                          })
                        : std::future<HostBuckets>();

@@ -1,11 +1,14 @@
 // Plans of the bucketed SpMV layouts (push and tiles), executed on the host as
 // the kernels execute them and compared with the plain CSR product on integer
-// data (exact).  Every index is checked against its buffer.  Prints one line
-// per matrix and layout.
+// data (exact).  Every index is checked against its buffer.  Then the planners
+// run out of memory at every allocation.  Prints one line per matrix and layout.
 #include <algorithm>
+#include <atomic>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <new>
 #include <random>
 
 #include "internal.h"
@@ -19,6 +22,16 @@ using namespace pdhg;
             std::exit(1);                                          \
         }                                                          \
     } while (0)
+
+// Allocations fail once `left` are made, on whichever thread.
+static std::atomic<long> left{LONG_MAX};
+void *operator new(size_t n) {
+    void *p = left.fetch_sub(1) > 0 ? std::malloc(n ? n : 1) : nullptr;
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 namespace {
 
@@ -247,6 +260,32 @@ int main() {
         CHECK(y == ref && std::count(seen.begin(), seen.end(), 1) == nnz);
         std::printf("small m %ld n %ld nnz %ld kind %d lanes %d slots %d entries %zu\n",
                     (long)c.m, (long)c.n, (long)nnz, c.kind, S.G, S.K, S.src.size());
+    }
+    // without memory the planners throw bad_alloc, from their threads too
+    {
+        const Csr A = make(30000, 50000, 25, 0, g);
+        std::vector<int64_t> trp(A.n + 1, 0);
+        for (int32_t j : A.ci) ++trp[j + 1];
+        for (int64_t j = 0; j < A.n; ++j) trp[j + 1] += trp[j];
+        const std::vector<double> v(A.ci.size(), 1.0);
+        long thrown = 0;
+        for (int kind = 0; kind < 4; ++kind)
+            for (long k = 0;; ++k) {
+                bool ok = true;
+                left = k;
+                try {
+                    if (kind == 0) build_push(A.m, A.n, A.rp.data(), A.ci.data(), true);
+                    if (kind == 1) build_tiles(A.m, A.rp.data(), A.ci.data(), 1, true);
+                    if (kind >= 2)
+                        relabel(A.m, A.n, A.rp[A.m], A.rp.data(), A.ci.data(), v.data(), trp.data(), 1, 1, 0, kind - 2);
+                } catch (const std::bad_alloc &) {
+                    ok = false;
+                }
+                left = LONG_MAX;
+                if (ok) break;
+                ++thrown;
+            }
+        std::printf("memory %ld\n", thrown);
     }
     std::printf("done\n");
     return 0;
