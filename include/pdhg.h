@@ -554,7 +554,9 @@ int pdhg_cpu_stream_bw(int threads, int64_t bytes, int reps, double *gb_s);
 /* One binned SpMV on the device: which = 0: out (m) = A in (n);
  * which = 1: out (n) = A^T in (m).  scaled = 1 uses A~, 0 the loaded A.
  * precision selects the FP64 or the FP32 kernel (FP32 rounds `in` and the
- * values to float and accumulates in float; out is widened to double). */
+ * values to float and accumulates in float; out is widened to double).  The
+ * bits of a product depend on the problem, its scaling and the layouts of its
+ * load, not on other calls in between. */
 int pdhg_spmv(pdhg_ctx *ctx, int which, int scaled, int precision,
               const double *in, double *out, int mem);
 

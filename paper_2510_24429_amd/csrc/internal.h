@@ -313,7 +313,8 @@ void spmv_f64_normed(const DevCsr &M, const double *in, const double *norm2,
                      double *out, hipStream_t s);
 void spmv_f64_in32(const DevCsr &M, const double *vals, const float *in,
                    double *out, hipStream_t s);
-void spmv_f32(const DevCsr &M, const float *in, float *out, hipStream_t s);
+void spmv_f32(const DevCsr &M, const float *in, float *out, hipStream_t s,
+              bool buckets = true);
 
 template <typename T>
 void launch_primal(const DevCsr &At, const Iter<T> &v, bool has_l,

@@ -951,11 +951,11 @@ void run_bins(const DevCsr &M, Elem e, Epi p, hipStream_t s) {
 // values, or others).  The scaled values of an M with buckets run through
 // these, a panelled M's through the panel twin (XCD-dealt panel pass, in tiles
 // or row blocks, then the combine with the epilogue); any other value array
-// takes the plain bins.
+// takes the plain bins, and without `buckets` every one does.
 template <typename Acc, typename MT, typename VT, class Epi>
 void rb_spmv(const DevCsr &M, const MT *vals, const VT *in, Epi e,
-             hipStream_t s) {
-    if (M.bkt) {
+             hipStream_t s, bool buckets = true) {
+    if (buckets && M.bkt) {
         if constexpr (std::is_same<MT, double>::value) {
             if (vals == M.v64 && M.bkt->f64) return run_buckets<Acc>(M, (const MT *)M.bkt->v64, in, e, s);
         } else {
@@ -982,7 +982,7 @@ void rb_spmv(const DevCsr &M, const MT *vals, const VT *in, Epi e,
         q = M.q64;
     else
         q = M.q32;
-    if (M.pan->bkt && (M.pan->bkt->f64 || std::is_same<MT, float>::value)) {
+    if (buckets && M.pan->bkt && (M.pan->bkt->f64 || std::is_same<MT, float>::value)) {
         const MT *kv;
         if constexpr (std::is_same<MT, double>::value)
             kv = M.pan->bkt->v64;
@@ -1019,8 +1019,9 @@ void spmv_f64_in32(const DevCsr &M, const double *vals, const float *in,
     rb_spmv<double>(M, vals, in, StoreEpi<double, double>{out}, s);
 }
 
-void spmv_f32(const DevCsr &M, const float *in, float *out, hipStream_t s) {
-    rb_spmv<float>(M, (const float *)M.v32, in, StoreEpi<float, float>{out}, s);
+void spmv_f32(const DevCsr &M, const float *in, float *out, hipStream_t s,
+              bool buckets) {
+    rb_spmv<float>(M, (const float *)M.v32, in, StoreEpi<float, float>{out}, s, buckets);
 }
 
 // ============================================================ PDHG iteration

@@ -469,7 +469,9 @@ void spmv_staged(pdhg_ctx *c, int which, int scaled, int precision,
         // the FP32 kernel reads M.v32 (or its panel copy): put the loaded
         // values there for an unscaled product, restore the scaled ones after
         if (!scaled) put_f32_values(c, M, M.v_orig);
-        spmv_f32(M, st.i32, st.o32, c->stream);
+        // (tiles that only FP32 iterations use come with the first of them: a
+        // product does not depend on whether there was one)
+        spmv_f32(M, st.i32, st.o32, c->stream, !(M.bkt && !M.bkt->f64));
         launch_to_f64(st.dout, st.o32, M.rows, c->stream);
         if (!scaled) put_f32_values(c, M, M.v64);
     } else {

@@ -150,6 +150,32 @@ def test_bucketed_spmv_bitwise_on_integers(Solver, kind):
                     assert np.array_equal(got, ref[which]), (m, n, which, precision)
 
 
+@pytest.mark.parametrize("m,n,k", [(8000, 20_000, 5), (50_000, 100_000, 8), (600, 1500, 5)])
+def test_products_do_not_depend_on_earlier_calls(Solver, m, n, k):
+    """Products in either precision keep their bits over an FP32 configure and
+    an FP32 unrolled pass, which prepare what only FP32 iterations use (sides
+    of 50,000 to 550,000 nonzeros; one below and one above beside them)."""
+    lp = lpgen.planted_uniform(m=m, n=n, k=k, seed=3)
+    rng = np.random.default_rng(3)
+    vec = rng.standard_normal(lp.n), rng.standard_normal(lp.m)
+
+    def products(s):
+        return [f(which, vec[which], scaled=scaled, precision=precision)
+                for f in (s.spmv, s.spmv_noalloc) for which in (0, 1)
+                for scaled in (False, True) for precision in (0, 1)]
+
+    with Solver.from_lp(lp) as s:
+        s.configure(power_iters=5)
+        ref = products(s)
+        x, tape = s.unrolled_forward(3, 1, 0.1, 0.1, precision=1)
+        tape.free()
+        unrolled = products(s)
+        s.configure(power_iters=5, precision=1)
+        s.iterate(3)
+        for other in (unrolled, products(s)):
+            assert all(np.array_equal(a, b) for a, b in zip(ref, other))
+
+
 @pytest.mark.parametrize("kind", list(LAYOUT_KINDS))
 @pytest.mark.parametrize("variant", [0, 1])
 def test_iterates_match_in_bucketed_layouts(Solver, oracle, variant, kind):
