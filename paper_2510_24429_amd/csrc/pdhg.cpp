@@ -446,13 +446,9 @@ size_t spmv_noalloc_bytes(int64_t cols, int64_t rows, int precision) {
 // from the same source) rounded from `vals` (nnz, M's order).
 void put_f32_values(pdhg_ctx *c, const DevCsr &M, const double *vals) {
     launch_to_f32(M.v32, vals, M.nnz, c->stream);
-    if (M.bkt)
-        launch_gather_pad(M.bkt->v64, M.bkt->v32, vals, M.bkt->src, 4 * M.bkt->quads, c->stream);
     if (M.pan) {
         launch_gather(M.pan->v64, vals, M.pan_src, M.nnz, c->stream);
         launch_to_f32(M.pan->v32, M.pan->v64, M.nnz, c->stream);
-        if (M.pan->bkt)
-            launch_gather_pad(M.pan->bkt->v64, M.pan->bkt->v32, M.pan->v64, M.pan->bkt->src, 4 * M.pan->bkt->quads, c->stream);
     }
 }
 
@@ -469,9 +465,10 @@ void spmv_staged(pdhg_ctx *c, int which, int scaled, int precision,
         // the FP32 kernel reads M.v32 (or its panel copy): put the loaded
         // values there for an unscaled product, restore the scaled ones after
         if (!scaled) put_f32_values(c, M, M.v_orig);
-        // (tiles that only FP32 iterations use come with the first of them: a
-        // product does not depend on whether there was one)
-        spmv_f32(M, st.i32, st.o32, c->stream, !(M.bkt && !M.bkt->f64));
+        // (the loaded values have no copy in buckets; and tiles that only FP32
+        // iterations use come with the first of them: a product does not
+        // depend on whether there was one)
+        spmv_f32(M, st.i32, st.o32, c->stream, scaled && !(M.bkt && !M.bkt->f64));
         launch_to_f64(st.dout, st.o32, M.rows, c->stream);
         if (!scaled) put_f32_values(c, M, M.v64);
     } else {

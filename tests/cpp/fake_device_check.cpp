@@ -2,7 +2,8 @@
 // device memory is host memory, kernels do nothing.  Every device allocation
 // of a load, an FP32 configure and an unrolled pass fails in turn; whatever
 // happens, the calls return an error code and nothing stays allocated.  A load
-// that fits without the bucketed layouts never fails for want of theirs.
+// that fits without the bucketed layouts never fails for want of theirs.  And
+// products with the loaded values launch nothing for layouts they don't use.
 // Usage: fake_device_check LIBRARY.  Prints one line per case.
 #include <dlfcn.h>
 
@@ -72,7 +73,8 @@ int hipGetSymbolAddress(void **p, const void *) {
     static char dummy[256];
     return *p = dummy, 0;
 }
-int hipLaunchKernel(const void *, ...) { return 0; }
+static long launches = 0;
+int hipLaunchKernel(const void *, ...) { return ++launches, 0; }
 int __hipPushCallConfiguration(...) { return 0; }
 int __hipPopCallConfiguration(...) { return 0; }
 void **__hipRegisterFatBinary(const void *) {
@@ -108,6 +110,7 @@ LIB(pdhg_params_default);
 LIB(pdhg_unrolled_forward);
 LIB(pdhg_unrolled_backward);
 LIB(pdhg_tape_free);
+LIB(pdhg_spmv);
 #undef LIB
 
 struct Lp {
@@ -191,6 +194,7 @@ int main(int argc, char **argv) {
     LIB(pdhg_unrolled_forward);
     LIB(pdhg_unrolled_backward);
     LIB(pdhg_tape_free);
+    LIB(pdhg_spmv);
     struct Case {
         const char *name;
         int64_t m, n;
@@ -251,6 +255,26 @@ int main(int argc, char **argv) {
             CHECK(live.empty());
         }
         std::printf("%s: %zu bytes, %zu with its layouts\n", c.name, need[0], need[1]);
+    }
+    // products with the loaded values are as many launches in any layout
+    {
+        const Lp L = make_lp(3000, 7000, 5);
+        std::vector<double> in(L.n, 1.0), out(L.n);
+        long n[3];
+        for (int layout = 0; layout < 3; ++layout) {
+            pdhg_ctx *x = nullptr;
+            CHECK(p_pdhg_create(0, nullptr, &x) == PDHG_OK);
+            for (const char *key : {"layout_a", "layout_at"}) CHECK(p_pdhg_set_tuning(x, key, layout) == PDHG_OK);
+            CHECK(load(x, L) == PDHG_OK);
+            launches = 0;
+            for (int which = 0; which < 2; ++which)
+                for (int prec : {PDHG_FP64, PDHG_FP32})
+                    CHECK(p_pdhg_spmv(x, which, 0, prec, in.data(), out.data(), PDHG_MEM_HOST) == PDHG_OK);
+            n[layout] = launches;
+            p_pdhg_destroy(x);
+        }
+        CHECK(n[0] > 0 && n[1] == n[0] && n[2] == n[0]);
+        std::printf("loaded values: %ld launches\n", n[0]);
     }
     std::printf("done\n");
     return 0;

@@ -1,7 +1,8 @@
 """The library's host paths against a stand-in for the HIP runtime (device
 memory is host memory, kernels do nothing; tests/cpp/fake_device_check.cpp):
 every device allocation of a user's calls fails in turn, and no call leaves
-memory behind or fails for want of a bucketed layout.  No GPU."""
+memory behind or fails for want of a bucketed layout; products with the loaded
+values launch nothing for layouts they don't use.  No GPU."""
 import os
 import subprocess
 
@@ -21,4 +22,4 @@ def test_out_of_memory_paths(tmp_path):
                        capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
     lines = r.stdout.strip().splitlines()
-    assert lines[-1] == "done" and len(lines) == 6 + 4 + 1
+    assert lines[-1] == "done" and len(lines) == 6 + 4 + 1 + 1
