@@ -636,20 +636,26 @@ static void pack_buckets(HostBuckets &B, int64_t row0, int64_t row1,
     }
 }
 
-// Stable sort by the high 32 bits (below 2^31), in radix passes of 11 bits.
+// Stable sort by the high 32 bits (below 2^31), in radix passes of as many bits
+// as give each key a counter, at most 11 (always 11: a plan of 55,000 nonzeros in
+// buckets of 256 took 1.5 ms against 0.6).
 static void sort_high(std::vector<uint64_t> &key, std::vector<uint64_t> &tmp) {
-    constexpr int kBits = 11;
+    constexpr int kMost = 11;
     uint64_t lo = ~0ull, hi = 0;
     for (uint64_t k : key) {
         lo = std::min(lo, k >> 32);
         hi = std::max(hi, k >> 32);
     }
     tmp.resize(key.size());
-    for (int sh = 0; key.size() > 1 && sh < 32 && ((hi - lo) >> sh) != 0; sh += kBits) {
-        uint32_t at[(1 << kBits) + 1] = {0};
-        auto digit = [&](uint64_t k) { return (((k >> 32) - lo) >> sh) & ((1u << kBits) - 1); };
+    int bits = 4;
+    while (bits < kMost && (size_t)1 << bits < key.size()) ++bits;
+    const uint64_t mask = ((uint64_t)1 << bits) - 1;
+    for (int sh = 0; key.size() > 1 && sh < 32 && ((hi - lo) >> sh) != 0; sh += bits) {
+        uint32_t at[(1 << kMost) + 1];
+        std::fill(at, at + mask + 2, 0);
+        auto digit = [&](uint64_t k) { return (((k >> 32) - lo) >> sh) & mask; };
         for (uint64_t k : key) ++at[digit(k) + 1];
-        for (int d = 0; d < 1 << kBits; ++d) at[d + 1] += at[d];
+        for (uint64_t d = 0; d <= mask; ++d) at[d + 1] += at[d];
         for (uint64_t k : key) tmp[at[digit(k)]++] = k;
         key.swap(tmp);
     }
@@ -658,7 +664,7 @@ static void sort_high(std::vector<uint64_t> &key, std::vector<uint64_t> &tmp) {
 // fn(b0, b1) over the buckets [0, nb) on a few threads.
 template <class Fn>
 static void over_buckets(int64_t nb, int64_t nnz, Fn fn) {
-    const int nt = (int)std::max<int64_t>(1, std::min<int64_t>(8, nnz / 100000));
+    const int nt = (int)std::max<int64_t>(1, std::min<int64_t>(8, nnz / 50000));
     on_threads(nt, [&](int t) { fn(nb * t / nt, nb * (t + 1) / nt); });
 }
 
@@ -811,7 +817,7 @@ HostBuckets build_tiles(int64_t rows, const int64_t *rp, const int32_t *ci,
     B.quads = q;
     B.word.assign((size_t)(4 * q), 0);
     B.base.assign((size_t)(q / 64), 0);
-    B.src.assign((size_t)(4 * q), -1);
+    B.first.assign((size_t)(q / 64), 0);
     over_buckets(nb, nnz, [&](int64_t b0, int64_t b1) {
         std::vector<uint64_t> key, tmp;
         for (int64_t b = b0; b < b1; ++b) {
@@ -828,13 +834,15 @@ HostBuckets build_tiles(int64_t rows, const int64_t *rp, const int32_t *ci,
                 while (n < kGroup && t + n < nz && (int64_t)(key[t + n] >> 32) - c0 < kSpan) ++n;
                 // neighbours in the order on neighbouring lanes (L of them)
                 const int64_t L = t + n < nz ? 64 : (n + 3) / 4;
-                for (int64_t i = 0; i < 4 * L; ++i) {
-                    const uint64_t e = key[t + std::min(i, n - 1)];
-                    const int64_t o = 4 * (K.q1 + i % L) + i / L, p = (int64_t)(e & 0xffffffffu);
-                    B.word[o] = (int32_t)((uint32_t)((int64_t)(e >> 32) - c0) << kTilePos | (uint32_t)p);
-                    B.src[o] = (int32_t)(K.p0 + p);
-                }
+                int64_t i = t;
+                for (int64_t u = 0; u < 4; ++u)
+                    for (int64_t l = 0; l < L; ++l, ++i) {
+                        const uint64_t e = key[std::min(i, t + n - 1)];
+                        const int64_t o = 4 * (K.q1 + l) + u, p = (int64_t)(e & 0xffffffffu);
+                        B.word[o] = (int32_t)((uint32_t)((int64_t)(e >> 32) - c0) << kTilePos | (uint32_t)p);
+                    }
                 B.base[K.q1 / 64] = (int32_t)c0;
+                B.first[K.q1 / 64] = K.p0;
                 K.q1 += (int32_t)L;
                 t += n;
             }

@@ -115,11 +115,12 @@ struct HostBuckets {
     std::vector<uint16_t> col, pos;   // 4 * quads: column in its block (push
                                       // order), CSR position in its bucket
                                       // (kBktCap: padding)
-    std::vector<int32_t> src;         // 4 * quads: position in the CSR (-1: padding)
+    std::vector<int32_t> src;         // push: 4 * quads: position in the CSR (-1: padding)
     std::vector<int32_t> dest;        // quads: quad of the products
     std::vector<int32_t> word;        // tiles: 4 * quads positions and columns
                                       // (padding: the entry before it again)
-    std::vector<int32_t> base;        // tiles: quads / 64 bases
+    std::vector<int32_t> base, first; // tiles: per group of 64 quads its base and
+                                      // the CSR position that its tile starts at
 };
 // Unless forced, both stop at a fragmented matrix.
 HostBuckets build_push(int64_t rows, int64_t cols, const int64_t *rp,
@@ -134,13 +135,14 @@ struct DevBuckets {
     int width = 0, nitems = 0, nbuckets = 0, nsplit = 0;
     bool f64 = true;                  // FP64 products run here too
     int64_t quads = 0;
+    char *mem = nullptr;              // the allocation of all but the products
     PushItem *items = nullptr;
     Bucket *buckets = nullptr;
     SplitRow *split = nullptr;
     uint16_t *col = nullptr, *pos = nullptr;
     int32_t *src = nullptr, *dest = nullptr;
-    int32_t *word = nullptr, *base = nullptr;   // tiles (no push pass)
-    double *v64 = nullptr;            // scaled values in the order of src
+    int32_t *word = nullptr, *base = nullptr, *first = nullptr;   // tiles (no push pass)
+    double *v64 = nullptr;            // scaled values in the order of col or word (f64)
     float *v32 = nullptr;
     void *prod = nullptr;             // products of either precision, shared by
                                       // both sides (of the same stream)
@@ -426,9 +428,11 @@ void launch_permute(double *dst, const double *src, const int32_t *perm,
                     int64_t k, hipStream_t s);
 void launch_gather(double *dst, const double *src, const int32_t *idx,
                    int64_t k, hipStream_t s);
-// ... the same in FP64 and rounded to FP32, 0 where idx < 0
+// ... the same in FP64 (dst may be null) and rounded to FP32, 0 where idx < 0
 void launch_gather_pad(double *dst, float *dst32, const double *src,
                        const int32_t *idx, int64_t k, hipStream_t s);
+// The scaled values of M's buckets from M's.
+void launch_fill_buckets(const DevCsr &M, hipStream_t s);
 
 // Refinement (FP64): residual data of the correction LP and its update.
 void launch_refine_rhs(const double *bs, const double *ax, const double *cs,

@@ -2435,7 +2435,7 @@ __global__ __launch_bounds__(kWG) void k_gather_pad(
          i += (int64_t)gridDim.x * kWG) {
         const int p = idx[i];
         const double v = p < 0 ? 0.0 : src[p];
-        dst[i] = v;
+        if (dst) dst[i] = v;
         dst32[i] = (float)v;
     }
 }
@@ -2445,6 +2445,30 @@ void launch_gather_pad(double *dst, float *dst32, const double *src,
                        const int32_t *idx, int64_t k, hipStream_t s) {
     hipLaunchKernelGGL(k_gather_pad, dim3(grid_for(k, kWG, 16384)), dim3(kWG),
                        0, s, dst, dst32, src, idx, k);
+}
+
+// As k_gather_pad, of tiles: an entry's place in the CSR is its position in the
+// tile beyond the tile's first.
+static __global__ __launch_bounds__(kWG) void k_gather_tiles(
+    double *__restrict__ dst, float *__restrict__ dst32,
+    const double *__restrict__ src, const int32_t *__restrict__ word,
+    const int32_t *__restrict__ first, int64_t k) {
+    for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < k;
+         i += (int64_t)gridDim.x * kWG) {
+        const double v = src[first[i >> 8] + (word[i] & ((1 << kTilePos) - 1))];
+        if (dst) dst[i] = v;
+        dst32[i] = (float)v;
+    }
+}
+
+void launch_fill_buckets(const DevCsr &M, hipStream_t s) {
+    const DevBuckets &K = *M.bkt;
+    const int64_t k = 4 * K.quads;
+    if (K.word)
+        hipLaunchKernelGGL(k_gather_tiles, dim3(grid_for(k, kWG, 16384)), dim3(kWG),
+                           0, s, K.v64, K.v32, M.v64, K.word, K.first, k);
+    else
+        launch_gather_pad(K.v64, K.v32, M.v64, K.src, k, s);
 }
 
 void launch_gather(double *dst, const double *src, const int32_t *idx,

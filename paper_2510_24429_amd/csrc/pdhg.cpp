@@ -165,11 +165,8 @@ struct pdhg_ctx {
     DevCsr A, At;
     double *prod = nullptr;     // products of the push passes
     bool small64 = false, small32 = false;   // iterates in one workgroup
-    // sides whose tiles are planned at the first FP32 iteration (A, A^T)
-    struct {
-        std::vector<int64_t> rp;
-        std::vector<int32_t> ci;
-    } later[2];
+    // planned tiles that go to the device at the first FP32 iteration (A, A^T)
+    HostBuckets later[2];
     // internal relabeling (rows and columns by decreasing length)
     int32_t *pr = nullptr;      // internal row -> original row of A
     int32_t *pc = nullptr;      // internal column -> original column
@@ -494,19 +491,7 @@ std::vector<T> to_host(pdhg_ctx *c, const T *p, int64_t count, int mem) {
 }
 
 void free_buckets(DevBuckets *&k) {
-    if (!k) return;
-    dfree(k->items);
-    dfree(k->buckets);
-    dfree(k->split);
-    dfree(k->col);
-    dfree(k->pos);
-    dfree(k->src);
-    dfree(k->dest);
-    dfree(k->word);
-    dfree(k->base);
-    dfree(k->v64);
-    dfree(k->v32);
-    dfree(k->part);
+    if (k) dfree(k->mem);
     delete k;
     k = nullptr;
 }
@@ -654,16 +639,10 @@ void upload_bins(DevCsr &M, const HostBins &b64, const HostBins &b32) {
 // kernels' aligned 16-byte group loads stay inside the allocation.
 int64_t padded(int64_t nnz) { return ((nnz + 3) & ~(int64_t)3) + 4; }
 
-// A vector to a device array of its own.
-template <typename T>
-void upload(T *&d, const std::vector<T> &h) {
-    d = dmalloc<T>((int64_t)h.size());
-    if (!h.empty()) HIPC(hipMemcpy(d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
-}
-
 // Buckets or tiles of M to the device (their values are filled by
-// apply_scaling); none when their rows do not fill them.  What was allocated
-// when an exception leaves here belongs to M.
+// apply_scaling); none when their rows do not fill them.  One allocation, and
+// one copy where the plan is small: fourteen calls a side took as long as
+// planning 55,000 nonzeros.
 void upload_buckets(DevCsr &M, const HostBuckets &H, bool f64, bool force) {
     if (H.fragmented && !force) return;
     DevBuckets *K = M.bkt = new DevBuckets();
@@ -671,23 +650,50 @@ void upload_buckets(DevCsr &M, const HostBuckets &H, bool f64, bool force) {
     K->quads = H.quads;
     K->nbuckets = (int)H.buckets.size();
     K->nsplit = (int)H.splits.size();
-    upload(K->buckets, H.buckets);
-    upload(K->split, H.splits);
-    upload(K->src, H.src);
-    K->v64 = dmalloc<double>(4 * K->quads);
-    K->v32 = dmalloc<float>(4 * K->quads);
-    K->part = dmalloc<double>(H.parts);
-    if (!H.word.empty()) {
-        upload(K->word, H.word);
-        upload(K->base, H.base);
-    } else {
-        upload(K->pos, H.pos);
-        upload(K->items, H.items);
-        K->nitems = (int)H.items.size();
-        K->width = H.width;
-        upload(K->col, H.col);
-        upload(K->dest, H.dest);
+    K->nitems = (int)H.items.size();
+    K->width = H.width;
+    size_t bytes = 0;
+    std::vector<std::function<void(char *)>> place;
+    struct Copy {
+        size_t at, bytes;
+        const void *from;
+    };
+    std::vector<Copy> copies;
+    auto room = [&](auto *&p, size_t count) {
+        const size_t at = bytes;
+        place.push_back([&p, at](char *mem) { p = (std::remove_reference_t<decltype(p)>)(mem + at); });
+        bytes += (count * sizeof *p + 255) & ~(size_t)255;
+        return at;
+    };
+    auto plan = [&](auto *&p, const auto &h) {
+        if (!h.empty()) copies.push_back({room(p, h.size()), h.size() * sizeof *p, h.data()});
+    };
+    plan(K->buckets, H.buckets);
+    plan(K->split, H.splits);
+    plan(K->items, H.items);
+    plan(K->src, H.src);
+    plan(K->dest, H.dest);
+    plan(K->col, H.col);
+    plan(K->pos, H.pos);
+    plan(K->word, H.word);
+    plan(K->base, H.base);
+    plan(K->first, H.first);
+    const size_t planned = bytes;
+    if (f64) room(K->v64, 4 * (size_t)K->quads);
+    room(K->v32, 4 * (size_t)K->quads);
+    char *&part = (char *&)K->part;
+    room(part, (size_t)H.parts * sizeof(double));
+    K->mem = dmalloc<char>((int64_t)bytes);
+    for (auto &f : place) f(K->mem);
+    constexpr size_t kStaged = (size_t)1 << 20;
+    std::vector<char> h(planned <= kStaged ? planned : 0);
+    for (const Copy &k : copies) {
+        if (!h.empty())
+            std::memcpy(h.data() + k.at, k.from, k.bytes);
+        else
+            HIPC(hipMemcpy(K->mem + k.at, k.from, k.bytes, hipMemcpyHostToDevice));
     }
+    if (!h.empty()) HIPC(hipMemcpy(K->mem, h.data(), planned, hipMemcpyHostToDevice));
 }
 
 // The panel twin of M (P > 1): the stacked panel matrix with its own index
@@ -770,7 +776,7 @@ void upload_csr(pdhg_ctx *c, DevCsr &M, int64_t rows, int64_t cols,
                 int64_t nnz, const std::vector<int64_t> &rp,
                 const std::vector<int32_t> &ci, const std::vector<double> &v,
                 int P, const std::vector<int64_t> &cut, int layout,
-                bool force, std::future<HostBuckets> tiles) {
+                bool force, std::future<HostBuckets> *tiles) {
     M.rows = rows;
     M.cols = cols;
     M.nnz = nnz;
@@ -801,8 +807,8 @@ void upload_csr(pdhg_ctx *c, DevCsr &M, int64_t rows, int64_t cols,
         M.P = P;
     else if (P > 1)
         upload_panels(c, M, rp, ci, P, cut, layout, force);
-    else if (tiles.valid())
-        upload_buckets(M, tiles.get(), true, force);
+    else if (tiles && tiles->valid())
+        upload_buckets(M, tiles->get(), true, force);
     // stream the CSR non-temporally when the FP64 gather table each XCD
     // works on exceeds 3 MiB, so that streaming does not evict it from L2
     M.stream_nt = c->stream_nt >= 0 ? c->stream_nt
@@ -854,12 +860,12 @@ void apply_scaling(pdhg_ctx *c) {
         if (M->small)
             launch_gather_pad(M->small->v64, M->small->v32, M->v64, M->small->src, M->small->entries, c->stream);
         if (M->bkt)
-            launch_gather_pad(M->bkt->v64, M->bkt->v32, M->v64, M->bkt->src, 4 * M->bkt->quads, c->stream);
+            launch_fill_buckets(*M, c->stream);
         if (M->pan) {
             launch_gather(M->pan->v64, M->v64, M->pan_src, c->nnz, c->stream);
             launch_to_f32(M->pan->v32, M->pan->v64, c->nnz, c->stream);
             if (M->pan->bkt)
-                launch_gather_pad(M->pan->bkt->v64, M->pan->bkt->v32, M->pan->v64, M->pan->bkt->src, 4 * M->pan->bkt->quads, c->stream);
+                launch_fill_buckets(*M->pan, c->stream);
         }
     }
 }
@@ -868,15 +874,13 @@ void apply_scaling(pdhg_ctx *c) {
 // (without memory for them these products stay in row blocks).
 void ensure_f32_tiles(pdhg_ctx *c) {
     for (int k = 0; k < 2; ++k) {
-        auto &l = c->later[k];
-        if (l.rp.empty()) continue;
+        if (c->later[k].buckets.empty()) continue;
         DevCsr &M = k ? c->At : c->A;
-        out_of_memory([&] {
-            upload_buckets(M, build_tiles(M.rows, l.rp.data(), l.ci.data(), 1, false), false, false);
-        }, [&] { free_buckets(M.bkt); });
-        l = {};
+        out_of_memory([&] { upload_buckets(M, c->later[k], false, false); },
+                      [&] { free_buckets(M.bkt); });
+        c->later[k] = {};
         if (M.bkt)
-            launch_gather_pad(M.bkt->v64, M.bkt->v32, M.v64, M.bkt->src, 4 * M.bkt->quads, c->stream);
+            launch_fill_buckets(M, c->stream);
     }
 }
 
@@ -1667,12 +1671,14 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
         const int la = layout(c->layout_a, c->panels_a, m, n, pa);
         const int lat = layout(c->layout_at, c->panels_at, n, m, pat);
         const bool fa = c->layout_a != LAYOUT_CHOOSE, fat = c->layout_at != LAYOUT_CHOOSE;
-        // tiles of an unpanelled side: planned while the arrays are uploaded, or,
-        // where only FP32 products use them, kept for the first FP32 iteration
+        // tiles of an unpanelled side: planned while the arrays are uploaded;
+        // where only FP32 products use them, the plan waits for the first FP32
+        // iteration (made only then, a first FP32 configure of 480,000 nonzeros
+        // took 5.1 ms instead of 2.7, and 2.0 without tiles)
         const bool ta = la == LAYOUT_TILES && pa == 1, tat = lat == LAYOUT_TILES && pat == 1;
         auto plan = [&](bool on, int64_t rows, const std::vector<int64_t> &rp,
                         const std::vector<int32_t> &ci, bool force) {
-            return on && (force || nnz >= kTileMin64)
+            return on
                        ? std::async(std::launch::async | std::launch::deferred, [&rp, &ci, rows, force] {
                              return build_tiles(rows, rp.data(), ci.data(), 1, force);
                          })
@@ -1680,8 +1686,9 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
         };
         auto plan_a = plan(ta, m, R.a_rp, R.a_ci, fa);
         auto plan_at = plan(tat, n, R.at_rp, R.at_ci, fat);
-        upload_csr(c, c->A, m, n, nnz, R.a_rp, R.a_ci, R.a_v, pa, R.a_cut, la, fa, std::move(plan_a));
-        upload_csr(c, c->At, n, m, nnz, R.at_rp, R.at_ci, R.at_v, pat, R.at_cut, lat, fat, std::move(plan_at));
+        const bool now = nnz >= kTileMin64;
+        upload_csr(c, c->A, m, n, nnz, R.a_rp, R.a_ci, R.a_v, pa, R.a_cut, la, fa, now || fa ? &plan_a : nullptr);
+        upload_csr(c, c->At, n, m, nnz, R.at_rp, R.at_ci, R.at_v, pat, R.at_cut, lat, fat, now || fat ? &plan_at : nullptr);
         // a small LP iterates in one workgroup unless row blocks, a layout or panels
         // were asked for
         const bool plain = !lean && c->small != 0 && !fa && !fat && !c->panels_a &&
@@ -1721,8 +1728,6 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
         }
         HIPC(hipMemcpy(c->pr, R.pr.data(), m * sizeof(int32_t), hipMemcpyHostToDevice));
         HIPC(hipMemcpy(c->pc, R.pc.data(), n * sizeof(int32_t), hipMemcpyHostToDevice));
-        if (ta && !c->A.bkt && !fa && nnz < kTileMin64) c->later[0] = {R.a_rp, R.a_ci};
-        if (tat && !c->At.bkt && !fat && nnz < kTileMin64) c->later[1] = {R.at_rp, R.at_ci};
         c->tmp_m = dmalloc<double>(m);
         c->tmp_n = dmalloc<double>(n);
         c->b_orig = dmalloc<double>(m);
@@ -1753,6 +1758,12 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
         c->partial = dmalloc<double>(2 * Q_NQ * kRedBlocks);
         c->scal = dmalloc<double>(16);
         c->log = dmalloc<double>(8 * (int64_t)c->log_cap);
+        for (int k = 0; k < 2; ++k) {
+            auto &p = k ? plan_at : plan_a;
+            if (!p.valid()) continue;
+            c->later[k] = p.get();
+            if (c->later[k].fragmented) c->later[k] = {};
+        }
     };
     // without memory for buckets (up to 29 bytes a nonzero and side) the lean
     // form may still fit

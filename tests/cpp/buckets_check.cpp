@@ -188,8 +188,13 @@ int main() {
             const HostBuckets B = build_tiles(c.m, S.rp.data(), S.ci.data(), P, true);
             std::vector<double> part(B.parts, NAN), ys(P * c.m, NAN), y(c.m, 0.0);
             std::vector<char> seen(nnz, 0);
-            CHECK((int64_t)B.word.size() == 4 * B.quads && B.src.size() == B.word.size() &&
-                  64 * (int64_t)B.base.size() == B.quads);
+            CHECK((int64_t)B.word.size() == 4 * B.quads && B.src.empty() &&
+                  64 * (int64_t)B.base.size() == B.quads && B.first.size() == B.base.size());
+            // the values of every entry, padding too, come from a nonzero
+            for (int64_t e = 0; e < 4 * B.quads; ++e) {
+                const int64_t p = B.first[e / 256] + (B.word[e] & ((1 << kTilePos) - 1));
+                CHECK(p >= 0 && p < nnz);
+            }
             for (size_t w = 0; w < B.buckets.size(); ++w) {
                 const Bucket &b = B.buckets[w];
                 if (b.r0 == b.r1) continue;
@@ -197,10 +202,9 @@ int main() {
                 CHECK(b.p1 - b.p0 <= kTileCap && b.q0 >= 0 && b.q0 % 64 == 0 && b.q0 <= b.q1 && b.q1 <= B.quads);
                 std::vector<double> s(kTileCap + 1, NAN);
                 for (int64_t e = 4 * (int64_t)b.q0; e < 4 * (int64_t)b.q1; ++e) {
-                    const int32_t p = B.src[e];
-                    const int64_t pos = B.word[e] & ((1 << kTilePos) - 1),
+                    const int64_t pos = B.word[e] & ((1 << kTilePos) - 1), p = b.p0 + pos,
                                   col = B.base[e / 256] + (int64_t)((uint32_t)B.word[e] >> kTilePos);
-                    CHECK(p >= 0 && p < nnz && S.ci[p] == col && pos == p - b.p0);
+                    CHECK(B.first[e / 256] == b.p0 && p < b.p1 && S.ci[p] == col);
                     seen[p] = 1;
                     s[pos] = v[S.src[p]] * x[col];
                 }
