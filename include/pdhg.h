@@ -455,7 +455,9 @@ int pdhg_refine_log(pdhg_ctx *ctx, double *out, int cap, int *count);
 /* Run K plain PDHG steps (no restarts, no averaging) on the configured,
  * scaled problem with fixed tau, sigma, from unscaled (x0, y0) (NULL: zero),
  * in `precision`; write unscaled x_K (n).  Stores (x, y, A~x) every
- * ckpt_every steps in a new tape (*tape; free with pdhg_tape_free). */
+ * ckpt_every steps in a new tape (*tape; free with pdhg_tape_free), or, where
+ * they take at most 256 MiB (tuning key "tape_bytes") and the memory is there,
+ * (x, y) of all K + 1 iterates, so that the reverse pass repeats no step. */
 int pdhg_unrolled_forward(pdhg_ctx *ctx, int K, int ckpt_every,
                           int precision, double tau, double sigma,
                           const double *x0, const double *y0, double *xK,
@@ -464,8 +466,10 @@ int pdhg_unrolled_forward(pdhg_ctx *ctx, int K, int ckpt_every,
  * dL/dc (n), dL/db (m) and dL/dA.values (nnz, A's CSR order), with the
  * scaling factors held fixed.  Segments between checkpoints are recomputed
  * with the forward kernels, which are deterministic, so the result does not
- * depend on ckpt_every (a tape whose K + 1 iterates take at most 256 MiB, or
- * what the tuning key "tape_bytes" says, keeps all of them instead).  The projection's subgradient is 0 at a tie.
+ * depend on ckpt_every, nor on whether the tape holds all iterates.  The
+ * projection's subgradient is 0 at a tie.  Beside the tape the pass takes 128
+ * bytes per row and column, up to 24 per nonzero, and the iterates of a
+ * segment.
  * The replay reads the context's current problem data, so a tape is valid
  * only until the next pdhg_load, pdhg_configure, pdhg_set_values or
  * pdhg_set_rhs_obj (with data) on its context: after any of them this call
@@ -591,9 +595,11 @@ int pdhg_spmv_noalloc(pdhg_ctx *ctx, int which, int scaled, int precision,
  *      which a panel count other than 0 also selects under -1;
  *  "tape_bytes": pdhg_unrolled_forward keeps the iterates of every step when
  *      they take at most this many bytes (256 MiB by default; at once, not
- *      at the next load), and the checkpoints otherwise.  The memory of a
- *      freed tape and of a finished pass, each up to as many bytes, stays with
- *      the context for the next ones until a load, pdhg_destroy or this key;
+ *      at the next load), and the checkpoints that its caller asked for
+ *      otherwise (0: always).  The memory of a freed tape and of a finished
+ *      pass, each up to as many bytes, stays with the context for the next
+ *      ones until a load, pdhg_destroy, this key, or until another call of the
+ *      context needs it;
  *  "small": 1 (default) lets an LP of at most about 4,000 columns, 2,000 rows
  *      and 25,000 nonzeros iterate in one workgroup when none of the layout,
  *      panel, split, stream or block keys is set; 0 does not;

@@ -167,6 +167,7 @@ struct pdhg_ctx {
     bool small64 = false, small32 = false;   // iterates in one workgroup
     // planned tiles that go to the device at the first FP32 iteration (A, A^T)
     HostBuckets later[2];
+    bool asked[2] = {false, false};     // layouts that the tuning asked for
     // internal relabeling (rows and columns by decreasing length)
     int32_t *pr = nullptr;      // internal row -> original row of A
     int32_t *pc = nullptr;      // internal column -> original column
@@ -336,8 +337,28 @@ void kept_free(pdhg_ctx *c) {
     }
 }
 
-// The smallest kept block of `bytes` or more, or a new one.
-Block block_take(pdhg_ctx *c, size_t bytes) {
+void drop_buckets(pdhg_ctx *c);
+
+// An allocation beside a loaded problem: what the context keeps for speed
+// alone, first the blocks of earlier passes, then the layouts that pdhg_load
+// chose, makes room for it.
+template <typename T>
+T *dmalloc(pdhg_ctx *c, int64_t count) {
+    T *p = nullptr;
+    auto get = [&] { p = dmalloc<T>(count); };
+    out_of_memory(get, [&] {
+        kept_free(c);
+        out_of_memory(get, [&] {
+            drop_buckets(c);
+            get();
+        });
+    });
+    return p;
+}
+
+// The smallest kept block of `bytes` or more, or a new one (optional: without
+// dropping buckets for it; *fresh is set then).
+Block block_take(pdhg_ctx *c, size_t bytes, bool optional = false, bool *fresh = nullptr) {
     {
         std::lock_guard<std::mutex> lk(c->kept_mu);
         Block *best = nullptr;
@@ -351,11 +372,16 @@ Block block_take(pdhg_ctx *c, size_t bytes) {
     }
     Block b;
     b.bytes = bytes;
-    if (hipMalloc((void **)&b.p, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        kept_free(c);
-        hip_check(hipMalloc((void **)&b.p, bytes), "hipMalloc");
+    if (fresh) *fresh = true;
+    if (!optional) {
+        b.p = dmalloc<char>(c, (int64_t)bytes);
+        return b;
     }
+    auto get = [&] { b.p = dmalloc<char>((int64_t)bytes); };
+    out_of_memory(get, [&] {
+        kept_free(c);
+        get();
+    });
     return b;
 }
 
@@ -376,8 +402,7 @@ struct WorkBlock {
     pdhg_ctx *c;
     Block b;
     char *at;
-    WorkBlock(pdhg_ctx *ctx, std::initializer_list<size_t> arrays)
-        : c(ctx), b(block_take(ctx, cut_bytes(arrays))), at(b.p) {}
+    WorkBlock(pdhg_ctx *ctx, size_t bytes) : c(ctx), b(block_take(ctx, bytes)), at(b.p) {}
     ~WorkBlock() { block_give(c, b); }
     WorkBlock(const WorkBlock &) = delete;
     WorkBlock &operator=(const WorkBlock &) = delete;
@@ -496,16 +521,19 @@ void free_buckets(DevBuckets *&k) {
     k = nullptr;
 }
 
+void free_small(DevSmall *&k) {
+    if (k) dfree(k->base);
+    delete k;
+    k = nullptr;
+}
+
 void free_csr(DevCsr &M) {
     if (M.pan) {
         free_csr(*M.pan);
         delete M.pan;
     }
     free_buckets(M.bkt);
-    if (DevSmall *k = M.small) {
-        dfree(k->base);
-        delete k;
-    }
+    free_small(M.small);
     dfree(M.pan_src);
     dfree(M.pan_mask);
     dfree(M.q64);
@@ -524,6 +552,30 @@ void free_csr(DevCsr &M) {
     M = DevCsr();
 }
 
+void invalidate_graph(pdhg_ctx *c) {
+    if (c->graph) (void)hipGraphExecDestroy(c->graph);
+    c->graph = nullptr;
+    c->graph_key.clear();
+}
+
+// Sides whose layout pdhg_load chose go on in row blocks (those of a pushed
+// side without panels), small LPs in two launches an iteration.
+void drop_buckets(pdhg_ctx *c) {
+    if (!c->loaded) return;
+    (void)hipStreamSynchronize(c->stream);
+    for (int k = 0; k < 2; ++k) {
+        DevCsr &M = k ? c->At : c->A;
+        c->later[k] = {};
+        free_small(M.small);
+        if (c->asked[k]) continue;
+        free_buckets(M.bkt);
+        if (M.pan) free_buckets(M.pan->bkt);
+    }
+    c->small64 = c->small32 = false;
+    if (!(c->A.bkt && c->A.bkt->prod) && !(c->At.bkt && c->At.bkt->prod)) dfree(c->prod);
+    invalidate_graph(c);
+}
+
 template <typename T>
 void free_iter(Iter<T> &v) {
     dfree(v.x);
@@ -534,12 +586,6 @@ void free_iter(Iter<T> &v) {
     dfree(v.yl);
     dfree(v.ax);
     dfree(v.ax0);
-}
-
-void invalidate_graph(pdhg_ctx *c) {
-    if (c->graph) (void)hipGraphExecDestroy(c->graph);
-    c->graph = nullptr;
-    c->graph_key.clear();
 }
 
 void free_problem(pdhg_ctx *c) {
@@ -816,16 +862,10 @@ void upload_csr(pdhg_ctx *c, DevCsr &M, int64_t rows, int64_t cols,
 }
 
 template <typename T>
-void alloc_iter(Iter<T> &v, int64_t m, int64_t n) {
+void alloc_iter(pdhg_ctx *c, Iter<T> &v) {
     if (v.x) return;
-    v.x = dmalloc<T>(n);
-    v.xbar = dmalloc<T>(n);
-    v.xl = dmalloc<T>(n);
-    v.y = dmalloc<T>(m);
-    v.ybar = dmalloc<T>(m);
-    v.yl = dmalloc<T>(m);
-    v.ax = dmalloc<T>(m);
-    v.ax0 = dmalloc<T>(m);
+    for (T **p : {&v.x, &v.xbar, &v.xl}) *p = dmalloc<T>(c, c->n);
+    for (T **p : {&v.y, &v.ybar, &v.yl, &v.ax, &v.ax0}) *p = dmalloc<T>(c, c->m);
 }
 
 template <typename T>
@@ -1686,6 +1726,8 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
         };
         auto plan_a = plan(ta, m, R.a_rp, R.a_ci, fa);
         auto plan_at = plan(tat, n, R.at_rp, R.at_ci, fat);
+        c->asked[0] = fa;
+        c->asked[1] = fat;
         const bool now = nnz >= kTileMin64;
         upload_csr(c, c->A, m, n, nnz, R.a_rp, R.a_ci, R.a_v, pa, R.a_cut, la, fa, now || fa ? &plan_a : nullptr);
         upload_csr(c, c->At, n, m, nnz, R.at_rp, R.at_ci, R.at_v, pat, R.at_cut, lat, fat, now || fat ? &plan_at : nullptr);
@@ -1712,7 +1754,7 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
             if (M->bkt && M->bkt->items) prods = std::max(prods, 4 * M->bkt->quads);
         if (prods) c->prod = dmalloc<double>(prods);
         for (DevCsr *M : {&c->A, &c->At})
-            if (M->bkt) M->bkt->prod = c->prod;
+            if (M->bkt && M->bkt->items) M->bkt->prod = c->prod;
         std::vector<int32_t> ridx((size_t)nnz);
         for (int64_t i = 0; i < m; ++i)
             for (int64_t p = R.a_rp[i]; p < R.a_rp[i + 1]; ++p) ridx[p] = (int32_t)i;
@@ -1787,7 +1829,7 @@ int pdhg_set_values(pdhg_ctx *c, const double *a_v, int mem) {
     if (!c->loaded) return fail(c, PDHG_E_STATE, "no problem loaded");
     if (!a_v && c->nnz) return fail(c, PDHG_E_ARG, "null values");
     ++c->data_gen;
-    WorkBlock k(c, {(size_t)c->nnz * 8});
+    WorkBlock k(c, cut_bytes({(size_t)c->nnz * 8}));
     double *tmp = (double *)k.b.p;
     copy_in(c, tmp, a_v, c->nnz, mem);
     launch_gather(c->A.v_orig, tmp, c->apos, c->nnz, c->stream);
@@ -1854,10 +1896,10 @@ void polish(pdhg_ctx *c) {
     if (budget < E) budget = E;
     const bool h = f32(c);
     if (h) {
-        alloc_iter(c->bk32, c->m, c->n);
+        alloc_iter(c, c->bk32);
         copy_iter(c, c->bk32, c->v32);
     } else {
-        alloc_iter(c->bk64, c->m, c->n);
+        alloc_iter(c, c->bk64);
         copy_iter(c, c->bk64, c->v64);
     }
     const pdhg_params saved = c->params;
@@ -2014,24 +2056,24 @@ int pdhg_configure(pdhg_ctx *c, const pdhg_params *p) {
     c->prec = p->precision;
     if (c->prec == PDHG_FP32) {
         ensure_f32_tiles(c);
-        alloc_iter(c->v32, c->m, c->n);
+        alloc_iter(c, c->v32);
     } else {
-        alloc_iter(c->v64, c->m, c->n);
+        alloc_iter(c, c->v64);
     }
     if (c->n_slots < (int)c->levels.size()) {
         dfree(c->slots);
         c->n_slots = (int)c->levels.size();
-        c->slots = dmalloc<double>((int64_t)c->n_slots * (2 * c->n + c->m));
+        c->slots = dmalloc<double>(c, (int64_t)c->n_slots * (2 * c->n + c->m));
     }
     if (p->polish && !c->pol_x) {
-        c->pol_x = dmalloc<double>(c->n);
-        c->pol_y = dmalloc<double>(c->m);
-        c->pol_xp = dmalloc<double>(c->n);
-        c->pol_yd = dmalloc<double>(c->m);
-        c->zero_n = dmalloc<double>(c->n);
-        c->zero_m = dmalloc<double>(c->m);
-        c->zero_n32 = dmalloc<float>(c->n);
-        c->zero_m32 = dmalloc<float>(c->m);
+        c->pol_x = dmalloc<double>(c, c->n);
+        c->pol_y = dmalloc<double>(c, c->m);
+        c->pol_xp = dmalloc<double>(c, c->n);
+        c->pol_yd = dmalloc<double>(c, c->m);
+        c->zero_n = dmalloc<double>(c, c->n);
+        c->zero_m = dmalloc<double>(c, c->m);
+        c->zero_n32 = dmalloc<float>(c, c->n);
+        c->zero_m32 = dmalloc<float>(c, c->m);
         launch_fill(c->zero_n, 0.0, c->n, c->stream);
         launch_fill(c->zero_m, 0.0, c->m, c->stream);
         launch_fill32(c->zero_n32, 0.0f, c->n, c->stream);
@@ -2248,11 +2290,11 @@ int pdhg_spmv(pdhg_ctx *c, int which, int scaled, int precision,
     if (which < 0 || which > 1 || !in || !out) return fail(c, PDHG_E_ARG, "bad argument");
     const DevCsr &M = which ? c->At : c->A;
     SpmvStage st;
-    st.din = dmalloc<double>(M.cols);
-    st.dout = dmalloc<double>(M.rows);
+    st.din = dmalloc<double>(c, M.cols);
+    st.dout = dmalloc<double>(c, M.rows);
     if (precision == PDHG_FP32) {
-        st.i32 = dmalloc<float>(M.cols);
-        st.o32 = dmalloc<float>(M.rows);
+        st.i32 = dmalloc<float>(c, M.cols);
+        st.o32 = dmalloc<float>(c, M.rows);
     }
     try {
         spmv_staged(c, which, scaled, precision, in, out, mem, st);
@@ -2584,21 +2626,21 @@ void refine_impl(pdhg_ctx *c, const pdhg_refine_params &R, pdhg_refine_info *inf
     const bool in64 = R.inner_precision == PDHG_FP64;
     const double *ls = c->has_l ? c->ls : nullptr;
     const double t0 = now_s();
-    alloc_iter(c->v32, c->m, c->n);
+    alloc_iter(c, c->v32);
     if (!c->bh) {
-        c->bh = dmalloc<double>(c->m);
-        c->ch = dmalloc<double>(c->n);
-        c->lh = dmalloc<double>(c->n);
-        c->bh32 = dmalloc<float>(c->m);
-        c->ch32 = dmalloc<float>(c->n);
-        c->lh32 = dmalloc<float>(c->n);
+        c->bh = dmalloc<double>(c, c->m);
+        c->ch = dmalloc<double>(c, c->n);
+        c->lh = dmalloc<double>(c, c->n);
+        c->bh32 = dmalloc<float>(c, c->m);
+        c->ch32 = dmalloc<float>(c, c->n);
+        c->lh32 = dmalloc<float>(c, c->n);
     }
-    double *xo = dmalloc<double>(c->n), *yo = dmalloc<double>(c->m);
+    double *xo = dmalloc<double>(c, c->n), *yo = dmalloc<double>(c, c->m);
     launch_fill(xo, 0.0, c->n, c->stream);
     launch_fill(yo, 0.0, c->m, c->stream);
     if (!c->ref_bx) {
-        c->ref_bx = dmalloc<double>(c->n);
-        c->ref_by = dmalloc<double>(c->m);
+        c->ref_bx = dmalloc<double>(c, c->n);
+        c->ref_by = dmalloc<double>(c, c->m);
     }
     const pdhg_params saved = c->params;
     const std::vector<double> saved_levels = c->levels;
@@ -2722,7 +2764,7 @@ void refine_impl(pdhg_ctx *c, const pdhg_refine_params &R, pdhg_refine_info *inf
             c->act_has_l = true;
             if (in64) {
                 c->prec = PDHG_FP64;
-                alloc_iter(c->v64, c->m, c->n);
+                alloc_iter(c, c->v64);
                 c->v64.bs = c->bh;
                 c->v64.cs = c->ch;
                 c->v64.ls = c->lh;
@@ -2832,7 +2874,7 @@ void refine_impl(pdhg_ctx *c, const pdhg_refine_params &R, pdhg_refine_info *inf
     configure_solve_state(c);
     invalidate_graph(c);
     c->prec = PDHG_FP64;
-    alloc_iter(c->v64, c->m, c->n);
+    alloc_iter(c, c->v64);
     zero_iter(c, c->v64);
     HIPC(hipMemcpyAsync(c->v64.x, xo, c->n * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
     HIPC(hipMemcpyAsync(c->v64.y, yo, c->m * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
@@ -2935,17 +2977,49 @@ void plain_steps(pdhg_ctx *c, Iter<T> w, T *X, T *Y, T *ax, int count, const Sta
     }
 }
 
+// Workspace of a reverse pass: gradients that start at zero, then the rest.
+template <typename T>
+size_t adj_zero_bytes(pdhg_ctx *c) {
+    const size_t nb = c->n * sizeof(T), mb = c->m * sizeof(T);
+    return cut_bytes({mb, nb, mb, c->nnz * sizeof(T)});
+}
+template <typename T>
+size_t adj_bytes(pdhg_ctx *c, const pdhg_tape *tp) {
+    constexpr size_t S = kAdjSteps<T>;
+    const size_t nb = c->n * sizeof(T), mb = c->m * sizeof(T), wk = tp->full ? 0 : tp->ck + 1,
+                 most = 8 * (size_t)std::max(c->nnz, std::max(c->n, c->m));
+    return cut_bytes({adj_zero_bytes<T>(c), nb, nb, mb * 2 * S, nb * 2 * S, most, most,
+                      wk * nb, wk * mb, tp->full ? 0 : mb});
+}
+
 template <typename T>
 void unrolled_forward_T(pdhg_ctx *c, pdhg_tape *tp, const double *x0,
                         const double *y0, double *xK, int mem) {
     const int64_t m = c->m, n = c->n;
     // a tape of few bytes keeps the iterates of every step, so that its reverse
     // pass recomputes nothing
+    // (while the memory is there)
     tp->full = ((int64_t)tp->K + 1) <= c->tape_bytes / ((m + n) * (int64_t)sizeof(T));
+    const size_t nb = n * sizeof(T), mb = m * sizeof(T);
+    auto tape_of = [&](size_t cks) {
+        return cut_bytes({cks * nb, cks * mb, tp->full ? 0 : cks * mb, sizeof(State)});
+    };
+    if (tp->full)
+        out_of_memory([&] {
+            bool fresh = false;
+            tp->mem = block_take(c, tape_of(tp->K + 1), true, &fresh);
+            // the reverse pass has to find its memory too (kept for it, or, too
+            // large to keep, tried once)
+            const size_t back = adj_bytes<T>(c, tp);
+            if (fresh || back <= (size_t)c->tape_bytes) block_give(c, block_take(c, back, true));
+        }, [&] {
+            tp->full = false;
+            dfree(tp->mem.p);
+            kept_free(c);
+        });
+    if (!tp->full) tp->mem = block_take(c, tape_of(tp->nseg));
     // iterates of a checkpoint segment at a time, the last of them its result
     const int seg = tp->full ? tp->K : 1, nck = tp->full ? tp->K + 1 : tp->nseg;
-    const size_t nb = n * sizeof(T), mb = m * sizeof(T);
-    tp->mem = block_take(c, cut_bytes({nck * nb, nck * mb, tp->full ? 0 : nck * mb, sizeof(State)}));
     char *at = tp->mem.p;
     tp->ckx = cut<T>(at, nck * n);
     tp->cky = cut<T>(at, nck * m);
@@ -2960,7 +3034,7 @@ void unrolled_forward_T(pdhg_ctx *c, pdhg_tape *tp, const double *x0,
     Iter<T> w = plain_data<T>(c);
     T *X = (T *)tp->ckx, *Y = (T *)tp->cky;
     const int wk = tp->full ? 0 : seg + 1;
-    WorkBlock k(c, {mb, wk * nb, wk * mb});
+    WorkBlock k(c, cut_bytes({mb, wk * nb, wk * mb}));
     T *ax = cut<T>(k.at, m);
     if (!tp->full) {
         X = cut<T>(k.at, wk * n);
@@ -3039,14 +3113,13 @@ void unrolled_backward_T(pdhg_tape *tp, const double *gxK, double *gc,
     pdhg_ctx *c = tp->ctx;
     const int64_t m = c->m, n = c->n, nnz = c->nnz;
     const int ck = tp->full ? tp->K : tp->ck, nseg = tp->full ? 1 : tp->nseg;
-    const bool small = sizeof(T) == 8 ? c->small64 : c->small32;
     constexpr int S = kAdjSteps<T>;
     T *X = (T *)tp->ckx, *Y = (T *)tp->cky, *axw = nullptr;
-    const size_t nb = n * sizeof(T), mb = m * sizeof(T), wk = tp->full ? 0 : ck + 1;
-    const size_t zero = cut_bytes({mb, nb, mb, nnz * sizeof(T)});
+    const int64_t wk = tp->full ? 0 : ck + 1;
+    const size_t zero = adj_zero_bytes<T>(c);
     const int64_t most = std::max(nnz, std::max(n, m));
-    WorkBlock k(c, {zero, nb, nb, mb * 2 * S, nb * 2 * S, (size_t)most * 8, (size_t)most * 8,
-                    wk * nb, wk * mb, tp->full ? 0 : mb});
+    WorkBlock k(c, adj_bytes<T>(c, tp));
+    const bool small = sizeof(T) == 8 ? c->small64 : c->small32;
     AdjVecs<T> v;
     v.gy = cut<T>(k.at, m);
     T *gcs = v.gc = cut<T>(k.at, n), *gbs = v.gb = cut<T>(k.at, m), *gAs = cut<T>(k.at, nnz);

@@ -227,34 +227,53 @@ int main(int argc, char **argv) {
         }
         std::printf("%s: %ld allocations, %ld failed a call\n", c.name, tried, failed);
     }
-    // the memory that row blocks need is enough, whatever the sizes choose
+    // the memory that row blocks and checkpoints need is enough, whatever the
+    // sizes choose, for a whole program
     fail_at = -1;
     for (const Case &c : {Case{"one workgroup", 300, 700, 5, {}}, Case{"FP32 tiles", 8000, 20000, 5, {}},
                           Case{"tiles", 90000, 200000, 4, {}}, Case{"pushed", 500000, 1100000, 2, {}}}) {
         const Lp L = make_lp(c.m, c.n, c.k);
-        budget = SIZE_MAX;
-        size_t need[2];
-        for (int k = 0; k < 2; ++k) {
-            pdhg_ctx *x = nullptr;
-            peak = 0;
-            CHECK(p_pdhg_create(0, nullptr, &x) == PDHG_OK);
-            if (k == 0)
-                for (const char *key : {"layout_a", "layout_at", "small"}) CHECK(p_pdhg_set_tuning(x, key, 0) == PDHG_OK);
-            CHECK(load(x, L) == PDHG_OK);
-            need[k] = peak;
-            p_pdhg_destroy(x);
-        }
-        // (FP32 tiles of few nonzeros come later)
-        CHECK(need[1] >= need[0]);
-        for (size_t part = 0; part <= 4; ++part) {
-            budget = need[0] + (need[1] - need[0]) * part / 4;
+        auto calls_of = [&](const Tuning &tuning) {
             pdhg_ctx *x = nullptr;
             CHECK(p_pdhg_create(0, nullptr, &x) == PDHG_OK);
+            for (auto &t : tuning) CHECK(p_pdhg_set_tuning(x, t.first, t.second) == PDHG_OK);
             CHECK(load(x, L) == PDHG_OK);
+            pdhg_params p;
+            p_pdhg_params_default(&p);
+            const double level = 1e-3;
+            std::vector<double> in(L.n), gb(L.m), gA(L.v.size()), out(L.n);
+            for (int prec : {PDHG_FP64, PDHG_FP32}) {
+                p.precision = prec;
+                p.levels = &level;
+                p.n_levels = 1;
+                CHECK(p_pdhg_configure(x, &p) == PDHG_OK);
+                for (int K : {3, 40}) {
+                    pdhg_tape *tape = nullptr;
+                    CHECK(p_pdhg_unrolled_forward(x, K, 2, prec, 0.1, 0.1, nullptr, nullptr, in.data(), PDHG_MEM_HOST, &tape) == PDHG_OK);
+                    CHECK(p_pdhg_unrolled_backward(tape, in.data(), out.data(), gb.data(), gA.data(), PDHG_MEM_HOST) == PDHG_OK);
+                    p_pdhg_tape_free(tape);
+                }
+            }
+            p.polish = 1;
+            CHECK(p_pdhg_configure(x, &p) == PDHG_OK);
+            CHECK(p_pdhg_spmv(x, 0, 1, PDHG_FP32, in.data(), out.data(), PDHG_MEM_HOST) == PDHG_OK);
             p_pdhg_destroy(x);
             CHECK(live.empty());
+        };
+        budget = SIZE_MAX;
+        peak = 0;
+        calls_of({{"layout_a", 0}, {"layout_at", 0}, {"small", 0}, {"tape_bytes", 0}});
+        const size_t least = peak;
+        peak = 0;
+        calls_of({});
+        const size_t most = peak;
+        CHECK(most > least);
+        for (size_t part = 0; part <= 8; ++part) {
+            budget = least + (most - least) * part / 8;
+            calls_of({});
         }
-        std::printf("%s: %zu bytes, %zu with its layouts\n", c.name, need[0], need[1]);
+        budget = SIZE_MAX;
+        std::printf("%s: %zu bytes, %zu as chosen\n", c.name, least, most);
     }
     // products with the loaded values are as many launches in any layout
     {
