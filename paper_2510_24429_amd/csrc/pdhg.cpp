@@ -356,6 +356,22 @@ T *dmalloc(pdhg_ctx *c, int64_t count) {
     return p;
 }
 
+// Arrays that belong together: all of them or, when an exception leaves, none.
+template <typename T>
+struct Want {
+    T *&p;
+    int64_t count;
+};
+template <typename... T>
+void dmalloc_all(pdhg_ctx *c, Want<T>... w) {
+    try {
+        ((w.p = dmalloc<T>(c, w.count)), ...);
+    } catch (...) {
+        (dfree(w.p), ...);
+        throw;
+    }
+}
+
 // The smallest kept block of `bytes` or more, or a new one (optional: without
 // dropping buckets for it; *fresh is set then).
 Block block_take(pdhg_ctx *c, size_t bytes, bool optional = false, bool *fresh = nullptr) {
@@ -864,8 +880,9 @@ void upload_csr(pdhg_ctx *c, DevCsr &M, int64_t rows, int64_t cols,
 template <typename T>
 void alloc_iter(pdhg_ctx *c, Iter<T> &v) {
     if (v.x) return;
-    for (T **p : {&v.x, &v.xbar, &v.xl}) *p = dmalloc<T>(c, c->n);
-    for (T **p : {&v.y, &v.ybar, &v.yl, &v.ax, &v.ax0}) *p = dmalloc<T>(c, c->m);
+    using W = Want<T>;
+    dmalloc_all(c, W{v.x, c->n}, W{v.xbar, c->n}, W{v.xl, c->n}, W{v.y, c->m}, W{v.ybar, c->m},
+                W{v.yl, c->m}, W{v.ax, c->m}, W{v.ax0, c->m});
 }
 
 template <typename T>
@@ -2048,6 +2065,7 @@ int pdhg_configure(pdhg_ctx *c, const pdhg_params *p) {
         if (!(p->levels[i] < p->levels[i - 1]))
             return fail(c, PDHG_E_ARG, "snapshot levels must be strictly descending");
     const double t0 = now_s();
+    c->configured = false;      // until everything below has succeeded
     invalidate_graph(c);
     ++c->data_gen;              // new scaling: earlier tapes are stale
     c->params = *p;
@@ -2062,18 +2080,16 @@ int pdhg_configure(pdhg_ctx *c, const pdhg_params *p) {
     }
     if (c->n_slots < (int)c->levels.size()) {
         dfree(c->slots);
+        c->n_slots = 0;
+        c->slots = dmalloc<double>(c, (int64_t)c->levels.size() * (2 * c->n + c->m));
         c->n_slots = (int)c->levels.size();
-        c->slots = dmalloc<double>(c, (int64_t)c->n_slots * (2 * c->n + c->m));
     }
     if (p->polish && !c->pol_x) {
-        c->pol_x = dmalloc<double>(c, c->n);
-        c->pol_y = dmalloc<double>(c, c->m);
-        c->pol_xp = dmalloc<double>(c, c->n);
-        c->pol_yd = dmalloc<double>(c, c->m);
-        c->zero_n = dmalloc<double>(c, c->n);
-        c->zero_m = dmalloc<double>(c, c->m);
-        c->zero_n32 = dmalloc<float>(c, c->n);
-        c->zero_m32 = dmalloc<float>(c, c->m);
+        using D = Want<double>;
+        using F = Want<float>;
+        dmalloc_all(c, D{c->pol_x, c->n}, D{c->pol_y, c->m}, D{c->pol_xp, c->n},
+                    D{c->pol_yd, c->m}, D{c->zero_n, c->n}, D{c->zero_m, c->m},
+                    F{c->zero_n32, c->n}, F{c->zero_m32, c->m});
         launch_fill(c->zero_n, 0.0, c->n, c->stream);
         launch_fill(c->zero_m, 0.0, c->m, c->stream);
         launch_fill32(c->zero_n32, 0.0f, c->n, c->stream);
@@ -2290,13 +2306,13 @@ int pdhg_spmv(pdhg_ctx *c, int which, int scaled, int precision,
     if (which < 0 || which > 1 || !in || !out) return fail(c, PDHG_E_ARG, "bad argument");
     const DevCsr &M = which ? c->At : c->A;
     SpmvStage st;
-    st.din = dmalloc<double>(c, M.cols);
-    st.dout = dmalloc<double>(c, M.rows);
-    if (precision == PDHG_FP32) {
-        st.i32 = dmalloc<float>(c, M.cols);
-        st.o32 = dmalloc<float>(c, M.rows);
-    }
     try {
+        st.din = dmalloc<double>(c, M.cols);
+        st.dout = dmalloc<double>(c, M.rows);
+        if (precision == PDHG_FP32) {
+            st.i32 = dmalloc<float>(c, M.cols);
+            st.o32 = dmalloc<float>(c, M.rows);
+        }
         spmv_staged(c, which, scaled, precision, in, out, mem, st);
     } catch (...) {
         (void)hipStreamSynchronize(c->stream);
@@ -2627,21 +2643,20 @@ void refine_impl(pdhg_ctx *c, const pdhg_refine_params &R, pdhg_refine_info *inf
     const double *ls = c->has_l ? c->ls : nullptr;
     const double t0 = now_s();
     alloc_iter(c, c->v32);
-    if (!c->bh) {
-        c->bh = dmalloc<double>(c, c->m);
-        c->ch = dmalloc<double>(c, c->n);
-        c->lh = dmalloc<double>(c, c->n);
-        c->bh32 = dmalloc<float>(c, c->m);
-        c->ch32 = dmalloc<float>(c, c->n);
-        c->lh32 = dmalloc<float>(c, c->n);
-    }
-    double *xo = dmalloc<double>(c, c->n), *yo = dmalloc<double>(c, c->m);
+    using D = Want<double>;
+    using F = Want<float>;
+    if (!c->bh)
+        dmalloc_all(c, D{c->bh, c->m}, D{c->ch, c->n}, D{c->lh, c->n}, F{c->bh32, c->m},
+                    F{c->ch32, c->n}, F{c->lh32, c->n});
+    if (!c->ref_bx) dmalloc_all(c, D{c->ref_bx, c->n}, D{c->ref_by, c->m});
+    struct Outer {
+        double *x = nullptr, *y = nullptr;
+        ~Outer() { dfree(x), dfree(y); }
+    } outer;
+    dmalloc_all(c, D{outer.x, c->n}, D{outer.y, c->m});
+    double *const xo = outer.x, *const yo = outer.y;
     launch_fill(xo, 0.0, c->n, c->stream);
     launch_fill(yo, 0.0, c->m, c->stream);
-    if (!c->ref_bx) {
-        c->ref_bx = dmalloc<double>(c, c->n);
-        c->ref_by = dmalloc<double>(c, c->m);
-    }
     const pdhg_params saved = c->params;
     const std::vector<double> saved_levels = c->levels;
     const int saved_slots = c->n_slots;
@@ -2863,8 +2878,6 @@ void refine_impl(pdhg_ctx *c, const pdhg_refine_params &R, pdhg_refine_info *inf
         c->levels = saved_levels;
         c->n_slots = saved_slots;
         configure_solve_state(c);
-        dfree(xo);
-        dfree(yo);
         throw;
     }
     // the refined iterate becomes the current FP64 iterate
@@ -2873,8 +2886,8 @@ void refine_impl(pdhg_ctx *c, const pdhg_refine_params &R, pdhg_refine_info *inf
     c->n_slots = saved_slots;
     configure_solve_state(c);
     invalidate_graph(c);
-    c->prec = PDHG_FP64;
     alloc_iter(c, c->v64);
+    c->prec = PDHG_FP64;
     zero_iter(c, c->v64);
     HIPC(hipMemcpyAsync(c->v64.x, xo, c->n * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
     HIPC(hipMemcpyAsync(c->v64.y, yo, c->m * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
@@ -2892,8 +2905,6 @@ void refine_impl(pdhg_ctx *c, const pdhg_refine_params &R, pdhg_refine_info *inf
     c->k_host = inner_total;
     c->status = s.status;
     c->initial_done = true;
-    dfree(xo);
-    dfree(yo);
     if (info) {
         std::memset(info, 0, sizeof *info);
         info->status = status;

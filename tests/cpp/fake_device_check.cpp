@@ -2,12 +2,14 @@
 // device memory is host memory, kernels do nothing.  Every device allocation
 // of a load, an FP32 configure and an unrolled pass fails in turn; whatever
 // happens, the calls return an error code and nothing stays allocated.  A load
-// that fits without the bucketed layouts never fails for want of theirs.  And
+// that fits without the bucketed layouts never fails for want of theirs, and
+// what a failed call left out the next one allocates.  And
 // products with the loaded values launch nothing for layouts they don't use.
 // Usage: fake_device_check LIBRARY.  Prints one line per case.
 #include <dlfcn.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -33,12 +35,14 @@ static std::mutex mu;
 static std::map<void *, size_t> live;       // device allocations
 static size_t used = 0, peak = 0, budget = SIZE_MAX;
 static long calls = 0, fail_at = -1;        // fail the fail_at-th allocation
+static long from = LONG_MAX;                // ... all from this one on
 
 extern "C" {
 int hipMalloc(void **p, size_t n) {
     std::lock_guard<std::mutex> lk(mu);
     *p = nullptr;
-    if (calls++ == fail_at || n > budget || used > budget - n) return 2;
+    const long k = calls++;
+    if (k == fail_at || k >= from || n > budget || used > budget - n) return 2;
     *p = std::calloc(1, n);
     live[*p] = n;
     used += n;
@@ -111,6 +115,7 @@ LIB(pdhg_unrolled_forward);
 LIB(pdhg_unrolled_backward);
 LIB(pdhg_tape_free);
 LIB(pdhg_spmv);
+LIB(pdhg_iterate);
 #undef LIB
 
 struct Lp {
@@ -195,6 +200,7 @@ int main(int argc, char **argv) {
     LIB(pdhg_unrolled_backward);
     LIB(pdhg_tape_free);
     LIB(pdhg_spmv);
+    LIB(pdhg_iterate);
     struct Case {
         const char *name;
         int64_t m, n;
@@ -274,6 +280,46 @@ int main(int argc, char **argv) {
         }
         budget = SIZE_MAX;
         std::printf("%s: %zu bytes, %zu as chosen\n", c.name, least, most);
+    }
+    // calls that ran out of memory leave nothing half done: no solve runs before
+    // a configure has succeeded, and the next one finds or makes every array
+    {
+        const Lp L = make_lp(3000, 7000, 5);
+        const double level = 1e-3;
+        size_t full = 0;
+        long tried = 0;
+        for (long k = -1;; ++k, ++tried) {
+            pdhg_ctx *x = nullptr;
+            CHECK(p_pdhg_create(0, nullptr, &x) == PDHG_OK);
+            for (const char *key : {"layout_a", "layout_at"}) CHECK(p_pdhg_set_tuning(x, key, 1) == PDHG_OK);
+            CHECK(load(x, L) == PDHG_OK);
+            pdhg_params p;
+            p_pdhg_params_default(&p);
+            CHECK(p_pdhg_configure(x, &p) == PDHG_OK);
+            p.precision = PDHG_FP32;
+            p.levels = &level;
+            p.n_levels = 1;
+            p.polish = 1;
+            calls = 0;
+            from = k < 0 ? LONG_MAX : k;
+            const int rc = p_pdhg_configure(x, &p);
+            const bool reached = calls > k;
+            std::vector<double> in(L.n, 1.0), out(L.n);
+            const int rs = p_pdhg_spmv(x, 1, 1, PDHG_FP32, in.data(), out.data(), PDHG_MEM_HOST);
+            from = LONG_MAX;
+            CHECK(rs == PDHG_OK || rs == PDHG_E_OOM);
+            if (rc != PDHG_OK) {
+                int status = 0;
+                CHECK(rc == PDHG_E_OOM && p_pdhg_iterate(x, 1, &status) == PDHG_E_STATE);
+            }
+            CHECK(p_pdhg_configure(x, &p) == PDHG_OK);
+            if (k < 0) full = used;
+            CHECK(used == full);
+            p_pdhg_destroy(x);
+            CHECK(live.empty());
+            if (k >= 0 && !reached) break;
+        }
+        std::printf("half a configure: %ld allocations\n", tried);
     }
     // products with the loaded values are as many launches in any layout
     {

@@ -1,8 +1,9 @@
 """The library's host paths against a stand-in for the HIP runtime (device
 memory is host memory, kernels do nothing; tests/cpp/fake_device_check.cpp):
 every device allocation of a user's calls fails in turn, and no call leaves
-memory behind or fails for want of a bucketed layout; products with the loaded
-values launch nothing for layouts they don't use.  No GPU."""
+memory behind, leaves things half done or fails for want of a bucketed layout;
+products with the loaded values launch nothing for layouts they don't use.  No
+GPU."""
 import os
 import subprocess
 
@@ -22,4 +23,4 @@ def test_out_of_memory_paths(tmp_path):
                        capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
     lines = r.stdout.strip().splitlines()
-    assert lines[-1] == "done" and len(lines) == 6 + 4 + 1 + 1
+    assert lines[-1] == "done" and len(lines) == 6 + 4 + 1 + 1 + 1
