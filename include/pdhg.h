@@ -600,9 +600,12 @@ int pdhg_spmv_noalloc(pdhg_ctx *ctx, int which, int scaled, int precision,
  *      pass, each up to as many bytes, stays with the context for the next
  *      ones until a load, pdhg_destroy, this key, or until another call of the
  *      context needs it;
- *  "small": 1 (default) lets an LP of at most about 4,000 columns, 2,000 rows
- *      and 25,000 nonzeros iterate in one workgroup when none of the layout,
- *      panel, split, stream or block keys is set; 0 does not;
+ *  "small": 1 (default) lets an LP of at most 4,096 columns, 2,048 rows and
+ *      24,576 nonzeros (FP64; FP32: 40,960) iterate in one workgroup when none
+ *      of the layout, panel, split, stream or block keys is set and no row
+ *      (column) holds more than 48 nonzeros for each of its lanes: the largest
+ *      power of two up to 64 that times the rows (columns) is at most 1,024,
+ *      or 1; 0 does not;
  *  "split_threshold": nnz above which a row is split over several
  *      workgroups; "split_chunk": nnz per split part;
  *  "panels_a", "panels_at": column panels (1, 2, 4 or 8; 0 = chosen from
@@ -669,8 +672,11 @@ int pdhg_gather_probe(pdhg_ctx *ctx, int64_t table_entries, int precision,
                       double *gathers_per_s);
 
 /* Enable (1) or disable (0) HIP-event timing of every iteration-kernel
- * launch (batches then run without graphs).  pdhg_kernel_times fills up to
- * cap records and sets *count; reset clears the records. */
+ * launch (batches then run without graphs).  An LP that iterates in one
+ * workgroup (tuning key "small") runs its halves as launches of their own
+ * meanwhile, so that they can be timed: its iterates then round differently,
+ * and the times are not those of its usual kernel.  pdhg_kernel_times fills up
+ * to cap records and sets *count; reset clears the records. */
 int pdhg_profile(pdhg_ctx *ctx, int enable);
 int pdhg_kernel_times(pdhg_ctx *ctx, pdhg_kernel_time *out, int cap,
                       int *count, int reset);
