@@ -575,7 +575,6 @@ __global__ __launch_bounds__(kWG) void k_panel_combine(
 // start at any element.)
 typedef unsigned short v2us __attribute__((ext_vector_type(2)));
 typedef unsigned short v4us __attribute__((ext_vector_type(4)));
-typedef int v2i __attribute__((ext_vector_type(2)));
 template <typename T>
 struct UnitOf;
 template <>
@@ -584,7 +583,6 @@ struct UnitOf<double> {
     using V = v2d;
     using Any = double __attribute__((ext_vector_type(2), aligned(8)));
     using H = v2us;
-    using I = v2i;
 };
 template <>
 struct UnitOf<float> {
@@ -592,7 +590,6 @@ struct UnitOf<float> {
     using V = v4f;
     using Any = float __attribute__((ext_vector_type(4), aligned(4)));
     using H = v4us;
-    using I = v4i;
 };
 
 // Push pass: each workgroup multiplies the quads of its item with their column
