@@ -921,22 +921,37 @@ HostSmall build_small(int64_t rows, int64_t cols, const int64_t *rp,
 //   ... dual, 5.6 MB:                         89 | 65 | 67;  63 | 41 | 40
 //   multicommodity primal, 14.6M, 10.8 MB:   134 | 117 | 120;  98 | 73 | 71
 //   ... dual, 40 MB in 8 panels:             145 | 141 | 100; 100 | 98 | 58
-//   840k-column one, dual, 2.4M, 6.7 MB:      30 | 25 | 26;  21 | 19 | 18
-//   ... primal, 1.9 MB:                       23 | 19 | 28;  21 | 14 | 19
+//   840k-column one, primal, 2.4M, 1.9 MB:    23 | 19 | 28;  21 | 14 | 19
 //   600k x 200k dual, 2.4M, 4.8 MB:           28 | 21 | 26;  21 | 17 | 18
 //   power-law 300k dual, 2.8M, 2.4 MB:        21 | 16 | 26;  18 | 13 | 19
 //   400k x 160k dual, 1.2M, 3.2 MB:           16 | 14 | 18;  14 | 12 | 13
 //   2M x 1M dual, 24M, 16 MB:                199 | 165 | 148; 151 | 115 | 83
 //   ... primal, 8 MB:                        200 | 166 | 143; 151 | 118 | 83
-//   coupled dual, 55M, 80 MB in 8 panels:    708 | 563 | 420; 431 | 406 | 212
-//   ... 110M, 160 MB:                       1764 |  -  |  985; 1260 | - | 547
-// (the last two with tiles of 16,384 nonzeros and 48-bit entries).
+//   coupled dual, 55M, 80 MB in 8 panels:    709 | 550 | 420; 427 | 390 | 210
+//   ... primal, 20 MB in 4 panels:           643 | 580 | 421; 487 | 394 | 214
+//   ... dual, 110M, 160 MB in 8 panels:     1740 | 1469 | 982; 1250 | 971 | 540
+//   ... primal, 40 MB in 4 panels:          1599 | 1246 | 1005; 1038 | 865 | 547
+// and panelled sides of uniform LPs, the second of a multicommodity one
+// (nonzeros, MB a panel, nonzeros a stacked
+// row):
+//   2.2M, 4.20,  5.5:  30 | 24 | 24; 24 | 19 | 17    5.0M, 3.81, 12.5:  47 | 40 | 39; 41 | 28 | 26
+//   2.4M, 3.35,  4.5:  30 | 25 | 26; 21 | 19 | 18    5.2M, 2.48,  3.3:  42 | 43 | 41; 36 | 30 | 26
+//   3.3M, 4.20,  5.5:  38 | 30 | 30; 33 | 23 | 21    5.6M, 2.67, 11.7:  40 | 40 | 41; 38 | 27 | 26
+//   3.9M, 2.48,  9.8:  32 | 28 | 30; 30 | 21 | 21    7.5M, 2.38,  6.3:  62 | 52 | 52; 46 | 33 | 33
+//   4.0M, 1.91, 10.0:  32 | 27 | 31; 30 | 20 | 22    8.4M, 2.29, 10.5:  58 | 51 | 57; 49 | 32 | 36
+//   4.8M, 2.29,  4.8:  37 | 32 | 40; 35 | 24 | 26    9.6M, 2.29,  6.0:  76 | 61 | 66; 55 | 36 | 40
+//   5.0M, 2.38, 10.4:  38 | 38 | 39; 36 | 27 | 27   10.4M, 2.48,  3.7:  93 | 83 | 69; 64 | 50 | 42
+//   7.0M, 3.81, 11.7:  62 | 49 | 50; 49 | 34 | 31   11.6M, 2.77,  9.7:  92 | 78 | 74; 66 | 51 | 45
+//   7.7M, 4.20,  7.7:  73 | 56 | 53; 53 | 37 | 33   23.2M, 2.77, 11.6: 173 | 137 | 139; 145 | 98 | 80
+// So panels take tiles up to 2.5 MB and from four nonzeros a stacked row on, and
+// below 2M nonzeros, where the alternative is row blocks, up to what an
+// unpanelled side takes.
 int choose_layout(int64_t rows, int64_t cols, int64_t nnz, int P) {
     constexpr double kMiB = 1048576.0;
     const double panel = 8.0 * (double)cols / P;
     if (nnz < kTileMin32) return LAYOUT_ROWS;
-    if (panel <= (P == 1 || nnz < 6000000 ? 5.5 : 2.25) * kMiB &&
-        (P == 1 || nnz >= 8 * (int64_t)P * rows))
+    if (panel <= (P == 1 || nnz < 2000000 ? 5.5 : 2.5) * kMiB &&
+        (P == 1 || nnz >= 4 * (int64_t)P * rows))
         return LAYOUT_TILES;
     // runs of eight nonzeros or more (41M columns)
     const bool runs = (cols + kBktCols - 1) / kBktCols <= kBktCap / 8;
