@@ -150,6 +150,57 @@ def test_bucketed_spmv_bitwise_on_integers(Solver, kind):
                     assert np.array_equal(got, ref[which]), (m, n, which, precision)
 
 
+def _many_buckets_lp():
+    """10M nonzeros in rows of 0 to 3, of 400 to 1,100 and of 17,000 to 33,000
+    entries, in turns: 820 buckets for 256 workgroups, one of few long rows after
+    one of thousands of short ones, split rows between them, and some 10,000
+    quads to an item of the push pass, which takes 2,048 (FP64) or 4,096 (FP32)
+    at a time."""
+    rng = np.random.default_rng(6)
+    n, lens = 33_000, []
+    for _ in range(30):
+        lens += [rng.integers(0, 4, 10_000), rng.integers(400, 1101, 400), rng.integers(17_000, n + 1, 1)]
+    lens = np.concatenate(lens)
+    m = lens.size
+    step = rng.integers(1, np.maximum((n - 1) // np.maximum(lens, 1), 1) + 1)
+    start = rng.integers(0, n - np.maximum(lens - 1, 0) * step)
+    rows = np.repeat(np.arange(m), lens)
+    k = np.arange(rows.size) - np.repeat(np.cumsum(lens) - lens, lens)
+    cols = start[rows] + k * step[rows]
+    vals = rng.integers(1, 4, rows.size) * rng.choice([-1.0, 1.0], rows.size)
+    return lpgen.from_coo(m, n, rows, cols, vals, np.ones(m), np.ones(n)), rows, cols, vals
+
+
+@pytest.mark.timeout(300)
+def test_pushed_products_through_whole_rounds(Solver):
+    """The loops of both push kernels that a matrix of millions of nonzeros
+    reaches: products equal numpy's exactly on integers, and Halpern steps the
+    row blocks'."""
+    lp, rows, cols, vals = _many_buckets_lp()
+    rng = np.random.default_rng(7)
+    x, y = rng.integers(-3, 4, lp.n).astype(float), rng.integers(-3, 4, lp.m).astype(float)
+    ref = (np.bincount(rows, weights=vals * x[cols], minlength=lp.m),
+           np.bincount(cols, weights=vals * y[rows], minlength=lp.n))
+    out = {}
+    for layout in (2, 0):
+        # (rows and columns in the given order)
+        with Solver.from_lp(lp, tuning={"layout_a": layout, "layout_at": layout,
+                                        "sort_rows": 0, "sort_cols": 0}) as s:
+            for precision in (0, 1):
+                for which, vec in ((0, x), (1, y)):
+                    for _ in range(2):
+                        got = s.spmv(which, vec, scaled=True, precision=precision)
+                        assert np.array_equal(got, ref[which]), (layout, which, precision)
+            for precision in (0, 1):
+                s.configure(precision=precision, variant=1, eta=0.05)
+                s.set_iterate(np.abs(x), y)
+                s.iterate(3)
+                out[layout, precision] = s.get_iterate()
+    for precision, tol in ((0, 1e-12), (1, 1e-4)):
+        for a, b in zip(out[2, precision], out[0, precision]):
+            assert err(a, b) <= tol
+
+
 @pytest.mark.parametrize("m,n,k", [(8000, 20_000, 5), (50_000, 100_000, 8), (600, 1500, 5)])
 def test_products_do_not_depend_on_earlier_calls(Solver, m, n, k):
     """Products in either precision keep their bits over an FP32 configure and
