@@ -182,7 +182,11 @@ struct pdhg_ctx {
     int panels_a = 0, panels_at = 0;    // column panels per side; 0 = choose
     int layout_a = LAYOUT_CHOOSE, layout_at = LAYOUT_CHOOSE;   // per side
     int small = 1;                      // small LPs iterate in one workgroup
-    int64_t tape_bytes = (int64_t)256 << 20;    // tapes up to this keep every step
+    // Tapes up to this keep every step.  A bound on memory (a thousandth of the
+    // GPU's), not on what pays: a forward and a reverse pass are 1.3 to 1.7 times
+    // as fast with whole tapes of 2 MB to 1.1 GB (800k nonzeros, 200 steps, FP64,
+    // 230 MB: 9.75 ms with checkpoints 20 apart, 6.59 without).
+    int64_t tape_bytes = (int64_t)256 << 20;
     int stream_nt = -1;                 // streamed-load kind; -1 = choose
     int sort_rows = -1, sort_cols = -1; // length sort of rows / columns; -1 = by skew
     int block_rows = kWG;               // row cap of multi-row blocks; 0 = tile
