@@ -772,26 +772,16 @@ __device__ __forceinline__ void bkt_fill(const Units &units,
 // further from 64 bits.)
 template <typename Acc>
 __device__ __forceinline__ Acc lane_sum(const Acc *s, int p, int p1, int G) {
-    Acc t = (Acc)0;
-    if (p + 7 * G < p1) {
-        double t0 = 0.0, t1 = 0.0;
-        auto eight = [&] {
-            Acc a[8];
+    double t = 0.0;
+    for (; p + 7 * G < p1; p += 8 * G) {
+        Acc a[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = s[p + u * G];
-            p += 8 * G;
-            return (double)(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
-        };
-        while (p + 15 * G < p1) {
-            t0 += eight();
-            t1 += eight();
-        }
-        if (p + 7 * G < p1) t0 += eight();
-        for (; p < p1; p += G) t += s[p];
-        return (Acc)((t0 + t1) + (double)t);
+        for (int u = 0; u < 8; ++u) a[u] = s[p + u * G];
+        t += (double)(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
     }
-    for (; p < p1; p += G) t += s[p];
-    return t;
+    Acc r = (Acc)0;
+    for (; p < p1; p += G) r += s[p];
+    return (Acc)(t + (double)r);
 }
 
 // Sum pass: a bucket's products go to their CSR positions in LDS, then a
