@@ -932,10 +932,9 @@ HostSmall build_small(int64_t rows, int64_t cols, const int64_t *rp,
 //   ... dual, 110M, 160 MB in 8 panels:     1740 | 1469 | 982; 1250 | 971 | 540
 //   ... primal, 40 MB in 4 panels:          1599 | 1246 | 1005; 1038 | 865 | 547
 // and panelled sides of uniform LPs, the second of a multicommodity one
-// (nonzeros, MB a panel, nonzeros a stacked
-// row):
+// (nonzeros, MB a panel, nonzeros a stacked row):
 //   2.2M, 4.20,  5.5:  30 | 24 | 24; 24 | 19 | 17    5.0M, 3.81, 12.5:  47 | 40 | 39; 41 | 28 | 26
-//   2.4M, 3.35,  4.5:  30 | 25 | 26; 21 | 19 | 18    5.2M, 2.48,  3.3:  42 | 43 | 41; 36 | 30 | 26
+//   2.4M, 3.35,  5.1:  30 | 25 | 26; 21 | 19 | 18    5.2M, 2.48,  3.3:  42 | 43 | 41; 36 | 30 | 26
 //   3.3M, 4.20,  5.5:  38 | 30 | 30; 33 | 23 | 21    5.6M, 2.67, 11.7:  40 | 40 | 41; 38 | 27 | 26
 //   3.9M, 2.48,  9.8:  32 | 28 | 30; 30 | 21 | 21    7.5M, 2.38,  6.3:  62 | 52 | 52; 46 | 33 | 33
 //   4.0M, 1.91, 10.0:  32 | 27 | 31; 30 | 20 | 22    8.4M, 2.29, 10.5:  58 | 51 | 57; 49 | 32 | 36

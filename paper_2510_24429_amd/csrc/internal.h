@@ -428,7 +428,7 @@ void launch_permute(double *dst, const double *src, const int32_t *perm,
                     int64_t k, hipStream_t s);
 void launch_gather(double *dst, const double *src, const int32_t *idx,
                    int64_t k, hipStream_t s);
-// ... the same in FP64 (dst may be null) and rounded to FP32, 0 where idx < 0
+// ... the same in FP64 and rounded to FP32, 0 where idx < 0
 void launch_gather_pad(double *dst, float *dst32, const double *src,
                        const int32_t *idx, int64_t k, hipStream_t s);
 // The scaled values of M's buckets from M's.

@@ -769,7 +769,7 @@ __device__ __forceinline__ void bkt_fill(const Units &units,
 // thousands 256 lanes that multiply as they add, a bucket at most 64: added one
 // by one, FP32 sums of 400 to 5,000 products had an rms error of 1.42e-7 of their
 // size against 9.2e-8 in row blocks, and FP32 iterates of a power-law LP were 8%
-// further from 64 bits.)
+// further from 64 bits; so it is 9.0e-8, at the same times.)
 template <typename Acc>
 __device__ __forceinline__ Acc lane_sum(const Acc *s, int p, int p1, int G) {
     double t = 0.0;
@@ -2448,7 +2448,7 @@ __global__ __launch_bounds__(kWG) void k_gather_pad(
          i += (int64_t)gridDim.x * kWG) {
         const int p = idx[i];
         const double v = p < 0 ? 0.0 : src[p];
-        if (dst) dst[i] = v;
+        dst[i] = v;
         dst32[i] = (float)v;
     }
 }
@@ -2460,8 +2460,8 @@ void launch_gather_pad(double *dst, float *dst32, const double *src,
                        0, s, dst, dst32, src, idx, k);
 }
 
-// As k_gather_pad, of tiles: an entry's place in the CSR is its position in the
-// tile beyond the tile's first.
+// As k_gather_pad, of tiles (dst null: FP32 alone): an entry's place in the CSR is
+// its position in the tile beyond the tile's first.
 static __global__ __launch_bounds__(kWG) void k_gather_tiles(
     double *__restrict__ dst, float *__restrict__ dst32,
     const double *__restrict__ src, const int32_t *__restrict__ word,
