@@ -131,6 +131,7 @@ namespace {
 constexpr int kMaxDevices = 64;
 constexpr int64_t kSplitThreshold = (int64_t)1 << 20, kSplitChunk = (int64_t)1 << 16;
 constexpr int kSmallSteps = 4096;     // most iterations of one k_small launch
+constexpr int64_t kPlanEarly = 300000;    // (see pdhg_load)
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices] = {nullptr};
 
@@ -165,8 +166,13 @@ struct pdhg_ctx {
     DevCsr A, At;
     double *prod = nullptr;     // products of the push passes
     bool small64 = false, small32 = false;   // iterates in one workgroup
-    // planned tiles that go to the device at the first FP32 iteration (A, A^T)
-    HostBuckets later[2];
+    // tiles that go to the device at the first FP32 iteration (A, A^T): their
+    // plan, or what it is made from then
+    struct {
+        HostBuckets plan;
+        std::vector<int64_t> rp;
+        std::vector<int32_t> ci;
+    } later[2];
     bool asked[2] = {false, false};     // layouts that the tuning asked for
     // internal relabeling (rows and columns by decreasing length)
     int32_t *pr = nullptr;      // internal row -> original row of A
@@ -935,11 +941,20 @@ void apply_scaling(pdhg_ctx *c) {
 // The tiles of sides that only FP32 products run in, before the first of them
 // (without memory for them these products stay in row blocks).
 void ensure_f32_tiles(pdhg_ctx *c) {
+    std::future<HostBuckets> plan[2];
+    for (int k = 0; k < 2; ++k)
+        if (!c->later[k].rp.empty())
+            plan[k] = std::async(std::launch::async | std::launch::deferred, [c, k] {
+                const auto &l = c->later[k];
+                return build_tiles((int64_t)l.rp.size() - 1, l.rp.data(), l.ci.data(), 1, false);
+            });
     for (int k = 0; k < 2; ++k) {
-        if (c->later[k].buckets.empty()) continue;
+        if (!plan[k].valid() && c->later[k].plan.buckets.empty()) continue;
         DevCsr &M = k ? c->At : c->A;
-        out_of_memory([&] { upload_buckets(M, c->later[k], false, false); },
-                      [&] { free_buckets(M.bkt); });
+        out_of_memory([&] {
+            if (plan[k].valid()) c->later[k].plan = plan[k].get();
+            upload_buckets(M, c->later[k].plan, false, false);
+        }, [&] { free_buckets(M.bkt); });
         c->later[k] = {};
         if (M.bkt)
             launch_fill_buckets(M, c->stream);
@@ -1735,12 +1750,14 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
         const bool fa = c->layout_a != LAYOUT_CHOOSE, fat = c->layout_at != LAYOUT_CHOOSE;
         // tiles of an unpanelled side: planned while the arrays are uploaded;
         // where only FP32 products use them, the plan waits for the first FP32
-        // iteration (made only then, a first FP32 configure of 480,000 nonzeros
-        // took 5.1 ms instead of 2.7, and 2.0 without tiles)
+        // iteration.  From kPlanEarly nonzeros on the upload does not hide it,
+        // and it is made there (load and first configure, ms, planned here |
+        // there: 480,000 nonzeros FP64 9.8 | 8.4, FP32 10.5 | 10.6; 240,000 5.1 |
+        // 4.9, 5.4 | 6.0; 55,000 2.9 | 2.8, 2.9 | 3.3)
         const bool ta = la == LAYOUT_TILES && pa == 1, tat = lat == LAYOUT_TILES && pat == 1;
         auto plan = [&](bool on, int64_t rows, const std::vector<int64_t> &rp,
                         const std::vector<int32_t> &ci, bool force) {
-            return on
+            return on && (force || nnz >= kTileMin64 || nnz < kPlanEarly)
                        ? std::async(std::launch::async | std::launch::deferred, [&rp, &ci, rows, force] {
                              return build_tiles(rows, rp.data(), ci.data(), 1, force);
                          })
@@ -1825,8 +1842,12 @@ int pdhg_load(pdhg_ctx *c, int64_t m, int64_t n, int64_t nnz,
         for (int k = 0; k < 2; ++k) {
             auto &p = k ? plan_at : plan_a;
             if (!p.valid()) continue;
-            c->later[k] = p.get();
-            if (c->later[k].fragmented) c->later[k] = {};
+            c->later[k].plan = p.get();
+            if (c->later[k].plan.fragmented) c->later[k] = {};
+        }
+        if (!now && nnz >= kPlanEarly) {
+            if (ta && !fa) c->later[0] = {{}, std::move(R.a_rp), std::move(R.a_ci)};
+            if (tat && !fat) c->later[1] = {{}, std::move(R.at_rp), std::move(R.at_ci)};
         }
     };
     // without memory for buckets (up to 29 bytes a nonzero and side) the lean

@@ -210,6 +210,7 @@ int main(int argc, char **argv) {
     const std::vector<Case> all = {
         {"one workgroup", 300, 700, 5, {}},
         {"FP32 tiles", 8000, 20000, 5, {}},
+        {"FP32 tiles, planned late", 20000, 62000, 5, {}},
         {"tiles", 3000, 7000, 5, {{"layout_a", 1}, {"layout_at", 1}}},
         {"panelled tiles", 3000, 7000, 5, {{"layout_a", 1}, {"layout_at", 1}, {"panels_a", 4}, {"panels_at", 2}}},
         {"pushed", 3000, 7000, 5, {{"layout_a", 2}, {"layout_at", 2}}},

@@ -23,4 +23,4 @@ def test_out_of_memory_paths(tmp_path):
                        capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
     lines = r.stdout.strip().splitlines()
-    assert lines[-1] == "done" and len(lines) == 6 + 4 + 1 + 1 + 1
+    assert lines[-1] == "done" and len(lines) == 7 + 4 + 1 + 1 + 1

@@ -201,7 +201,7 @@ def test_pushed_products_through_whole_rounds(Solver):
             assert err(a, b) <= tol
 
 
-@pytest.mark.parametrize("m,n,k", [(8000, 20_000, 5), (50_000, 100_000, 8), (600, 1500, 5)])
+@pytest.mark.parametrize("m,n,k", [(8000, 20_000, 5), (30_000, 80_000, 5), (50_000, 100_000, 8), (600, 1500, 5)])
 def test_products_do_not_depend_on_earlier_calls(Solver, m, n, k):
     """Products in either precision keep their bits over an FP32 configure and
     an FP32 unrolled pass, which prepare what only FP32 iterations use (sides
